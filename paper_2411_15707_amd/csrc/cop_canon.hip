@@ -49,22 +49,6 @@ __device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v)
 }
 __device__ __forceinline__ void tie64(uint64_t &x) { asm volatile("" : "+v"(x)); }
 
-// bytes (a0 a1 a2 a3), (b0 ..), (c0 ..), (d0 ..) -> (a0 b0 c0 d0), (a1 b1 c1 d1), ...
-// (a 4 x 4 byte transpose: word j of the result holds byte j of each input)
-__device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, uint32_t d,
-                                           uint32_t (&t)[4])
-{
-    // v_perm_b32(hi, lo, sel): byte i of the result is byte sel_i of the 8 bytes {hi, lo}
-    const uint32_t ab_lo = __builtin_amdgcn_perm(b, a, 0x05010400u);   // a0 b0 a1 b1
-    const uint32_t ab_hi = __builtin_amdgcn_perm(b, a, 0x07030602u);   // a2 b2 a3 b3
-    const uint32_t cd_lo = __builtin_amdgcn_perm(d, c, 0x05010400u);   // c0 d0 c1 d1
-    const uint32_t cd_hi = __builtin_amdgcn_perm(d, c, 0x07030602u);   // c2 d2 c3 d3
-    t[0] = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x05040100u);           // a0 b0 c0 d0
-    t[1] = __builtin_amdgcn_perm(cd_lo, ab_lo, 0x07060302u);           // a1 b1 c1 d1
-    t[2] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x05040100u);
-    t[3] = __builtin_amdgcn_perm(cd_hi, ab_hi, 0x07060302u);
-}
-
 // FULL: m is a multiple of 128.  SHARED: several row blocks per column tile (m > 128); they
 // start at the same k-block and load the ciphertext without the streaming hint, so that the
 // tile is found in the L2 of their XCD by all but the first.

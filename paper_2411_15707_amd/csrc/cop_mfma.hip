@@ -34,65 +34,6 @@
 namespace nimbus {
 
 // ---------------------------------------------------------------------------
-// setup phase: canonical ctW -> signed byte planes of the centred residues
-// one thread fills the 16 bytes of one lane slot in each of the DQ planes of a tile
-// ---------------------------------------------------------------------------
-template <int DQ>
-__global__ __launch_bounds__(256) void prepare_planes_kernel(
-    const uint64_t *__restrict__ ctW, int k, uint32_t C, int N, int L, LimbTable limbs,
-    int KB, uint64_t total, uint4 *__restrict__ planes)
-{
-    const uint64_t gid = (uint64_t)blockIdx.x * 256u + threadIdx.x;
-    if (gid >= total) return;
-    const uint32_t lane = (uint32_t)(gid & 63u);
-    const uint64_t tile = gid >> 6;                 // ct * KB + kb
-    const uint32_t kb = (uint32_t)(tile % (uint64_t)KB);
-    const uint32_t ct = (uint32_t)(tile / (uint64_t)KB);
-    const uint32_t col = ct * kTile + (lane & 31u);
-    const int kbase = (int)kb * kTile + (int)(lane >> 5) * 16;
-    const uint64_t q = limbs.limb[(col / (uint32_t)N) % (uint32_t)L].q;
-    const uint64_t half = (q - 1) >> 1;
-
-    uint64_t bias = 0;                              // 0x80 in each of the DQ low bytes
-#pragma unroll
-    for (int d = 0; d < DQ; ++d) bias |= (uint64_t)0x80 << (8 * d);
-
-    uint32_t w[DQ][4];
-#pragma unroll
-    for (int d = 0; d < DQ; ++d) { w[d][0] = w[d][1] = w[d][2] = w[d][3] = 0; }
-
-#pragma unroll
-    for (int b = 0; b < 16; ++b) {
-        const int i = kbase + b;
-        if (i < k) {
-            const uint64_t c = ctW[(size_t)i * C + col];
-            const uint64_t cc = c > half ? c - q : c;          // two's complement of c'
-            // c' + bias has unsigned bytes dq_b + 128; flipping bit 7 gives dq_b as int8
-            const uint64_t v = (cc + bias) ^ bias;
-#pragma unroll
-            for (int d = 0; d < DQ; ++d)
-                w[d][b >> 2] |= (uint32_t)((v >> (8 * d)) & 0xffu) << (8 * (b & 3));
-        }
-    }
-#pragma unroll
-    for (int d = 0; d < DQ; ++d)
-        planes[(tile * DQ + d) * 64u + lane] = make_uint4(w[d][0], w[d][1], w[d][2], w[d][3]);
-}
-
-// S[col] = sum_i ctW[i][col] mod q
-__global__ __launch_bounds__(256) void column_sums_kernel(
-    const uint64_t *__restrict__ ctW, int k, uint32_t C, int N, int L, LimbTable limbs,
-    uint64_t *__restrict__ colsum)
-{
-    const uint32_t col = blockIdx.x * 256u + threadIdx.x;
-    if (col >= C) return;
-    const Limb P = limbs.limb[(col / (uint32_t)N) % (uint32_t)L];
-    uint64_t hi = 0, lo = 0;
-    for (int i = 0; i < k; ++i) add128(hi, lo, 0, ctW[(size_t)i * C + col]);
-    colsum[col] = barrett128(hi, lo, P);            // k * q < 2^(b+63)
-}
-
-// ---------------------------------------------------------------------------
 // per call: X -> DX signed byte planes in A-operand tile order
 // ---------------------------------------------------------------------------
 // (blockIdx.y: the problem, when the shares of several calls are staged in one launch)
@@ -763,30 +704,6 @@ bool mfma_supported(const Problem &p)
     // 2^32 q: the previous pass of a wide share); the floating-point quotient needs it
     // below 2^47 * q
     return bias_shift(p) + 2 <= 47;
-}
-
-template <int DQ>
-static hipError_t prepare_impl(const Problem &p, const uint64_t *ctW, void *prepared,
-                               hipStream_t stream)
-{
-    const int KB = kblocks(p.k);
-    const uint32_t CT = (uint32_t)(p.C / kTile);
-    const uint64_t total = (uint64_t)CT * KB * 64;
-    uint4 *planes = (uint4 *)prepared;
-    uint64_t *colsum = (uint64_t *)((char *)prepared + (size_t)CT * KB * DQ * kTileBytes);
-    const hipError_t e =
-        launch(prepare_planes_kernel<DQ>, dim3((unsigned)((total + 255) / 256)), dim3(256), stream,
-               ctW, p.k, (uint32_t)p.C, p.N, p.L, p.limbs, KB, total, planes);
-    if (e != hipSuccess) return e;
-    return launch(column_sums_kernel, dim3((unsigned)((p.C + 255) / 256)), dim3(256), stream,
-                  ctW, p.k, (uint32_t)p.C, p.N, p.L, p.limbs, colsum);
-}
-
-hipError_t launch_prepare(const Problem &p, const uint64_t *ctW, void *prepared,
-                          hipStream_t stream)
-{
-    if (planes_q(p.q_bits_max) == 7) return prepare_impl<7>(p, ctW, prepared, stream);
-    return prepare_impl<8>(p, ctW, prepared, stream);
 }
 
 template <int DX>
