@@ -156,6 +156,29 @@ static hipError_t matmul_all(const Problem &p, const void *staged, const void *p
     return launch_cop_mfma(half_problem(p, 32), staged, prepared, mask, out, out, stream);
 }
 
+// both steps of a call that stages and multiplies.  With few rows the kernel takes the shares
+// themselves and leaves their planes in the workspace on the way.
+static hipError_t stage_and_matmul(const Problem &p, const uint64_t *X, void *workspace,
+                                   const void *prepared, const uint64_t *mask, uint64_t *out,
+                                   hipStream_t stream)
+{
+    const bool wide = p.x_bits > 32;
+    const Problem lo = half_problem(p, wide ? 32 : p.x_bits), hi = half_problem(p, p.x_bits - 32);
+    if (!thin_raw_applies(lo) || (wide && !thin_raw_applies(hi))) {
+        const hipError_t e = stage_all(p, X, workspace, stream);
+        return e == hipSuccess ? matmul_all(p, workspace, prepared, mask, out, stream) : e;
+    }
+    const void *const staged_lo = workspace;
+    if (wide) {
+        const void *const staged_hi = (const char *)workspace + half_bytes(p.m, p.k, 32);
+        const uint64_t *const no_mask = nullptr;
+        const hipError_t e =
+            launch_cop_thin(hi, 1, X, 32, &staged_hi, &prepared, &no_mask, nullptr, &out, stream);
+        if (e != hipSuccess) return e;
+    }
+    return launch_cop_thin(lo, 1, X, 0, &staged_lo, &prepared, &mask, wide ? out : nullptr, &out, stream);
+}
+
 }  // namespace nimbus
 
 using namespace nimbus;
@@ -377,9 +400,7 @@ static int matmul_prepared_impl(const uint64_t *X, int m, int k, int x_bits,
             overlaps(workspace, ws_bytes, prepared, prepared_bytes_of(p)))
             return NIMBUS_COP_ERR_INVALID_ARG;
     }
-    hipError_t e = stage_all(p, X, workspace, (hipStream_t)stream);
-    if (e != hipSuccess) return NIMBUS_COP_ERR_LAUNCH;
-    e = matmul_all(p, workspace, prepared, mask, out, (hipStream_t)stream);
+    const hipError_t e = stage_and_matmul(p, X, workspace, prepared, mask, out, (hipStream_t)stream);
     return e == hipSuccess ? NIMBUS_COP_OK : NIMBUS_COP_ERR_LAUNCH;
 }
 

@@ -73,6 +73,13 @@ hipError_t launch_cop_mfma(const Problem &p, const void *staged, const void *pre
                            const uint64_t *mask, const uint64_t *prev, uint64_t *out,
                            hipStream_t stream);
 bool mfma_supported(const Problem &p);
+// few rows (cop_thin.hip): from staged shares, or (X, half_shift) from the shares themselves
+bool thin_applies(const Problem &p);
+bool thin_raw_applies(const Problem &p);
+hipError_t launch_cop_thin(const Problem &p, int count, const uint64_t *X, int half_shift,
+                           const void *const *staged, const void *const *prepared,
+                           const uint64_t *const *masks, const uint64_t *prev, uint64_t *const *outs,
+                           hipStream_t stream);
 // matrix-core kernel on the canonical layout (cop_canon.hip)
 bool canon_supported(const Problem &p);
 hipError_t launch_cop_canon(const Problem &p, const uint64_t *X, const uint64_t *ctW,

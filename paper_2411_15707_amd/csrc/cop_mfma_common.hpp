@@ -262,46 +262,28 @@ __device__ __forceinline__ void wait_vmem_loads(int n)
 
 // ---------------------------------------------------------------------------
 // epilogue: rebuild the sums from the diagonals, add the constant and the mask, reduce, store
-//   mask, prev, out  the problem's mask (or null), the result of the pass over the upper share
-//              halves (or null) and its output, [m][C] each
-//   acc        the wave's ND = DX + DQ - 1 accumulator tiles (32 x 32 outputs: element r of
-//              the lane is row row0 + 8 (r / 4) + r % 4, column col)
-//   limb       limb of the wave's 32 columns;  colsum_S  sum of the column's residues mod q
+//   D(d, r)    diagonal d (< ND = DX + DQ - 1) of the lane's element r (< NE)
+//   roff(r)    row of element r minus row0 (wave-uniform)
+//   mask_of(r) the mask word of element r, 0 without a mask
+//   prev, out  the result of the pass over the upper share halves (or null) and the problem's
+//              output, [m][C] each
+//   limb       limb of the wave's columns;  colsum_S  sum of the column's residues mod q
 //   row0, col  the lane's first row and its column in the whole output
-//   mask_tile  MASKLDS: the lane's word of row0 in the workgroup's mask tile in LDS
 // ---------------------------------------------------------------------------
-template <int ND, bool FULL, bool MASKLDS>
-__device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
-                                             const uint64_t *mask, const uint64_t *prev,
-                                             uint64_t *out, uint32_t limb, uint64_t colsum_S,
-                                             int row0, uint32_t col, const unsigned char *mask_tile)
+template <int ND, int NE, bool FULL, typename Digit, typename RowOf, typename MaskOf>
+__device__ __forceinline__ void cop_finish(Digit D, RowOf roff, MaskOf mask_of, const MfmaArgs &a,
+                                           const uint64_t *prev, uint64_t *out, uint32_t limb,
+                                           uint64_t colsum_S, int row0, uint32_t col)
 {
     const uint64_t q = a.q[limb];
     const double qinv = a.qinv[limb];
-    // every load of the epilogue first (mask words, then the column sum), so that their
-    // latencies overlap
-    // element r of the lane is row row0 + roff(r); addresses are the lane's address of
-    // row0 plus a wave-uniform multiple of the row length
-    auto roff = [](int r) -> int { return 8 * (r >> 2) + (r & 3); };
+    // addresses are the lane's address of row0 plus a wave-uniform multiple of the row length
     const size_t lane_elem = (size_t)row0 * a.C + col;
-    const uint64_t *const mask0 = mask ? mask + lane_elem : nullptr;
     const uint64_t *const prev0 = prev ? prev + lane_elem : nullptr;
     uint64_t *const out0 = out + lane_elem;
-    uint64_t mk[16];                                // read once: streaming loads
-    if constexpr (MASKLDS) {
-        // the tile is in LDS, row-major [128][64] words; mask_tile is the lane's word of row0
+    uint64_t mk[NE];                                // every load of the epilogue first
 #pragma unroll
-        for (int r = 0; r < 16; ++r) mk[r] = *(const uint64_t *)(mask_tile + roff(r) * 512);
-    } else if (mask) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            mk[r] = (FULL || row0 + roff(r) < a.m)
-                        ? __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C])
-                        : 0;
-    } else {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mk[r] = 0;
-    }
+    for (int r = 0; r < NE; ++r) mk[r] = mask_of(r);
     uint64_t cst_hi = a.cst_hi[limb], cst_lo = a.cst_lo[limb];
     {
         const uint64_t S = colsum_S;
@@ -340,21 +322,20 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
 #pragma unroll
     for (int d = 0; d < 4; ++d) asm volatile("" : "+s"(pow256[d]));
     static_assert(ND >= 8, "two full groups of diagonals");
-    int64_t g0[16];
-    uint32_t g1_lo[16];
-    double v_hi[16];                                // 2^32 g1 + 2^64 (...), in double
+    int64_t g0[NE];
+    uint32_t g1_lo[NE];
+    double v_hi[NE];                                // 2^32 g1 + 2^64 (...), in double
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-        auto D = [&](int d) -> int32_t { return acc[d][r]; };
+    for (int r = 0; r < NE; ++r) {
         int64_t s0 = c0, s1 = c1;
 #pragma unroll
-        for (int d = 0; d < 4; ++d) s0 += (int64_t)D(d) * (int64_t)pow256[d];
+        for (int d = 0; d < 4; ++d) s0 += (int64_t)D(d, r) * (int64_t)pow256[d];
 #pragma unroll
-        for (int d = 4; d < 8; ++d) s1 += (int64_t)D(d) * (int64_t)pow256[d - 4];
+        for (int d = 4; d < 8; ++d) s1 += (int64_t)D(d, r) * (int64_t)pow256[d - 4];
         double top = k2, scale = two32 * two32;
 #pragma unroll
         for (int d = 8; d < ND; ++d) {
-            top = fma((double)D(d), scale, top);
+            top = fma((double)D(d, r), scale, top);
             scale *= 256.0;
         }
         g0[r] = s0;
@@ -365,7 +346,7 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
     // the second half stays behind the first: volatile statements keep their order, and
     // these make the first half's results and the loaded words pass through them
 #pragma unroll
-    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(g0[r]), "+v"(g1_lo[r]), "+v"(v_hi[r]));
+    for (int r = 0; r < NE; ++r) asm volatile("" : "+v"(g0[r]), "+v"(g1_lo[r]), "+v"(v_hi[r]));
     // Shares wider than 32 bits take two passes, x = x_lo + 2^32 x_hi: the second one adds
     // 2^32 times the (reduced) result of the pass over the upper halves, read from where
     // this pass writes its own result (prev may be out: an element is read and written by
@@ -373,12 +354,12 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
     // V below 2^47 q.  (A block of its own behind one wave-uniform branch: the narrow path
     // does not execute any of it.)
     if (prev) {
-        uint64_t pv[16];
+        uint64_t pv[NE];
 #pragma unroll
-        for (int r = 0; r < 16; ++r)
+        for (int r = 0; r < NE; ++r)
             pv[r] = (FULL || row0 + roff(r) < a.m) ? __builtin_nontemporal_load(&prev0[(size_t)roff(r) * a.C]) : 0;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < NE; ++r) {
             g1_lo[r] += (uint32_t)pv[r];
             // exact below 2^53; above, off by < 2^-53 of a term that is < 2^32 q
             v_hi[r] = fma(fma((double)(uint32_t)(pv[r] >> 32), two32, (double)(uint32_t)pv[r]),
@@ -387,7 +368,7 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
         asm volatile("" ::: "memory");
     }
 #pragma unroll
-    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(mk[r]));
+    for (int r = 0; r < NE; ++r) asm volatile("" : "+v"(mk[r]));
     // wave-uniform constants of the quotient estimate, kept in vector registers
     // (the constant starts out in scalar registers behind an opaque statement: a caller that
     // runs this epilogue in a loop would otherwise have it built once in front of the loop
@@ -399,7 +380,7 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
     uint32_t q_hi_v = q_hi;
     asm volatile("" : "+v"(qinv_v), "+v"(magic_c), "+v"(q_hi_v));
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
+    for (int r = 0; r < NE; ++r) {
         const int64_t t0 = g0[r] + (int64_t)mk[r];          // |g0| < 2^56, mask < 2^62
         const uint32_t lo_lo = (uint32_t)t0;
         const uint32_t lo_hi = (uint32_t)(t0 >> 32) + g1_lo[r];
@@ -441,6 +422,29 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
         // not sit dirty in L2 need no write-back when the kernel ends)
         if (FULL || row0 + roff(r) < a.m) __builtin_nontemporal_store(res, &out0[(size_t)roff(r) * a.C]);
     }
+}
+
+// the same for a wave's 32 x 32 tile:
+//   acc        ND accumulator tiles (element r of the lane is row row0 + 8 (r / 4) + r % 4)
+//   mask       the problem's mask (or null)
+//   mask_tile  MASKLDS: the lane's word of row0 in the workgroup's mask tile in LDS
+template <int ND, bool FULL, bool MASKLDS>
+__device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
+                                             const uint64_t *mask, const uint64_t *prev,
+                                             uint64_t *out, uint32_t limb, uint64_t colsum_S,
+                                             int row0, uint32_t col, const unsigned char *mask_tile)
+{
+    auto roff = [](int r) -> int { return 8 * (r >> 2) + (r & 3); };
+    const uint64_t *const mask0 = mask ? mask + ((size_t)row0 * a.C + col) : nullptr;
+    cop_finish<ND, 16, FULL>(
+        [&](int d, int r) -> int32_t { return acc[d][r]; }, roff,
+        [&](int r) -> uint64_t {
+            // (the tile is in LDS, row-major [128][64] words; else read once: a streaming load)
+            if constexpr (MASKLDS) return *(const uint64_t *)(mask_tile + roff(r) * 512);
+            if (!mask0) return 0;
+            return FULL || row0 + roff(r) < a.m ? __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C]) : 0;
+        },
+        a, prev, out, limb, colsum_S, row0, col);
 }
 
 }  // namespace nimbus

@@ -1,0 +1,430 @@
+// Matrix-core (int8 MFMA) kernel of the COP accumulation for few token rows (m <= 32), gfx950:
+// the same contraction, operand bytes and epilogue as cop_mfma.hip (Algorithm 1 step 2 + step 4
+// of the paper), laid out for a call that is nothing but a pass over the weights.
+//
+// What bounds it: the bytes of the prepared weights (m = 1, 768 x 16384 residues of 54 bits:
+// 88 MB, 14 us at the 6.3 TB/s that a streaming read reaches; the products of 16 rows take a
+// fifth of that) and, with few columns, what is in flight of them.  So nothing is shared and nothing is synchronised in the loop: a wave owns 16
+// columns and a slice of k, and its operand tiles come from memory straight into the registers
+// the products read them from, PD stages of 64 k ahead.  With eight waves of 7 KB a stage that
+// keeps up to 224 KB in flight per compute unit, and whatever the wave waits for is its own.
+//
+// v_mfma_i32_16x16x64_i8: 16 rows x 16 columns x 64 k, a stage is two k-blocks of the prepared
+// layout.  Lane l holds row (or column) l % 16 and the k-slots 16 (l / 16) .. +15 of the stage:
+// 16 bytes that lie together in the 32 x 32 operand tiles of the layout (k-block l / 32 of the
+// stage, half (l / 16) % 2), so a lane's operand is one 16-byte load at its own address.
+//
+// A workgroup is eight waves, CGW column groups x KS slices of k (CGW KS = 8).  Slices are for
+// weights with too few columns to fill the chip: the host takes as many as bring the number of
+// workgroups to the number of compute units.  The slices' sums meet in LDS once, at the end.
+//
+// Shares: staged planes (the batch and the staged entry points), read like the weights; or, for
+// up to 16 rows of the entry points that stage and multiply in one call, the raw words (RAW):
+// the workgroup splits them into byte planes in LDS while its first weights are on their way,
+// and the staging launch and the gap behind it go away.  The planes are left in the workspace
+// all the same (workgroup b writes the stages b, b + grid, ...), as that entry point promises.
+//
+// Measured against the 128 x 64 tiles of cop_mfma.hip behind a staging launch (us a call, 20-bit
+// shares, 54-bit moduli): 1 x 768 x 16384 21.7 -> 17.5, 16 x 768 x 16384 22.1 -> 19.4, 4 x 768 x
+// 49152 57.4 -> 49.4, 32 x 768 x 4096 20.2 -> 12.5, 1 x 3072 x 8192 56.0 -> 29.8; no better with 17
+// to 32 rows and 16384 columns (22.8 and 22.6).  With a third and a fourth 16-row tile the shares'
+// planes cost more than the tiles of cop_mfma.hip (64 x 768 x 16384: 33 us and 28).
+#include "cop_mfma_common.hpp"
+
+namespace nimbus {
+
+struct ThinArgs {
+    const uint64_t *X;        // RAW: [m][k]
+    uint4 *staged;            // RAW: where the planes are left, [KB][DX][64] uint4 (one row tile)
+    int k;
+    int half_shift;           // RAW: 0 or 32, which half of a share
+    uint32_t log_ks;          // KS = 2^log_ks
+    uint32_t quads_magic;     // RAW: ceil(2^32 / Q), Q = 16 ceil(KB / 2) four-word items of a row: x / Q = umulhi(x, .)
+};
+
+constexpr int kThinRows = 32;
+constexpr int kThinStage = 64;                          // k of a stage
+constexpr int kThinSharesLds = 144 * 1024;
+
+// where a wave's operands of the shares come from
+enum ThinShares {
+    kDirect,    // staged planes, read like the weights, per wave
+    kCopied,    // staged planes, brought into LDS once per workgroup
+    kRaw        // the shares themselves, split into planes in LDS once per workgroup
+};
+
+template <int DX, int DQ, int RT16, ThinShares FROM>
+struct Thin {
+    static constexpr int ND = DX + DQ - 1;
+    static constexpr int A_REGS = DX * 4 * RT16, B_REGS = DQ * 4, ACC_REGS = ND * 4 * RT16;
+    // stages in flight per wave: what 256 registers hold next to the accumulators, four at most
+    static constexpr int STAGE_REGS = B_REGS + (FROM == kDirect ? A_REGS : 0);
+    static constexpr int FIT = (256 - 40 - ACC_REGS - (FROM == kDirect ? 0 : 20)) / STAGE_REGS;
+    static constexpr int PD = FIT > 4 ? 4 : FIT < 2 ? 2 : FIT;
+    // planes of the shares, [stage][16-row tile][plane][64 lanes][16 B]
+    static constexpr int A_LDS = FROM == kDirect ? 0 : kThinSharesLds;
+    // the slices' sums meet TP tiles at a time: two where eight waves' sums of two fit the LDS
+    static constexpr int TP = RT16 > 1 && ND <= 9 ? 2 : 1;
+    static constexpr int SUM_LDS = 8 * ND * TP * 1024;
+    static constexpr int PHASES = (RT16 + TP - 1) / TP;
+    static constexpr int LDS = A_LDS > SUM_LDS ? A_LDS : SUM_LDS;
+};
+
+__device__ __forceinline__ v4i load_operand(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, bool stream)
+{
+    return stream ? __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 2)
+                  : __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
+}
+
+template <int DX, int DQ, int RT16, ThinShares FROM>
+__global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, const BatchPtrs b, const ThinArgs t)
+{
+    using T_ = Thin<DX, DQ, RT16, FROM>;
+    constexpr int ND = T_::ND, PD = T_::PD;
+    constexpr bool RAW = FROM == kRaw, IN_LDS = FROM != kDirect;
+    static_assert(RT16 <= 2, "one row tile of the staged planes");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[T_::LDS];
+
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t log_cgw = 3u - t.log_ks;
+    const uint32_t cg = (blockIdx.x << log_cgw) + ((uint32_t)wave & ((1u << log_cgw) - 1u));
+    const uint32_t ks = (uint32_t)wave >> log_cgw;
+    const bool active = cg < a.CT * 2u;                 // (the last workgroup may have columns to spare)
+    const ProblemPtrs pp = b.prob[blockIdx.y];
+    const int KB = a.KB;
+    const uint32_t S = ((uint32_t)KB + 1u) >> 1;
+    // this wave's stages: s0 .. s1-1, started at a place that follows from the column tile so
+    // that waves which walk equally spaced regions do not ask the same channels at one moment
+    const uint32_t s0 = (S * ks) >> t.log_ks, s1 = (S * (ks + 1u)) >> t.log_ks;
+    const uint32_t len = active ? s1 - s0 : 0u;
+    const uint32_t j = (uint32_t)lane >> 4, r16 = (uint32_t)lane & 15u;
+    const uint32_t ct = cg >> 1, c16 = cg & 1u;
+
+    // Element e of the lane in 16-row tile i is row 16 i + 4 j + e.  One slice: the wave finishes
+    // every element.  Several: their sums meet TP tiles (4 TP elements) at a time, and wave ks of a
+    // column group finishes the elements ks ne .. of them, ne = max(1, 4 TP / KS).
+    const uint32_t col = cg * 16u + r16;
+    const auto share = [&](int phase, uint32_t &tile, uint32_t &e0) -> uint32_t {   // elements of this wave
+        const uint32_t tiles = RT16 - phase * T_::TP < T_::TP ? RT16 - phase * T_::TP : T_::TP;
+        const uint32_t ne = (4u * tiles) >> t.log_ks ? (4u * tiles) >> t.log_ks : 1u;
+        tile = phase * T_::TP + ks * ne / 4u;
+        e0 = ks * ne % 4u;
+        return active && ks * ne < 4u * tiles ? ne : 0u;
+    };
+    auto mask_word = [&](uint32_t row) -> uint64_t {
+        return pp.mask != nullptr && (int)row < a.m ? __builtin_nontemporal_load(&pp.mask[(size_t)row * a.C + col]) : 0;
+    };
+
+    // ---- operand addresses ----
+    // (reads past the last k-block lie past the end of the descriptor and give zero weights:
+    // whatever the shares' operand holds there, the products vanish)
+    constexpr uint32_t kPastEnd = 0xf0000000u;
+    constexpr uint32_t kBStage = 2u * DQ * kTileBytes, kAStage = 2u * DX * kTileBytes;
+    const uint32_t b_bytes = (uint32_t)KB * DQ * kTileBytes;
+    const uint32_t a_bytes = (uint32_t)KB * DX * kTileBytes;
+    const __amdgpu_buffer_rsrc_t rsrc_b = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)((const unsigned char *)pp.planes + (size_t)(active ? ct : 0u) * b_bytes), 0, b_bytes, 0x00027000);
+    const uint32_t lane_b = (j >> 1) * (DQ * kTileBytes) + ((j & 1u) * 32u + c16 * 16u + r16) * 16u;
+    const __amdgpu_buffer_rsrc_t rsrc_a =
+        __builtin_amdgcn_make_buffer_rsrc((void *)pp.xd, 0, a_bytes, 0x00027000);
+    const uint32_t lane_a = (j >> 1) * (DX * kTileBytes) + ((j & 1u) * 32u + r16) * 16u;
+
+    v4i xb[PD][DQ], xs[PD][IN_LDS ? 1 : RT16][DX];
+    uint32_t s_load = s0 + (len ? ct % len : 0u);       // next stage to ask for
+    uint32_t asked = 0;
+    auto next_stage = [&](uint32_t s) { return s + 1u == s1 ? s0 : s + 1u; };
+    // one more stage into register set p.  Past the last one the loads are issued all the same, at
+    // an offset behind the descriptors' end (no memory is read): the compiler's counted waits then
+    // see the same loads on every path through the loop.
+    auto ask = [&](auto p_c) {
+        constexpr int p = decltype(p_c)::value;
+        const uint32_t ob = asked < len ? lane_b + s_load * kBStage : kPastEnd;
+        static_for<0, DQ>([&](auto d) {
+            xb[p][decltype(d)::value] = load_operand(rsrc_b, ob + decltype(d)::value * kTileBytes, true);
+        });
+        if constexpr (!IN_LDS) {
+            const uint32_t oa = asked < len ? lane_a + s_load * kAStage : kPastEnd;
+            static_for<0, RT16 * DX>([&](auto i_c) {
+                constexpr int i = decltype(i_c)::value / DX, d = decltype(i_c)::value % DX;
+                xs[p][i][d] = load_operand(rsrc_a, oa + i * 256u + d * kTileBytes, false);
+            });
+        }
+        s_load = next_stage(s_load);
+        ++asked;
+    };
+    const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(RAW ? t.X : (const uint64_t *)pp.xd), 0, (uint32_t)a.m * (uint32_t)t.k * 8u, 0x00027000);
+    // ---- RAW: four consecutive k of a row per thread and turn, split into byte planes in LDS ----
+    const uint32_t quads = S * (kThinStage / 4);        // of a row
+    const uint32_t items = (uint32_t)a.m * quads;
+    auto read_quad = [&](uint32_t at, v4i (&w)[2]) {
+        const uint32_t row = __umulhi(at, t.quads_magic), k0 = (at - row * quads) * 4u;
+        const uint32_t off = at < items ? (row * (uint32_t)t.k + k0) * 8u : kPastEnd;
+        // (words past the row are dropped by split_quad, words past the end read as zero)
+        w[0] = load_operand(rsrc_x, off, false);
+        w[1] = load_operand(rsrc_x, off + 16u, false);
+    };
+    auto split_quad = [&](uint32_t at, const v4i (&w)[2]) {
+        if (at >= items) return;
+        const uint32_t row = __umulhi(at, t.quads_magic), kq = at - row * quads;
+        uint32_t x[4], w4[4];
+        const bool upper = t.half_shift != 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i)
+            x[i] = kq * 4u + i >= (uint32_t)t.k ? 0u
+                   : (uint32_t)(upper ? w[i >> 1][2 * (i & 1) + 1] : w[i >> 1][2 * (i & 1)]) ^ a.offx;
+        transpose4(x[0], x[1], x[2], x[3], w4);
+        // stage kq / 16, 16-row tile row / 16, lane 16 (kq / 4 % 4) + row % 16, word kq % 4
+        const uint32_t first =
+            (((kq >> 4) * RT16 + (row >> 4)) * (DX * 64u) + ((kq >> 2) & 3u) * 16u + (row & 15u)) * 4u + (kq & 3u);
+#pragma unroll
+        for (int d = 0; d < DX; ++d) ((uint32_t *)lds)[first + d * 256u] = w4[d];
+    };
+    // ---- copied: 16 bytes of a staged plane per thread and turn ----
+    const uint32_t chunks = S * (RT16 * DX * 64u);
+    auto read_chunk = [&](uint32_t at) -> v4i {
+        const uint32_t l = at & 63u, d = at / 64u % DX, i = at / (64u * DX) % RT16, s = at / (64u * DX * RT16);
+        const uint32_t kb = 2u * s + (l >> 5);
+        const uint32_t off = (kb * DX + d) * kTileBytes + (((l >> 4) & 1u) * 32u + i * 16u + (l & 15u)) * 16u;
+        return load_operand(rsrc_a, at < chunks && kb < (uint32_t)KB ? off : kPastEnd, false);
+    };
+    auto keep_chunk = [&](uint32_t at, v4i v) {
+        if (at < chunks) ((v4i *)lds)[at] = v;
+    };
+    // The turns of a thread, U at a time.  The first U are asked for in front of the weights: loads
+    // come back in order.
+    if constexpr (RAW) {
+        constexpr uint32_t U = 2;
+        v4i w[U][2];
+        static_for<0, U>([&](auto u) { read_quad(threadIdx.x + 512u * decltype(u)::value, w[decltype(u)::value]); });
+        static_for<0, PD>([&](auto p) { ask(p); });
+        for (uint32_t at = threadIdx.x; at < items;) {
+            static_for<0, U>([&](auto u) { split_quad(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+            at += 512u * U;
+            if (at < items)
+                static_for<0, U>([&](auto u) { read_quad(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+        }
+        __syncthreads();
+    } else if constexpr (FROM == kCopied) {
+        constexpr uint32_t U = 4;
+        v4i w[U];
+        static_for<0, U>([&](auto u) { w[decltype(u)::value] = read_chunk(threadIdx.x + 512u * decltype(u)::value); });
+        static_for<0, PD>([&](auto p) { ask(p); });
+        for (uint32_t at = threadIdx.x; at < chunks;) {
+            static_for<0, U>([&](auto u) { keep_chunk(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+            at += 512u * U;
+            if (at < chunks)
+                static_for<0, U>([&](auto u) { w[decltype(u)::value] = read_chunk(at + 512u * decltype(u)::value); });
+        }
+        __syncthreads();
+    } else {
+        static_for<0, PD>([&](auto p) { ask(p); });
+    }
+    if constexpr (RAW) {
+        // the planes as nimbus_cop_stage_shares leaves them: rows past m are zero
+        for (uint32_t s = blockIdx.x; s < S; s += gridDim.x) {
+            for (uint32_t i = threadIdx.x; i < 2u * DX * 64u; i += 512u) {
+                const uint32_t kb = 2u * s + i / (DX * 64u), d = i / 64u % DX, l = i & 63u;
+                const uint32_t row = l & 31u, half = (i / (DX * 64u)) * 2u + (l >> 5);
+                uint4 v = {0, 0, 0, 0};
+                if (row < (uint32_t)a.m)
+                    v = ((const uint4 *)lds)[((s * RT16 + (row >> 4)) * DX + d) * 64u + half * 16u + (row & 15u)];
+                if (kb < (uint32_t)KB) t.staged[((size_t)kb * DX + d) * 64u + l] = v;
+            }
+        }
+    }
+
+    // ---- the epilogue's operands: asked for behind the first weights, used after the last ----
+    uint64_t mk[T_::PHASES][4 * T_::TP];
+    const uint64_t colsum_S = active ? pp.colsum[col] : 0;
+#pragma unroll
+    for (int ph = 0; ph < T_::PHASES; ++ph) {
+        uint32_t tile, e0;
+        const uint32_t ne = share(ph, tile, e0);
+#pragma unroll
+        for (uint32_t u = 0; u < 4 * T_::TP; ++u)
+            mk[ph][u] = u < ne ? mask_word(16u * (tile + (e0 + u) / 4u) + 4u * j + (e0 + u) % 4u) : 0;
+    }
+    uint32_t limb;
+    {
+        const uint32_t blk = (cg * 16u) >> a.log_n;
+        limb = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
+        limb = __builtin_amdgcn_readfirstlane(limb);
+    }
+
+    // ---- the loop ----
+    v4i acc[ND][RT16];
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+        for (int i = 0; i < RT16; ++i) acc[d][i] = v4i{0, 0, 0, 0};
+    uint32_t s_use = s0 + (len ? ct % len : 0u);
+    // (the shares' planes in LDS are written for the rows below m only; for rows past m any row's
+    // bytes will do, their sums are not stored)
+    uint32_t a_row[RT16];
+#pragma unroll
+    for (int i = 0; i < RT16; ++i) {
+        const uint32_t last = (uint32_t)a.m - 1u - 16u * i;     // of this tile, m > 16 (RT16 - 1)
+        a_row[i] = r16 > last ? last : r16;
+    }
+    auto products = [&](auto p_c) {
+        constexpr int p = decltype(p_c)::value;
+        const v4i *const at = (const v4i *)lds + s_use * (RT16 * DX * 64u) + j * 16u;
+        static_for<0, DX * RT16>([&](auto x_c) {
+            constexpr int i = decltype(x_c)::value % RT16, dx = decltype(x_c)::value / RT16;
+            v4i x;
+            if constexpr (IN_LDS) x = at[(i * DX + dx) * 64 + a_row[i]];
+            else x = xs[p][i][dx];
+            static_for<0, DQ>([&](auto d_c) {
+                constexpr int dq = decltype(d_c)::value;
+                acc[dx + dq][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(x, xb[p][dq], acc[dx + dq][i], 0, 0, 0);
+            });
+        });
+        s_use = next_stage(s_use);
+    };
+    // (whole rounds of PD stages: what is past the last one has zero weights.  One copy of the code
+    // and one way through it; a tail of its own would be fetched for a single use.)
+    for (uint32_t done = 0; done < len; done += PD)
+        static_for<0, PD>([&](auto p) {
+            products(p);
+            ask(p);
+            asm volatile("" ::: "memory");              // (the loads stay where they are asked for)
+        });
+
+    // ---- epilogue ----
+    // The sums meet in LDS, [wave][diagonal][element of the phase][lane], and the elements are
+    // finished one by one: code that runs once is fetched at some twenty cycles per instruction, so
+    // a loop over the elements is faster than the same code unrolled (two elements: 1.2 us instead
+    // of 2.6).
+    int32_t *const sums = (int32_t *)lds;
+    const uint32_t cgl = (uint32_t)wave & ((1u << log_cgw) - 1u), KS = 1u << t.log_ks;
+    static_for<0, T_::PHASES>([&](auto ph_c) {
+        constexpr int ph = decltype(ph_c)::value, i0 = ph * T_::TP;
+        constexpr int TILES = RT16 - i0 < T_::TP ? RT16 - i0 : T_::TP;
+        __syncthreads();                                // the planes, or the phase before, are read
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int e = 0; e < 4 * TILES; ++e)
+                sums[(((uint32_t)wave * ND + d) * (4 * TILES) + e) * 64u + lane] = acc[d][i0 + e / 4][e % 4];
+        __syncthreads();
+        uint32_t tile, e0;
+        const uint32_t ne = share(ph, tile, e0);
+#pragma unroll 1
+        for (uint32_t u = 0; u < ne; ++u) {
+            const uint32_t e = 4u * (tile - i0) + e0 + u;       // of the phase
+            const uint64_t word = mk[ph][0];
+#pragma unroll
+            for (uint32_t v = 1; v < 4 * T_::TP; ++v) mk[ph][v - 1] = mk[ph][v];
+            int32_t digit[ND];
+#pragma unroll
+            for (int d = 0; d < ND; ++d) digit[d] = 0;
+#pragma unroll 1
+            for (uint32_t o = 0; o < KS; ++o)
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+                    digit[d] += sums[((((o << log_cgw) + cgl) * ND + d) * (4 * TILES) + e) * 64u + lane];
+            cop_finish<ND, 1, false>([&](int d, int) { return digit[d]; }, [](int) { return 0; },
+                                     [&](int) { return word; }, a, a.prev, pp.out, limb, colsum_S,
+                                     (int)(16u * (i0 + e / 4u) + 4u * j + e % 4u), col);
+        }
+    });
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+bool thin_applies(const Problem &p) { return p.m <= kThinRows; }
+
+// the shares' planes of a workgroup fit the LDS
+static bool thin_planes_fit(const Problem &p)
+{
+    const long long S = (kblocks(p.k) + 1) / 2, tiles = (p.m + 15) / 16;
+    return S * tiles * planes_x(p.x_bits) * kTileBytes <= kThinSharesLds;
+}
+
+// With a second 16-row tile the splitting takes as long as the staging launch (m = 32 on 768 x 16384:
+// 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).
+bool thin_raw_applies(const Problem &p) { return p.m <= 16 && thin_planes_fit(p); }
+
+template <int DX, int DQ>
+static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int half_shift,
+                            const void *const *staged, const void *const *prepared,
+                            const uint64_t *const *masks, const uint64_t *prev, uint64_t *const *outs,
+                            hipStream_t stream)
+{
+    const int KB = kblocks(p.k);
+    const uint32_t CT = (uint32_t)(p.C / kTile);
+    MfmaArgs a{};
+    fill_common_args(p, DX, masks[0], prev, outs[0], &a);
+    BatchPtrs b{};
+    for (int i = 0; i < count; ++i) {
+        b.prob[i].xd = (const uint4 *)staged[i];
+        b.prob[i].planes = (const uint4 *)prepared[i];
+        b.prob[i].colsum = (const uint64_t *)((const char *)prepared[i] + (size_t)CT * KB * DQ * kTileBytes);
+        b.prob[i].mask = masks[i];
+        b.prob[i].out = outs[i];
+    }
+    b.count = (uint32_t)count;
+    ThinArgs t{};
+    t.X = X;
+    t.staged = (uint4 *)const_cast<void *>(staged[0]);
+    t.k = p.k;
+    t.half_shift = half_shift;
+    const uint32_t quads = 16u * ((uint32_t)(KB + 1) / 2u);
+    t.quads_magic = (uint32_t)(((1ull << 32) + quads - 1) / quads);     // (items below 2^16, Q below 2^13)
+    // Slices of k: a compute unit holds one workgroup, so the launch takes as many rounds as there
+    // are multiples of 256 workgroups, and a round takes the stages of a slice and what starting and
+    // ending a workgroup costs, about three stages of eight waves.  (20 x 400 x 12288: two
+    // slices in one round 16.0 us, four in two rounds 20.6.)
+    const uint64_t S = (uint64_t)(KB + 1) / 2u, groups = (uint64_t)CT * 2u;
+    uint64_t least = ~0ull;
+    for (uint32_t l = 0; l <= 3 && (1ull << l) <= S; ++l) {
+        const uint64_t blocks = (groups + (8u >> l) - 1) / (8u >> l) * (uint64_t)count;
+        const uint64_t cost = (blocks + 255u) / 256u * (((S + (1u << l) - 1) >> l) + 3u);
+        if (cost < least) {
+            least = cost;
+            t.log_ks = l;
+        }
+    }
+    const uint32_t cgw = 8u >> t.log_ks;
+    const dim3 grid((uint32_t)((groups + cgw - 1) / cgw), (uint32_t)count), block(512);
+    auto go = [&](auto rt_c, auto from_c) {
+        return launch(cop_thin_kernel<DX, DQ, decltype(rt_c)::value, decltype(from_c)::value>, grid, block, stream,
+                      a, b, t);
+    };
+    const std::integral_constant<ThinShares, kDirect> direct;
+    const std::integral_constant<ThinShares, kCopied> copied;
+    const std::integral_constant<ThinShares, kRaw> raw;
+    const std::integral_constant<int, 1> one;
+    const std::integral_constant<int, 2> two;
+    if (X) return go(one, raw);
+    if (p.m <= 16) return go(one, direct);
+    // The planes of 32 rows weigh nearly as much as the weights of a wave: eight waves that read the
+    // same ones (one slice) read them once, from LDS (32 x 768 x 24576: 31.5 us against 34.4); with
+    // several slices fewer waves share them and nobody waits for the copy (x 8192: 17.8 and 16.0).
+    return t.log_ks == 0 && thin_planes_fit(p) ? go(two, copied) : go(two, direct);
+}
+
+hipError_t launch_cop_thin(const Problem &p, int count, const uint64_t *X, int half_shift,
+                           const void *const *staged, const void *const *prepared,
+                           const uint64_t *const *masks, const uint64_t *prev, uint64_t *const *outs,
+                           hipStream_t stream)
+{
+    if (count < 1 || count > kMaxBatch) return hipErrorInvalidValue;
+    const int DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);
+#define NIMBUS_CASE(dx, dq) \
+    if (DX == dx && DQ == dq) \
+        return thin_impl<dx, dq>(p, count, X, half_shift, staged, prepared, masks, prev, outs, stream);
+    NIMBUS_CASE(2, 7)
+    NIMBUS_CASE(3, 7)
+    NIMBUS_CASE(4, 7)
+    NIMBUS_CASE(2, 8)
+    NIMBUS_CASE(3, 8)
+    NIMBUS_CASE(4, 8)
+#undef NIMBUS_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace nimbus
