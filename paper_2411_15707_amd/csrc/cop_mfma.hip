@@ -37,14 +37,15 @@ namespace nimbus {
 // per call: X -> DX signed byte planes in A-operand tile order
 // ---------------------------------------------------------------------------
 // (blockIdx.y: the problem, when the shares of several calls are staged in one launch)
+template <int NB>
 struct StagePtrs {
-    const uint64_t *X[kMaxBatch];
-    uint32_t *xd[kMaxBatch];
+    const uint64_t *X[NB];
+    uint32_t *xd[NB];
 };
 
-template <int DX>
+template <int DX, int NB>
 __global__ __launch_bounds__(256) void x_planes_kernel(
-    const StagePtrs sp, int m, int k, int KB, uint32_t total, uint32_t offx, int half_shift)
+    const StagePtrs<NB> sp, int m, int k, int KB, uint32_t total, uint32_t offx, int half_shift)
 {
     const uint64_t *__restrict__ const X = sp.X[blockIdx.y];
     uint32_t *__restrict__ const xd = sp.xd[blockIdx.y];
@@ -161,15 +162,15 @@ constexpr int kMaskTileBytes = 128 * 64 * 8;
 constexpr int kMaskLoads = kMaskTileBytes / kTileBytes / 8;     // per wave: 8
 constexpr int kMaskPhase = kMaskLoads + 2;                      // iterations that count them
 
-template <int DX, int DQ, bool FULL, bool MASKLDS, bool SHARED>
-__global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, const BatchPtrs b)
+template <int DX, int DQ, bool FULL, bool MASKLDS, bool SHARED, int NB>
+__global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, const BatchPtrs<NB> b)
 {
     using P_ = Pipe<DX, DQ>;
     // Every scalar argument the setup needs, asked for in one batch: left to the compiler the
     // loads sit next to their first uses, and the setup waits for the constant cache once
     // per group of them instead of once.
     asm volatile("" ::"s"(b.prob[0].xd), "s"(b.prob[0].planes), "s"(b.prob[0].colsum),
-                 "s"(b.prob[0].mask), "s"(b.prob[0].out), "s"(b.count), "s"(a.m), "s"(a.KB), "s"(a.RB),
+                 "s"(b.prob[0].mask), "s"(b.prob[0].out), "s"(a.m), "s"(a.KB), "s"(a.RB),
                  "s"(a.L), "s"(a.CT), "s"(a.kb_magic), "s"(a.log_n), "s"(a.l_magic));
     constexpr int ND = P_::ND;
     constexpr bool PIPELINED = P_::PIPELINED;
@@ -191,7 +192,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     // once.  (The column tiles past the last multiple of 8, if any, are not worth the trouble.)
     // (the pointers of a single call are asked for with the first batch of scalar loads: an
     // indexed load would sit on the path to the first loads of the launch)
-    const bool single = b.count == 1;
+    const bool single = NB == 1 || b.count == 1;
     // (a launch may hold several problems of the same shape: tile ids run through the first
     // problem's tiles, then the second's, ...; p is the problem)
     auto map_tile = [&](uint32_t id, uint32_t &p, uint32_t &ct2, uint32_t &rb) {
@@ -713,13 +714,17 @@ static hipError_t stage_impl(const Problem &p, int count, const uint64_t *const 
     const int KB = kblocks(p.k);
     const int RT = (p.m + kTile - 1) / kTile;
     const uint32_t xtotal = (uint32_t)RT * KB * 256;
-    StagePtrs sp{};
-    for (int i = 0; i < count; ++i) {
-        sp.X[i] = X[i];
-        sp.xd[i] = (uint32_t *)workspace[i];
-    }
-    return launch(x_planes_kernel<DX>, dim3((xtotal + 255) / 256, (uint32_t)count), dim3(256), stream,
-                  sp, p.m, p.k, KB, xtotal, share_offset(p.x_bits, DX), half_shift);
+    auto go = [&](auto nb_c) {
+        constexpr int NB = decltype(nb_c)::value;
+        StagePtrs<NB> sp{};
+        for (int i = 0; i < count; ++i) {
+            sp.X[i] = X[i];
+            sp.xd[i] = (uint32_t *)workspace[i];
+        }
+        return launch(x_planes_kernel<DX, NB>, dim3((xtotal + 255) / 256, (uint32_t)count), dim3(256), stream,
+                      sp, p.m, p.k, KB, xtotal, share_offset(p.x_bits, DX), half_shift);
+    };
+    return count == 1 ? go(std::integral_constant<int, 1>{}) : go(std::integral_constant<int, kMaxBatch>{});
 }
 
 // p.x_bits (<= 32) is the width of the half that is staged; half_shift is 0 or 32
@@ -754,16 +759,7 @@ static hipError_t mfma_impl(const Problem &p, int count, const void *const *stag
 
     MfmaArgs a{};
     fill_common_args(p, DX, mask, prev, outs[0], &a);
-    BatchPtrs b{};
-    for (int i = 0; i < count; ++i) {
-        b.prob[i].xd = (const uint4 *)staged[i];
-        b.prob[i].planes = (const uint4 *)prepared[i];
-        b.prob[i].colsum = (const uint64_t *)((const char *)prepared[i] + (size_t)CT * KB * DQ * kTileBytes);
-        b.prob[i].mask = masks[i];
-        b.prob[i].out = outs[i];
-    }
-    b.count = (uint32_t)count;
-    b.tiles_each = a.tiles;
+    const uint32_t tiles_each = a.tiles;
     a.tiles *= (uint32_t)count;
     // One workgroup per compute unit at most (a compute unit holds one at a time anyway);
     // each walks the tiles id, id + grid, ...  A grid that is a multiple of 8 keeps a tile id's
@@ -777,10 +773,25 @@ static hipError_t mfma_impl(const Problem &p, int count, const void *const *stag
     const bool mask_lds = kCanMaskLds && mask != nullptr && p.m % 128 == 0 &&
                           KB - P_::LEAD >= kMaskPhase && (uint64_t)p.C * 8u * 128u < (1ull << 32);
     const bool full = p.m % 128 == 0;
-    auto launch = [&](auto full_c, auto masklds_c, auto shared_c) {
-        return nimbus::launch(cop_mfma_kernel<DX, DQ, decltype(full_c)::value,
-                                              decltype(masklds_c)::value, decltype(shared_c)::value>,
+    auto launch_with = [&](auto full_c, auto masklds_c, auto shared_c, auto nb_c) {
+        constexpr int NB = decltype(nb_c)::value;
+        BatchPtrs<NB> b{};
+        for (int i = 0; i < count; ++i) {
+            b.prob[i].xd = (const uint4 *)staged[i];
+            b.prob[i].planes = (const uint4 *)prepared[i];
+            b.prob[i].colsum = (const uint64_t *)((const char *)prepared[i] + (size_t)CT * KB * DQ * kTileBytes);
+            b.prob[i].mask = masks[i];
+            b.prob[i].out = outs[i];
+        }
+        b.count = (uint32_t)count;
+        b.tiles_each = tiles_each;
+        return nimbus::launch(cop_mfma_kernel<DX, DQ, decltype(full_c)::value, decltype(masklds_c)::value,
+                                              decltype(shared_c)::value, NB>,
                               grid, dim3(512), stream, a, b);
+    };
+    auto launch = [&](auto full_c, auto masklds_c, auto shared_c) {
+        return count == 1 ? launch_with(full_c, masklds_c, shared_c, std::integral_constant<int, 1>{})
+                          : launch_with(full_c, masklds_c, shared_c, std::integral_constant<int, kMaxBatch>{});
     };
     using T = std::true_type;
     using F = std::false_type;

@@ -51,10 +51,13 @@ struct ProblemPtrs {
     const uint64_t *mask;       // or null (all problems or none)
     uint64_t *out;
 };
+// NB: room for problems, 1 or kMaxBatch.  A launch writes its arguments to device memory over the
+// host link: the table of sixteen problems alone costs a single call 3 us of the host's time.
+template <int NB>
 struct BatchPtrs {
     uint32_t count;
     uint32_t tiles_each;        // output tiles of one problem
-    ProblemPtrs prob[kMaxBatch];    // (problem 0 first: one cache line with the two words above)
+    ProblemPtrs prob[NB];       // (problem 0 first: one cache line with the two words above)
 };
 
 // ---- host side: constants of the argument block ----

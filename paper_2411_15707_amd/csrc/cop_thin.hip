@@ -76,8 +76,8 @@ __device__ __forceinline__ v4i load_operand(__amdgpu_buffer_rsrc_t rsrc, uint32_
                   : __builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0);
 }
 
-template <int DX, int DQ, int RT16, ThinShares FROM>
-__global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, const BatchPtrs b, const ThinArgs t)
+template <int DX, int DQ, int RT16, ThinShares FROM, int NB>
+__global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, const BatchPtrs<NB> b, const ThinArgs t)
 {
     using T_ = Thin<DX, DQ, RT16, FROM>;
     constexpr int ND = T_::ND, PD = T_::PD;
@@ -91,7 +91,7 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
     const uint32_t cg = (blockIdx.x << log_cgw) + ((uint32_t)wave & ((1u << log_cgw) - 1u));
     const uint32_t ks = (uint32_t)wave >> log_cgw;
     const bool active = cg < a.CT * 2u;                 // (the last workgroup may have columns to spare)
-    const ProblemPtrs pp = b.prob[blockIdx.y];
+    const ProblemPtrs pp = b.prob[NB == 1 ? 0 : blockIdx.y];
     const int KB = a.KB;
     const uint32_t S = ((uint32_t)KB + 1u) >> 1;
     // this wave's stages: s0 .. s1-1, started at a place that follows from the column tile so
@@ -358,15 +358,6 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     const uint32_t CT = (uint32_t)(p.C / kTile);
     MfmaArgs a{};
     fill_common_args(p, DX, masks[0], prev, outs[0], &a);
-    BatchPtrs b{};
-    for (int i = 0; i < count; ++i) {
-        b.prob[i].xd = (const uint4 *)staged[i];
-        b.prob[i].planes = (const uint4 *)prepared[i];
-        b.prob[i].colsum = (const uint64_t *)((const char *)prepared[i] + (size_t)CT * KB * DQ * kTileBytes);
-        b.prob[i].mask = masks[i];
-        b.prob[i].out = outs[i];
-    }
-    b.count = (uint32_t)count;
     ThinArgs t{};
     t.X = X;
     t.staged = (uint4 *)const_cast<void *>(staged[0]);
@@ -390,9 +381,24 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     }
     const uint32_t cgw = 8u >> t.log_ks;
     const dim3 grid((uint32_t)((groups + cgw - 1) / cgw), (uint32_t)count), block(512);
-    auto go = [&](auto rt_c, auto from_c) {
-        return launch(cop_thin_kernel<DX, DQ, decltype(rt_c)::value, decltype(from_c)::value>, grid, block, stream,
+    auto go_with = [&](auto rt_c, auto from_c, auto nb_c) {
+        constexpr int NB = decltype(nb_c)::value;
+        BatchPtrs<NB> b{};
+        for (int i = 0; i < count; ++i) {
+            b.prob[i].xd = (const uint4 *)staged[i];
+            b.prob[i].planes = (const uint4 *)prepared[i];
+            b.prob[i].colsum = (const uint64_t *)((const char *)prepared[i] + (size_t)CT * KB * DQ * kTileBytes);
+            b.prob[i].mask = masks[i];
+            b.prob[i].out = outs[i];
+        }
+        b.count = (uint32_t)count;
+        return launch(cop_thin_kernel<DX, DQ, decltype(rt_c)::value, decltype(from_c)::value, NB>, grid, block, stream,
                       a, b, t);
+    };
+    auto go = [&](auto rt_c, auto from_c) {
+        if constexpr (decltype(from_c)::value != kRaw)
+            if (count > 1) return go_with(rt_c, from_c, std::integral_constant<int, kMaxBatch>{});
+        return go_with(rt_c, from_c, std::integral_constant<int, 1>{});
     };
     const std::integral_constant<ThinShares, kDirect> direct;
     const std::integral_constant<ThinShares, kCopied> copied;
