@@ -128,14 +128,12 @@ struct Pipe {
     static constexpr int B_BYTES = B_TILES * kTileBytes;
     // accumulators + two operand sets + addressing must fit 256 registers (two waves per SIMD)
     static constexpr bool PIPELINED = ND * 16 + 2 * (DX + DQ) * 4 + 12 <= 256;
-    static constexpr int AHEAD = PIPELINED ? 1 : 0;
-    // Lead: stages 0 .. LEAD-1 are issued up front, iteration s issues stage s + LEAD
-    // after its barrier, into the slot of stage s + LEAD - RING.  That slot has been read
-    // by every wave once all have passed the barrier of iteration s + LEAD - RING + 1 -
-    // AHEAD, so RING = LEAD + 1 - AHEAD slots are enough.
+    // Stages 0 .. LEAD-1 are issued up front, iteration s issues stage s + LEAD: behind its
+    // barrier, by which every wave has stage s in registers, so that LEAD slots are enough; the
+    // variants with one operand set issue it in front of theirs and need a slot more.
+    // (LEAD = 5 where the LDS has room: 3 to 4 % slower throughout, the prologue is longer.)
     static constexpr int LEAD = 3;
-    static constexpr int RING = LEAD + 1 - AHEAD;
-    static_assert(LEAD >= 1 + AHEAD, "the stage read next must have been issued");
+    static constexpr int RING = PIPELINED ? LEAD : LEAD + 1;
     // load slots per wave and stage: a row tile's DX planes, or half of a column tile's DQ
     static constexpr int MAXU = ((A_TILES > B_TILES ? A_TILES : B_TILES) + 3) / 4;
     static_assert((LEAD - 1) * MAXU <= 63, "pending-load count must fit the wait counter");
@@ -174,7 +172,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
                  "s"(a.L), "s"(a.CT), "s"(a.kb_magic), "s"(a.log_n), "s"(a.l_magic));
     constexpr int ND = P_::ND;
     constexpr bool PIPELINED = P_::PIPELINED;
-    constexpr int AHEAD = P_::AHEAD, LEAD = P_::LEAD, RING = P_::RING;
+    constexpr int LEAD = P_::LEAD, RING = P_::RING;
     constexpr int SETS = PIPELINED ? 2 : 1;
     static_assert(!MASKLDS || (FULL && P_::PIPELINED && P_::LDS_BYTES + kMaskTileBytes <= 160 * 1024),
                   "mask tile in LDS: full row blocks, pipelined variant, and it must fit");
@@ -422,38 +420,39 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         for (int d = 0; d < DQ; ++d) tie(xb[SET][d]);
     };
 
-    // Loads of this wave younger than those of stage j = s + AHEAD, before iteration s:
-    // stages j+1 .. min(KB, s + LEAD) - 1, that is min(LEAD - 1 - AHEAD, KB - 1 - j) stages.
-    // No stage j: nothing to wait for.
+    // Loads of this wave younger than those of stage s + 1 at the barrier of iteration s: those of
+    // the stages behind it that have been issued, W of them at most.  No stage s + 1: nothing to
+    // wait for.
+    constexpr int W = PIPELINED ? LEAD - 2 : LEAD - 1;
     auto younger = [&](int s) -> int {
-        const int j = s + AHEAD;
-        if (j >= KB) return 63;
-        int st = KB - 1 - j;
-        if (st > LEAD - 1 - AHEAD) st = LEAD - 1 - AHEAD;
+        if (s + 1 >= KB) return 63;
+        int st = KB - 2 - s;
+        if (st > W) st = W;
         return st * n_loads;
     };
     asm volatile("" ::: "memory");
-    if constexpr (PIPELINED) {
+    {
         // stage 0 is read before the loop; its younger loads are those of stages 1 .. LEAD-1
         const int st = (KB < LEAD ? KB : LEAD) - 1;
         wait_vmem_n(st * n_loads);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if (active) read_ops(std::integral_constant<int, 0>{});
-        NIMBUS_NEXT_READ();
+        if constexpr (PIPELINED) {
+            if (active) read_ops(std::integral_constant<int, 0>{});
+            NIMBUS_NEXT_READ();
+        }
     }
 
     // iteration s, pipelined: make stage s+1 visible, issue stage s+LEAD into a slot
     // whose stage every wave has in registers, read stage s+1 into the other operand
-    // set, run the matrix cores on stage s.  Not pipelined (register budget of the
-    // widest variants): make stage s visible, issue, read stage s, wait, run.
+    // set, run the matrix cores on stage s.  (One operand set: see one_set_iteration.)
     //
     // Between consecutive matrix-core instructions goes at most one other instruction
     // (all eight waves leave the barrier together: a burst of loads or LDS reads would
     // fill the queues of the CU and hold back the matrix-core instructions behind it):
-    // first the X loads, then the LDS reads of stage s+1 (pipelined variants), the
-    // ciphertext loads last.  The empty volatile asm statements pin this order.
-    constexpr int R0 = PIPELINED ? DX + DQ : 0;     // LDS reads placed between the MFMAs
+    // first the X loads, then the LDS reads of stage s+1, the ciphertext loads last.  The
+    // empty volatile asm statements pin this order.
+    constexpr int R0 = DX + DQ;                     // LDS reads placed between the MFMAs
     constexpr int NPOS = DX * DQ;
     static_assert(NPOS >= R0 + 1 && NPOS >= P_::MAXU, "not enough positions between the MFMAs");
     // positions: [0, MAXU) X loads, [RP0, RP0 + R0) reads, the last MAXU ciphertext loads
@@ -464,13 +463,9 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         constexpr int SET = decltype(set_c)::value;
         constexpr bool ACTIVE = decltype(active_c)::value;
         wait_vmem_n(younger(s));
-        if constexpr (PIPELINED && ACTIVE) wait_ops(set_c);
+        if constexpr (ACTIVE) wait_ops(set_c);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        if constexpr (!PIPELINED && ACTIVE) {
-            read_ops(set_c);
-            wait_ops(set_c);
-        }
         const int issue_n = s + LEAD < KB ? n_loads : 0;    // stage s + LEAD exists: its loads
         static_for<0, NPOS>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value;
@@ -488,8 +483,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             if constexpr (i >= RP0 && i < RP0 + R0) {
                 // (the last iteration reads a stale slot: valid LDS, never used)
                 if constexpr (ACTIVE)
-                    read_one(std::integral_constant<int, (PIPELINED ? 1 - SET : SET)>{},
-                             std::integral_constant<int, i - RP0>{});
+                    read_one(std::integral_constant<int, 1 - SET>{}, std::integral_constant<int, i - RP0>{});
             }
             if constexpr (i >= XP0) {
                 constexpr int u = i - XP0;
@@ -535,7 +529,6 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     auto steady_iteration = [&](auto set_c, auto phase_c, int t) {
         constexpr int SET = decltype(set_c)::value;
         constexpr bool MASKPHASE = decltype(phase_c)::value;   // iteration t < kMaskPhase
-        constexpr int W = LEAD - 1 - AHEAD;
         wait_ops(set_c);
         static_for<0, NPOS>([&](auto i_c) {
             constexpr int i = decltype(i_c)::value;
@@ -581,9 +574,71 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     // the carried offsets move on between iterations (outside the lambda: plain locals)
     using C0 = std::integral_constant<int, 0>;
     using C1 = std::integral_constant<int, 1>;
+    // One operand set (DX + DQ - 1 accumulators leave no room for two): the operands rotate.  The
+    // products run share plane by share plane; share plane dx + 1 of the stage is read while plane
+    // dx is multiplied, and during the last plane every ciphertext plane is refilled from stage
+    // s + 1 right behind its last use.  The barrier that makes stage s + 1 visible and frees the
+    // slot of stage s stands behind the first NPRE1 products of the last plane; the loads of stage
+    // s + LEAD go out during the first two planes, into the slot that the barrier before has freed.
+    // LDS reads come back in order, so every wait is a count of younger reads.
+    // (Reading a whole stage behind its barrier, as before, left the matrix cores idle for the
+    // reads' latency in every k-block: 128 x 768 x 32768 with 64-bit shares and moduli of 59 bits
+    // 194 us, now 184; four problems of 77 x 1001 x 16384 with 32-bit shares 185 us, now 172.)
+    constexpr int NPRE1 = 2;
+    auto one_set_iteration = [&](int s, auto steady_c) {
+        constexpr bool STEADY = decltype(steady_c)::value;      // stage s + LEAD exists
+        const uint32_t nextA = bump(rdA, P_::A_BYTES, RING * P_::A_BYTES);
+        const uint32_t nextB = bump(rdB, P_::B_BYTES, RING * P_::B_BYTES);
+        static_for<0, NPOS>([&](auto i_c) {
+            constexpr int i = decltype(i_c)::value;
+            constexpr int dx = i / DQ, dq = i % DQ;
+            constexpr bool LAST = dx == DX - 1;
+            if constexpr (dq == 0 && !LAST) xa[0][dx + 1] = lds_read_b128<(dx + 1) * kTileBytes>(laneA + rdA);
+            // plane 0: reads younger than ciphertext plane dq are the planes behind it and share plane 1
+            if constexpr (dx == 0) {
+                wait_lds<DQ - dq>(xb[0][dq]);
+                if constexpr (dq == 0) tie(xa[0][0]);
+            } else if constexpr (dq == 0) {
+                wait_lds<LAST ? 0 : 1>(xa[0][dx]);
+            }
+            tie(xa[0][dx]);
+            tie(xb[0][dq]);
+            acc[dx + dq] =
+                __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[0][dx], xb[0][dq], acc[dx + dq], 0, 0, 0);
+            tie_acc(acc[dx + dq]);
+            // loads of stage s + LEAD, one at a time over the first two planes
+            if constexpr (STEADY && DX > 2 && i % 4 == 2 && i / 4 < P_::MAXU) {
+                constexpr int u = i / 4;
+                if (u < NMIN || u < n_loads) issue_one(std::integral_constant<int, u>{});
+            }
+            if constexpr (LAST && dq == NPRE1 - 1) {
+                if constexpr (STEADY) wait_vmem_loads<W, P_::MAXU, NMIN>(n_loads);
+                else wait_vmem_n(younger(s));
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                xa[0][0] = lds_read_b128<0>(laneA + nextA);
+                static_for<0, NPRE1>([&](auto d_c) {
+                    xb[0][decltype(d_c)::value] = lds_read_b128<decltype(d_c)::value * kTileBytes>(laneB + nextB);
+                });
+            }
+            // (the last iteration reads a stale slot: valid LDS, never used)
+            if constexpr (LAST && dq >= NPRE1) xb[0][dq] = lds_read_b128<dq * kTileBytes>(laneB + nextB);
+        });
+        asm volatile("" ::: "memory");
+    };
     if (!active) {
         for (int s = 0; s < KB; ++s) {
-            iteration(s, C0{}, std::false_type{});
+            if constexpr (PIPELINED) {
+                iteration(s, C0{}, std::false_type{});
+            } else {
+                if (s + LEAD < KB)
+                    static_for<0, P_::MAXU>([&](auto u_c) {
+                        if (decltype(u_c)::value < n_loads) issue_one(u_c);
+                    });
+                wait_vmem_n(younger(s));
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+            }
             NIMBUS_NEXT_ISSUE();
         }
     } else if constexpr (PIPELINED) {
@@ -618,9 +673,18 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             }
         }
     } else {
-        for (int s = 0; s < KB; ++s) {
-            iteration(s, C0{}, std::true_type{});
+        xa[0][0] = lds_read_b128<0>(laneA + rdA);
+        static_for<0, DQ>([&](auto d_c) {
+            xb[0][decltype(d_c)::value] = lds_read_b128<decltype(d_c)::value * kTileBytes>(laneB + rdB);
+        });
+        int s = 0;
+        for (; s < KB - LEAD; ++s) {
+            one_set_iteration(s, std::true_type{});
             NIMBUS_NEXT_ISSUE();
+            NIMBUS_NEXT_READ();
+        }
+        for (; s < KB; ++s) {
+            one_set_iteration(s, std::false_type{});
             NIMBUS_NEXT_READ();
         }
     }
@@ -630,15 +694,13 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
 
     // ---- the next tile's first stages, issued in front of this tile's epilogue ----
-    // Every wave has the last stage in registers once all have passed the last barrier
-    // (pipelined variants: the reads are waited for in front of it; the others read behind
-    // it, so they meet once more here): the rings are free, and the loads have the whole
+    // Every wave has the last stage in registers once all have passed the last barrier (its
+    // reads are waited for in front of it): the rings are free, and the loads have the whole
     // epilogue, which uses neither the rings nor the memory pipeline much, to land.
     const uint32_t next = tile + gridDim.x;
     const bool more = next < a.tiles;
     uint32_t next_prob = 0, next_ct2 = 0, next_rb = 0;
     if (more) {
-        if constexpr (!PIPELINED) __builtin_amdgcn_s_barrier();
         map_tile(next, next_prob, next_ct2, next_rb);
         begin_tile(next_prob, next_ct2, next_rb);
 #pragma unroll
@@ -759,13 +821,13 @@ static hipError_t mfma_impl(const Problem &p, int count, const void *const *stag
 
     MfmaArgs a{};
     fill_common_args(p, DX, mask, prev, outs[0], &a);
-    const uint32_t tiles_each = a.tiles;
-    a.tiles *= (uint32_t)count;
     // One workgroup per compute unit at most (a compute unit holds one at a time anyway);
     // each walks the tiles id, id + grid, ...  A grid that is a multiple of 8 keeps a tile id's
     // XCD the same on every pass.
     uint32_t cus = (uint32_t)compute_units();
     if (cus >= 8) cus &= ~7u;
+    const uint32_t tiles_each = a.tiles;
+    a.tiles *= (uint32_t)count;
     const dim3 grid(a.tiles < cus ? a.tiles : cus);
     using P_ = Pipe<DX, DQ>;
     constexpr bool kCanMaskLds = P_::PIPELINED && P_::LDS_BYTES + kMaskTileBytes <= 160 * 1024;
