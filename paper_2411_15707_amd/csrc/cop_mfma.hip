@@ -217,6 +217,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         }
     };
     const int RT = (a.m + kTile - 1) / kTile;       // row tiles that exist in the workspace
+    const uint32_t block_tiles = FULL ? 4u : a.block_tiles;         // row tiles of a row block
     const int KB = a.KB;
 
     // ---- this wave's share of the loads of one stage (sources at k-block 0) ----
@@ -273,7 +274,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             planes_p = b.prob[p].planes;
         }
         const unsigned char *const a_base =
-            (const unsigned char *)xd_p + (size_t)rb * 4u * a_tile_bytes;
+            (const unsigned char *)xd_p + (size_t)rb * block_tiles * a_tile_bytes;
         const unsigned char *const b_base =
             (const unsigned char *)planes_p + (size_t)ct2 * 2u * b_tile_bytes;
         rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(loads_x ? a_base : b_base), 0, 0xffffffff,
@@ -281,7 +282,8 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         uint32_t first_off;
         if (loads_x) {
             int r = wave;
-            const int last = RT - 1 - (int)rb * 4;  // last row tile of the block that exists (>= 0)
+            const int last = RT - 1 - (int)(rb * block_tiles);      // last row tile that exists (>= 0)
+            if (r > (int)block_tiles - 1) r = (int)block_tiles - 1;
             if (r > last) r = last;
             first_off = (uint32_t)r * a_tile_bytes;
         } else {
@@ -351,8 +353,8 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     }
     __builtin_amdgcn_sched_barrier(0);
     // ---- what the first loads did not need ----
-    const int rt = (int)rb * 4 + wr;                // this wave's row tile
-    const bool active = FULL || rt < RT;            // wave-uniform
+    const int rt = (int)(rb * block_tiles) + wr;    // this wave's row tile
+    const bool active = FULL || ((uint32_t)wr < block_tiles && rt < RT);    // wave-uniform
     // Loads and stores complete in the order they were issued, so the counted waits of the
     // loop would still be right with the epilogue's stores among the younger ones; waiting
     // for everything once (the loads have had the whole epilogue to land) keeps them simple.
@@ -826,15 +828,24 @@ static hipError_t mfma_impl(const Problem &p, int count, const void *const *stag
     // XCD the same on every pass.
     uint32_t cus = (uint32_t)compute_units();
     if (cus >= 8) cus &= ~7u;
+    // Row blocks of 64 rows where all of those find a compute unit of their own: half as many
+    // products per workgroup, one wave per SIMD (128 x 2000 x 2048: 46.8 us a call with blocks of 128
+    // rows, 29.5 with 64; 128 x 768 x 8192, as many blocks as compute units: 24.5 and 22.3).  With
+    // a second round of workgroups the larger blocks are ahead (100 x 768 x 12288).
+    if (p.m > 64 && (uint64_t)(CT / 2u) * (uint64_t)((p.m + 63) / 64) * (uint32_t)count <= cus) {
+        a.block_tiles = 2;
+        a.RB = (p.m + 63) / 64;
+        a.tiles = (CT / 2u) * (uint32_t)a.RB;
+    }
     const uint32_t tiles_each = a.tiles;
     a.tiles *= (uint32_t)count;
     const dim3 grid(a.tiles < cus ? a.tiles : cus);
     using P_ = Pipe<DX, DQ>;
     constexpr bool kCanMaskLds = P_::PIPELINED && P_::LDS_BYTES + kMaskTileBytes <= 160 * 1024;
     // mask tile in LDS: see the kernel; 128 rows of the mask must span less than 4 GB
-    const bool mask_lds = kCanMaskLds && mask != nullptr && p.m % 128 == 0 &&
+    const bool mask_lds = kCanMaskLds && mask != nullptr && p.m % 128 == 0 && a.block_tiles == 4 &&
                           KB - P_::LEAD >= kMaskPhase && (uint64_t)p.C * 8u * 128u < (1ull << 32);
-    const bool full = p.m % 128 == 0;
+    const bool full = p.m % 128 == 0 && a.block_tiles == 4;
     auto launch_with = [&](auto full_c, auto masklds_c, auto shared_c, auto nb_c) {
         constexpr int NB = decltype(nb_c)::value;
         BatchPtrs<NB> b{};

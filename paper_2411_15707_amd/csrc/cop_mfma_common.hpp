@@ -35,6 +35,7 @@ struct MfmaArgs {
     uint32_t log_n;           // N = 2^log_n
     uint32_t l_magic;         // ceil(2^32 / L) for L >= 2: x / L = umulhi(x, l_magic) for x < 2^31
     uint32_t offx;            // OFFX
+    uint32_t block_tiles;     // 32-row tiles of a row block: 4, or 2 (see mfma_impl)
     uint64_t q[kMaxLimbs];
     double qinv[kMaxLimbs];   // 1 / q_l, rounded
     // q_l << sh
@@ -100,6 +101,7 @@ static inline void fill_common_args(const Problem &p, int DX, const uint64_t *ma
     a->m = p.m;
     a->KB = KB;
     a->RB = (p.m + 127) / 128;
+    a->block_tiles = 4;
     a->N = p.N;
     a->L = p.L;
     a->C = (uint32_t)p.C;

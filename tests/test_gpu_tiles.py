@@ -1,5 +1,5 @@
-"""The 128 x 64 tile kernel where its loop has a single operand set, at every length of the loop's
-ends, against the oracle."""
+"""The tile kernel of more than 32 rows against the oracle: where its loop has a single operand set, at
+every length of the loop's ends; row blocks of 64 rows (few columns) and where they end."""
 import numpy as np
 import pytest
 
@@ -37,3 +37,14 @@ def test_one_operand_set(oracle, m, k, x_bits, q_bits):
                                                  (256, 40, 4096, 24, 62)])
 def test_one_operand_set_full_blocks(oracle, m, k, N, x_bits, q_bits):
     check(oracle, m, k, N, N, 1 if N > 4096 else 2, x_bits, q_bits)
+
+
+# row blocks of 64 rows: rows on both sides of a block, the last block without its second row tile; one
+# and several tiles per XCD; both sides of the line (256 compute units: 16 x 16 blocks, then 17 x 16)
+@pytest.mark.parametrize("m,k,N,L,x_bits,q_bits", [
+    (65, 33, 32, 1, 20, 54), (96, 100, 64, 2, 20, 54), (128, 450, 64, 1, 20, 54), (129, 70, 256, 2, 16, 50),
+    (300, 64, 128, 1, 32, 54), (1024, 40, 512, 1, 20, 54), (1025, 40, 512, 1, 20, 54), (200, 130, 64, 2, 24, 62),
+    (100, 200, 32, 1, 12, 62),
+])
+def test_row_blocks_of_64(oracle, m, k, N, L, x_bits, q_bits):
+    check(oracle, m, k, N, N, L, x_bits, q_bits)
