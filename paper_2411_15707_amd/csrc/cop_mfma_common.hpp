@@ -269,14 +269,14 @@ __device__ __forceinline__ void wait_vmem_loads(int n)
 // epilogue: rebuild the sums from the diagonals, add the constant and the mask, reduce, store
 //   D(d, r)    diagonal d (< ND = DX + DQ - 1) of the lane's element r (< NE)
 //   roff(r)    row of element r minus row0 (wave-uniform)
-//   mask_of(r) the mask word of element r, 0 without a mask
+//   masks(mk)  fills in the mask words of the elements, 0 without a mask
 //   prev, out  the result of the pass over the upper share halves (or null) and the problem's
 //              output, [m][C] each
 //   limb       limb of the wave's columns;  colsum_S  sum of the column's residues mod q
 //   row0, col  the lane's first row and its column in the whole output
 // ---------------------------------------------------------------------------
-template <int ND, int NE, bool FULL, typename Digit, typename RowOf, typename MaskOf>
-__device__ __forceinline__ void cop_finish(Digit D, RowOf roff, MaskOf mask_of, const MfmaArgs &a,
+template <int ND, int NE, bool FULL, typename Digit, typename RowOf, typename Masks>
+__device__ __forceinline__ void cop_finish(Digit D, RowOf roff, Masks masks, const MfmaArgs &a,
                                            const uint64_t *prev, uint64_t *out, uint32_t limb,
                                            uint64_t colsum_S, int row0, uint32_t col)
 {
@@ -287,8 +287,7 @@ __device__ __forceinline__ void cop_finish(Digit D, RowOf roff, MaskOf mask_of, 
     const uint64_t *const prev0 = prev ? prev + lane_elem : nullptr;
     uint64_t *const out0 = out + lane_elem;
     uint64_t mk[NE];                                // every load of the epilogue first
-#pragma unroll
-    for (int r = 0; r < NE; ++r) mk[r] = mask_of(r);
+    masks(mk);
     uint64_t cst_hi = a.cst_hi[limb], cst_lo = a.cst_lo[limb];
     {
         const uint64_t S = colsum_S;
@@ -443,11 +442,21 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
     const uint64_t *const mask0 = mask ? mask + ((size_t)row0 * a.C + col) : nullptr;
     cop_finish<ND, 16, FULL>(
         [&](int d, int r) -> int32_t { return acc[d][r]; }, roff,
-        [&](int r) -> uint64_t {
-            // (the tile is in LDS, row-major [128][64] words; else read once: a streaming load)
-            if constexpr (MASKLDS) return *(const uint64_t *)(mask_tile + roff(r) * 512);
-            if (!mask0) return 0;
-            return FULL || row0 + roff(r) < a.m ? __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C]) : 0;
+        [&](uint64_t (&mk)[16]) {
+            // (read once: from the tile in LDS, row-major [128][64] words, or by streaming loads)
+            if constexpr (MASKLDS) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mk[r] = *(const uint64_t *)(mask_tile + roff(r) * 512);
+            } else if (mask) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    mk[r] = (FULL || row0 + roff(r) < a.m)
+                                ? __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C])
+                                : 0;
+            } else {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) mk[r] = 0;
+            }
         },
         a, prev, out, limb, colsum_S, row0, col);
 }

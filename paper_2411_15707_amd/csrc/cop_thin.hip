@@ -326,7 +326,7 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
                 for (int d = 0; d < ND; ++d)
                     digit[d] += sums[((((o << log_cgw) + cgl) * ND + d) * (4 * TILES) + e) * 64u + lane];
             cop_finish<ND, 1, false>([&](int d, int) { return digit[d]; }, [](int) { return 0; },
-                                     [&](int) { return word; }, a, a.prev, pp.out, limb, colsum_S,
+                                     [&](uint64_t (&w)[1]) { w[0] = word; }, a, a.prev, pp.out, limb, colsum_S,
                                      (int)(16u * (i0 + e / 4u) + 4u * j + e % 4u), col);
         }
     });
