@@ -141,68 +141,47 @@ __global__ __launch_bounds__(256) void rlwe_table_set_kernel(Twiddle *__restrict
 // ---------------------------------------------------------------------------
 // decoding: CRT of the limb phases, then rounding division by Delta
 // ---------------------------------------------------------------------------
+// Up to four limbs, Q < 2^248.  Mixed-radix form of the Chinese remainder theorem:
+//   phi = a_0 + q_0 (a_1 + q_1 (a_2 + q_2 a_3)),
+//   a_j = ( ... ((phi_j - a_0) q_0^-1 - a_1) q_1^-1 - ... - a_{j-1}) q_{j-1}^-1  mod q_j.
+// The products by the constants q_i^-1 take any 64-bit factor and leave a value below 2 q_j
+// (mul_lazy), so nothing is reduced on the way: with c_ij the multiple of q_j from q_i up to q_i + q_j,
+// phi_j + c_ij - a_i < 2 q_j + q_i + q_j < 2^64.  One conditional subtraction makes the digit
+// canonical.
+//
+// The quotient (phi + Delta/2) / Delta, below 2^33, is formed in double precision: the digits
+// and moduli, sums, products and the reciprocal round fewer than sixteen times, so the estimate, below
+// 2^33, is off by less than 2^33 16 2^-53 = 2^-16.  Only where its fraction lies within 2^-14 of an
+// integer (never for a ciphertext that decrypts with noise to spare) is it settled with integers
+// of L words.
+//
+// Bound by HBM: (L + 1) 8 bytes a coefficient.  256 x 8192 coefficients of three limbs: 15 us; 26.5 with
+// a reduction of a 128-bit value per step and four-word integers throughout.
 struct DecodeArgs {
     const uint64_t *phi;    // [T][L][N]
     uint64_t *m_hat;        // [T][N]
-    int L, logN;
+    int logN;
     uint64_t total;         // T * N
-    uint64_t q0;
-    Limb red1;              // limb 1 (L == 2)
-    uint64_t q0_inv;        // q0^-1 mod q1
-    uint64_t delta_hi, delta_lo, half_hi, half_lo;   // Delta and floor(Delta / 2)
-    double delta_inv;       // 1 / Delta, rounded
+    uint64_t q[kMaxLimbs];
+    Twiddle inv[kMaxLimbs][kMaxLimbs];      // inv[i][j] = q_i^-1 mod q_j for i < j
+    uint64_t above[kMaxLimbs][kMaxLimbs];   // c_ij
+    uint64_t delta[kMaxLimbs], half[kMaxLimbs];     // Delta and floor(Delta / 2), least significant word first
+    double q_d[kMaxLimbs], half_d, delta_inv;       // rounded; delta_inv = 1 / Delta
     uint64_t t_mask;
 };
 
-__global__ __launch_bounds__(256) void rlwe_decode_kernel(DecodeArgs a)
-{
-    const uint64_t gid = (uint64_t)blockIdx.x * 256u + threadIdx.x;
-    if (gid >= a.total) return;
-    const uint64_t N = 1ull << a.logN;
-    const uint64_t row = gid >> a.logN, c = gid & (N - 1);
-    const uint64_t *const ph = a.phi + row * (uint64_t)a.L * N;
-    const uint64_t p0 = ph[c];
-    u128 v = p0;
-    if (a.L == 2) {
-        // Garner: phi = p0 + q0 * ((p1 - p0) * q0^-1 mod q1)
-        const uint64_t q1 = a.red1.q;
-        const uint64_t p1 = ph[N + c];
-        const uint64_t p0r = barrett128(0, p0, a.red1);
-        uint64_t diff = p1 + q1 - p0r;
-        diff = diff >= q1 ? diff - q1 : diff;
-        const uint64_t h = mulmod(diff, a.q0_inv, a.red1);
-        v += (u128)a.q0 * h;
-    }
-    const u128 delta = ((u128)a.delta_hi << 64) | a.delta_lo;
-    const u128 num = v + (((u128)a.half_hi << 64) | a.half_lo);
-    // quotient <= 2^32 + 1: a double-precision estimate is within one of it
-    const double nd = fma((double)(uint64_t)(num >> 64), 18446744073709551616.0,
-                          (double)(uint64_t)num);
-    uint64_t est = (uint64_t)(nd * a.delta_inv);
-    u128 prod = delta * est;                    // about num: no overflow
-    if (prod > num) {                           // one too many
-        est -= 1;
-        prod -= delta;
-    }
-    if (num - prod >= delta) est += 1;          // one too few
-    a.m_hat[gid] = est & a.t_mask;
-}
-
-// The same for three and four limbs: Q < 2^248, so the reconstructed phase and Delta take
-// four 64-bit words (least significant first).  Mixed-radix form of the Chinese remainder
-// theorem: phi = a_0 + q_0 (a_1 + q_1 (a_2 + q_2 a_3)) with
-//   a_j = ( ... ((phi_j - a_0) q_0^-1 - a_1) q_1^-1 - ... - a_{j-1}) q_{j-1}^-1  mod q_j,
-// all of it 64-bit modular arithmetic; only the final Horner evaluation is wide.
+template <int W>
 struct Wide {
-    uint64_t w[4];
+    uint64_t w[W];
 };
 
-__device__ __forceinline__ Wide wide_mul_add(const Wide &a, uint64_t m, uint64_t add)   // a m + add
+template <int W>
+__device__ __forceinline__ Wide<W> wide_mul_add(const Wide<W> &a, uint64_t m, uint64_t add)    // a m + add
 {
-    Wide r;
+    Wide<W> r;
     u128 carry = add;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < W; ++i) {
         const u128 p = (u128)a.w[i] * m + carry;
         r.w[i] = (uint64_t)p;
         carry = p >> 64;
@@ -210,12 +189,13 @@ __device__ __forceinline__ Wide wide_mul_add(const Wide &a, uint64_t m, uint64_t
     return r;
 }
 
-__device__ __forceinline__ Wide wide_add(const Wide &a, const Wide &b)
+template <int W>
+__device__ __forceinline__ Wide<W> wide_add(const Wide<W> &a, const Wide<W> &b)
 {
-    Wide r;
+    Wide<W> r;
     u128 carry = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < W; ++i) {
         const u128 t = (u128)a.w[i] + b.w[i] + carry;
         r.w[i] = (uint64_t)t;
         carry = t >> 64;
@@ -223,12 +203,13 @@ __device__ __forceinline__ Wide wide_add(const Wide &a, const Wide &b)
     return r;
 }
 
-// a - b modulo 2^256 and whether it borrowed (a < b)
-__device__ __forceinline__ bool wide_sub(const Wide &a, const Wide &b, Wide &r)
+// a - b modulo 2^(64 W) and whether it borrowed (a < b)
+template <int W>
+__device__ __forceinline__ bool wide_sub(const Wide<W> &a, const Wide<W> &b, Wide<W> &r)
 {
     uint64_t borrow = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < W; ++i) {
         const u128 t = (u128)a.w[i] - b.w[i] - borrow;
         r.w[i] = (uint64_t)t;
         borrow = (uint64_t)(t >> 64) & 1u;
@@ -236,62 +217,55 @@ __device__ __forceinline__ bool wide_sub(const Wide &a, const Wide &b, Wide &r)
     return borrow != 0;
 }
 
-struct DecodeWideArgs {
-    const uint64_t *phi;    // [T][L][N]
-    uint64_t *m_hat;        // [T][N]
-    int L, logN;            // L = 3 or 4
-    uint64_t total;         // T * N
-    Limb red[kMaxLimbs];
-    uint64_t inv[kMaxLimbs][kMaxLimbs];     // inv[i][j] = q_i^-1 mod q_j for i < j
-    Wide delta, half;       // Delta and floor(Delta / 2)
-    double delta_inv;       // 1 / Delta, rounded
-    uint64_t t_mask;
-};
+// floor((phi + half) / Delta) from an estimate within one of it, for the phase with these digits
+template <int L>
+__device__ __forceinline__ uint64_t settle_quotient(const DecodeArgs &a, const uint64_t (&digit)[L], uint64_t est)
+{
+    Wide<L> num = {}, delta, half;
+    num.w[0] = digit[L - 1];
+#pragma unroll
+    for (int j = L - 2; j >= 0; --j) num = wide_mul_add<L>(num, a.q[j], digit[j]);
+#pragma unroll
+    for (int i = 0; i < L; ++i) {
+        delta.w[i] = a.delta[i];
+        half.w[i] = a.half[i];
+    }
+    num = wide_add<L>(num, half);               // < 1.5 Q: fits
+    const Wide<L> prod = wide_mul_add<L>(delta, est, 0);    // about num
+    Wide<L> rem, over;
+    if (wide_sub<L>(num, prod, rem)) {          // one too many
+        est -= 1;
+        rem = wide_add<L>(rem, delta);          // wraps back to num - est Delta
+    }
+    return wide_sub<L>(rem, delta, over) ? est : est + 1;   // one too few
+}
 
-__global__ __launch_bounds__(256) void rlwe_decode_wide_kernel(DecodeWideArgs a)
+template <int L>
+__global__ __launch_bounds__(256) void rlwe_decode_kernel(const DecodeArgs a)
 {
     const uint64_t gid = (uint64_t)blockIdx.x * 256u + threadIdx.x;
     if (gid >= a.total) return;
     const uint64_t N = 1ull << a.logN;
     const uint64_t row = gid >> a.logN, c = gid & (N - 1);
-    const uint64_t *const ph = a.phi + row * (uint64_t)a.L * N + c;
-    uint64_t digit[kMaxLimbs] = {0, 0, 0, 0};
-    digit[0] = ph[0];
+    const uint64_t *const ph = a.phi + row * (uint64_t)L * N + c;
+    uint64_t digit[L];
 #pragma unroll
-    for (int j = 1; j < kMaxLimbs; ++j) {
-        if (j >= a.L) break;
-        const Limb &P = a.red[j];
-        uint64_t v = ph[(uint64_t)j * N];
+    for (int j = 0; j < L; ++j) digit[j] = ph[(uint64_t)j * N];
 #pragma unroll
-        for (int i = 0; i < j; ++i) {
-            const uint64_t d = barrett128(0, digit[i], P);      // a_i mod q_j
-            v = v + P.q - d;
-            v = v >= P.q ? v - P.q : v;
-            v = mulmod(v, a.inv[i][j], P);
-        }
-        digit[j] = v;
+    for (int j = 1; j < L; ++j) {
+        const uint64_t nq = negated(a.q[j]);
+        uint64_t v = digit[j];
+#pragma unroll
+        for (int i = 0; i < j; ++i) v = mul_lazy(v + (a.above[i][j] - digit[i]), a.inv[i][j], nq);
+        digit[j] = cond_sub(v, nq);             // below 2 q_j -> below q_j
     }
-    Wide v = {{a.L == 4 ? digit[3] : 0, 0, 0, 0}};
-    if (a.L == 4) v = wide_mul_add(v, a.red[2].q, digit[2]);
-    else v.w[0] = digit[2];
-    v = wide_mul_add(v, a.red[1].q, digit[1]);
-    v = wide_mul_add(v, a.red[0].q, digit[0]);
-    const Wide num = wide_add(v, a.half);
-    // quotient <= 2^32 + 1: a double-precision estimate is within one of it
-    const double two64 = 18446744073709551616.0;
-    double nd = (double)num.w[3];
-    nd = fma(nd, two64, (double)num.w[2]);
-    nd = fma(nd, two64, (double)num.w[1]);
-    nd = fma(nd, two64, (double)num.w[0]);
-    uint64_t est = (uint64_t)(nd * a.delta_inv);
-    Wide prod = wide_mul_add(a.delta, est, 0);  // about num: no overflow
-    Wide rem;
-    if (wide_sub(num, prod, rem)) {             // one too many
-        est -= 1;
-        rem = wide_add(rem, a.delta);           // wraps back to num - (est) Delta
-    }
-    Wide over;
-    if (!wide_sub(rem, a.delta, over)) est += 1;    // one too few
+    double num = (double)digit[L - 1];
+#pragma unroll
+    for (int j = L - 2; j >= 0; --j) num = fma(num, a.q_d[j], (double)digit[j]);
+    const double quo = (num + a.half_d) * a.delta_inv;
+    const double whole = floor(quo), frac = quo - whole;
+    uint64_t est = (uint64_t)whole;
+    if (frac < 0x1p-14 || frac > 1.0 - 0x1p-14) est = settle_quotient<L>(a, digit, est);
     a.m_hat[gid] = est & a.t_mask;
 }
 
@@ -562,43 +536,33 @@ int nimbus_rlwe_decode(const uint64_t *phi, int T, int N, int L, const uint64_t 
     if (ranges_overlap(m_hat, (size_t)total * sizeof(uint64_t), phi, (size_t)total * (size_t)L * sizeof(uint64_t)))
         return NIMBUS_COP_ERR_INVALID_ARG;
     const dim3 grid((unsigned)((total + 255u) / 256u));
+    DecodeArgs a{};
+    a.phi = phi;
+    a.m_hat = m_hat;
+    a.logN = log2_exact(N);
+    a.total = total;
+    for (int j = 0; j < L; ++j) {
+        const uint64_t q = moduli[j];
+        a.q[j] = q;
+        a.q_d[j] = (double)q;
+        for (int i = 0; i < j; ++i) {
+            a.inv[i][j] = Twiddle{inv[i][j], (uint64_t)(((u128)inv[i][j] << 64) / q)};
+            a.above[i][j] = (moduli[i] / q + 1) * q;
+        }
+    }
+    for (int i = 0; i < kMaxLimbs; ++i) {
+        a.delta[i] = sc.delta.w[i];
+        a.half[i] = sc.half.w[i];
+    }
+    a.half_d = hw_to_double(sc.half);
+    a.delta_inv = sc.delta_inv;
+    a.t_mask = (1ull << t_bits) - 1;
     hipError_t e;
-    if (L <= 2) {
-        DecodeArgs a{};
-        a.phi = phi;
-        a.m_hat = m_hat;
-        a.L = L;
-        a.logN = log2_exact(N);
-        a.total = total;
-        a.q0 = moduli[0];
-        if (L == 2) {
-            a.red1 = limbs.limb[1].red;
-            a.q0_inv = inv[0][1];
-        }
-        a.delta_hi = sc.delta.w[1];
-        a.delta_lo = sc.delta.w[0];
-        a.half_hi = sc.half.w[1];
-        a.half_lo = sc.half.w[0];
-        a.delta_inv = sc.delta_inv;
-        a.t_mask = (1ull << t_bits) - 1;
-        e = launch(rlwe_decode_kernel, grid, dim3(256), (hipStream_t)stream, a);
-    } else {
-        DecodeWideArgs a{};
-        a.phi = phi;
-        a.m_hat = m_hat;
-        a.L = L;
-        a.logN = log2_exact(N);
-        a.total = total;
-        for (int l = 0; l < L; ++l) a.red[l] = limbs.limb[l].red;
-        for (int i = 0; i < kMaxLimbs; ++i)
-            for (int j = 0; j < kMaxLimbs; ++j) a.inv[i][j] = inv[i][j];
-        for (int i = 0; i < 4; ++i) {
-            a.delta.w[i] = sc.delta.w[i];
-            a.half.w[i] = sc.half.w[i];
-        }
-        a.delta_inv = sc.delta_inv;
-        a.t_mask = (1ull << t_bits) - 1;
-        e = launch(rlwe_decode_wide_kernel, grid, dim3(256), (hipStream_t)stream, a);
+    switch (L) {
+    case 1: e = launch(rlwe_decode_kernel<1>, grid, dim3(256), (hipStream_t)stream, a); break;
+    case 2: e = launch(rlwe_decode_kernel<2>, grid, dim3(256), (hipStream_t)stream, a); break;
+    case 3: e = launch(rlwe_decode_kernel<3>, grid, dim3(256), (hipStream_t)stream, a); break;
+    default: e = launch(rlwe_decode_kernel<4>, grid, dim3(256), (hipStream_t)stream, a); break;
     }
     return e == hipSuccess ? NIMBUS_COP_OK : NIMBUS_COP_ERR_LAUNCH;
 }
