@@ -617,7 +617,10 @@ int nimbus_rlwe_encrypt(const uint64_t *W, int k, int n, int t_bits, int N, int 
             ranges_overlap(ctW, ct_bytes, e, rows * (size_t)N))
             return NIMBUS_COP_ERR_INVALID_ARG;
     }
-    for (int l = 0; l < L; ++l) a.limbs.limb[l].delta = hw_mod(sc.delta, moduli[l]);
+    for (int l = 0; l < L; ++l) {
+        const uint64_t d = hw_mod(sc.delta, moduli[l]);
+        a.limbs.limb[l].delta = Twiddle{d, (uint64_t)(((u128)d << 64) / moduli[l])};
+    }
     a.tables = (const Twiddle *)tables;
     a.L = L;
     a.src = a_poly;

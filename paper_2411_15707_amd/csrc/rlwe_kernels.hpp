@@ -34,7 +34,7 @@ struct RlweLimb {
     uint64_t psi;       // primitive 2N-th root of unity mod q (setup only)
     uint64_t psi_inv;   // its inverse (setup only)
     uint64_t n_inv;     // N^-1 mod q (setup only)
-    uint64_t delta;     // floor(Q / t) mod q (encryption only)
+    Twiddle delta;      // floor(Q / t) mod q (encryption only)
     uint32_t fold_m;    // floor(2^(64 + fold_k) / q), below 2^32 (see fold(); q >= 2^34 only)
     uint32_t fold_k;    // bit length of q minus 33
 };
@@ -658,15 +658,18 @@ __device__ __forceinline__ uint64_t encrypt_weight(const PolyArgs &a, uint32_t r
     const uint32_t col = ch * (uint32_t)N + c;
     return col < (uint32_t)a.n ? a.W[(size_t)i * a.n + col] : 0;
 }
-// c0 = Delta w + e - a s  for the weight w and the error ev of the coefficient, as < q
-__device__ __forceinline__ uint64_t finish_encrypt(uint64_t as, uint64_t w, int ev, const RlweLimb &P)
+// c0 = Delta w + e - a s  for the weight w and the error ev of the coefficient, as < q.  The product
+// by Delta is one by a table constant (a reduction of its 128 bits took three times the
+// instructions: 768 rows of 4096 coefficients, two limbs, 85.9 us, now 82.7).
+__device__ __forceinline__ uint64_t finish_encrypt(uint64_t as, uint64_t w, int ev, const RlweLimb &P, const Mod &md)
 {
     const uint64_t q = P.red.q;
-    uint64_t v = barrett128(__umul64hi(P.delta, w), P.delta * w, P.red);       // w < t < q
-    v += ev < 0 ? q - (uint64_t)(-ev) : (uint64_t)ev;
-    v += q - as;                                // < 3q
-    v = v >= q ? v - q : v;
-    return v >= q ? v - q : v;
+    int64_t u = (int64_t)(q - as) + ev;             // from -127 to q + 127
+    u = u < 0 ? u + (int64_t)q : u;
+    uint64_t v = mul_lazy(w, P.delta, md.nq) + (uint64_t)u;     // below 3q + 127
+    v = cond_sub(v, md.n2q);
+    v = cond_sub(v, md.nq);
+    return v;
 }
 
 // PRE = 0: the whole product and what follows it in one kernel.  PRE = 1 (ring of 2^15
@@ -756,7 +759,7 @@ __global__ __launch_bounds__(threads_for(LOGN - PRE, MAXS)) void rlwe_poly_kerne
         if constexpr (PRE != 0) {
             out[h * NP + mine(i)] = as;
         } else if constexpr (ENCRYPT) {
-            out[mine(i)] = finish_encrypt(as, addend[i], err[i], P);
+            out[mine(i)] = finish_encrypt(as, addend[i], err[i], P, md);
         } else {
             out[mine(i)] = finish_phase(as, addend[i], q);
         }
@@ -785,8 +788,11 @@ __global__ __launch_bounds__(256) void rlwe_join_kernel(PolyArgs a, int logN, ui
     uint64_t hi = mul_lazy(u + q - v, w0_inv, 0 - q);       // [0, 2q)
     hi = hi >= q ? hi - q : hi;
     if constexpr (ENCRYPT) {
-        out[c] = finish_encrypt(lo, encrypt_weight(a, row, c, N), a.e[(size_t)row * N + c], P);
-        out[c + NP] = finish_encrypt(hi, encrypt_weight(a, row, c + NP, N), a.e[(size_t)row * N + c + NP], P);
+        // (the limb is not uniform here: no scalar registers for its constants)
+        const Mod md{q, 2 * q, 0 - q, 0 - 2 * q, 0, 0};
+        out[c] = finish_encrypt(lo, encrypt_weight(a, row, c, N), a.e[(size_t)row * N + c], P, md);
+        out[c + NP] =
+            finish_encrypt(hi, encrypt_weight(a, row, c + NP, N), a.e[(size_t)row * N + c + NP], P, md);
     } else {
         const uint64_t *const c0 = a.src + (((size_t)row * 2 + 0) * a.L + l) * N;
         out[c] = finish_phase(lo, c0[c], q);
