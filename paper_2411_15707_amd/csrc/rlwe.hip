@@ -155,7 +155,7 @@ __global__ __launch_bounds__(256) void rlwe_table_set_kernel(Twiddle *__restrict
 // integer (never for a ciphertext that decrypts with noise to spare) is it settled with integers
 // of L words.
 //
-// Bound by HBM: (L + 1) 8 bytes a coefficient.  256 x 8192 coefficients of three limbs: 15 us; 26.5 with
+// Bound by HBM: (L + 1) 8 bytes a coefficient.  256 x 8192 coefficients of three limbs: 12.6 us; 26.5 with
 // a reduction of a 128-bit value per step and four-word integers throughout.
 struct DecodeArgs {
     const uint64_t *phi;    // [T][L][N]
