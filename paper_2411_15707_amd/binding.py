@@ -45,6 +45,8 @@ LOADER_SYMBOLS = (
     "nimbus_loader_release",
 )
 
+ROUTE_SYMBOLS = ("nimbus_route_prepare", "nimbus_route_matmul")
+
 RLWE_SYMBOLS = (
     "nimbus_rlwe_tables_bytes",
     "nimbus_rlwe_setup",
@@ -115,6 +117,10 @@ def load_library():
     lib.nimbus_calib_stream_read.argtypes = [vp, sz, vp, vp]
     lib.nimbus_calib_butterflies.restype = ctypes.c_longlong
     lib.nimbus_calib_butterflies.argtypes = [ci, ci, ctypes.c_ulonglong, vp, sz, vp]
+    lib.nimbus_route_prepare.restype = ci
+    lib.nimbus_route_prepare.argtypes = [ci, ci, ci, ci, vp, ctypes.c_char_p, sz]
+    lib.nimbus_route_matmul.restype = ci
+    lib.nimbus_route_matmul.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci, vp, ci, ctypes.c_char_p, sz]
     lib.nimbus_rlwe_tables_bytes.restype = sz
     lib.nimbus_rlwe_tables_bytes.argtypes = [ci, ci]
     lib.nimbus_rlwe_setup.restype = ci
@@ -412,6 +418,27 @@ def nimbus_calib_stream_read(src, sink, stream=None) -> int:
     if n < 0:
         raise NimbusCopError(NIMBUS_INVALID, "nimbus_calib_stream_read")
     return int(n)
+
+
+# ---------------------------------------------------------------------------
+# which kernels a call launches (host only): lines "kernel<...> grid=x,y block=threads"
+# ---------------------------------------------------------------------------
+def nimbus_route_prepare(k, n, N, L, moduli) -> list:
+    text = ctypes.create_string_buffer(4096)
+    rc = load_library().nimbus_route_prepare(k, n, N, L, _moduli(moduli), text, len(text))
+    if rc != 0:
+        raise NimbusCopError(rc, "nimbus_route_prepare")
+    return text.value.decode().splitlines()
+
+
+def nimbus_route_matmul(m, k, x_bits, n, N, L, moduli, masked=True, staged=False, count=1) -> list:
+    """staged=False: nimbus_cop_matmul_prepared; True: the staged call, or the batch of `count`"""
+    text = ctypes.create_string_buffer(4096)
+    rc = load_library().nimbus_route_matmul(int(bool(staged)), count, m, k, x_bits, n, N, L, _moduli(moduli),
+                                            int(bool(masked)), text, len(text))
+    if rc != 0:
+        raise NimbusCopError(rc, "nimbus_route_matmul")
+    return text.value.decode().splitlines()
 
 
 # ---------------------------------------------------------------------------

@@ -2,7 +2,13 @@
 // Declarations and the contract of every entry point: include/nimbus_cop.h.
 #include "cop_common.hpp"
 #include "../../include/nimbus_cop.h"
+#include "../../include/nimbus_route.h"
+#include <cxxabi.h>
+#include <dlfcn.h>
 #include <mutex>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
 
 namespace nimbus {
 
@@ -177,6 +183,48 @@ static hipError_t stage_and_matmul(const Problem &p, const uint64_t *X, void *wo
         if (e != hipSuccess) return e;
     }
     return launch_cop_thin(lo, 1, X, 0, &staged_lo, &prepared, &mask, wide ? out : nullptr, &out, stream);
+}
+
+// ---- launches written down (include/nimbus_route.h) ----
+thread_local LaunchLog *launch_log = nullptr;
+
+// "name<template arguments>" of a kernel, from the symbol of its handle; empty if it has none
+static void kernel_name(const void *kernel, char *name, size_t size)
+{
+    name[0] = 0;
+    Dl_info info;
+    if (!dladdr(kernel, &info) || !info.dli_sname || info.dli_saddr != kernel) return;
+    int status = -1;
+    char *const full = abi::__cxa_demangle(info.dli_sname, nullptr, nullptr, &status);
+    if (!full) return;
+    // "void nimbus::name<...>(parameters)": an argument list may hold parentheses of its own
+    char *end = strstr(full, ">(");
+    if (end) end[1] = 0;
+    else if ((end = strchr(full, '(')) != nullptr) *end = 0;
+    const char *const from = strstr(full, "nimbus::");
+    snprintf(name, size, "%s", from ? from + strlen("nimbus::") : full);
+    free(full);
+}
+
+// runs the dispatch with its launches written down and prints them
+template <typename F>
+static int route(F &&dispatch, char *text, size_t size)
+{
+    LaunchLog log{};
+    launch_log = &log;
+    const hipError_t e = dispatch();
+    launch_log = nullptr;
+    if (e != hipSuccess) return NIMBUS_COP_ERR_LAUNCH;
+    size_t at = 0;
+    text[0] = 0;
+    for (int i = 0; i < log.count && at + 1 < size; ++i) {
+        char name[256];
+        kernel_name(log.at[i].kernel, name, sizeof(name));
+        const int len = snprintf(text + at, size - at, "%s grid=%u,%u block=%u\n", name, log.at[i].grid.x,
+                                 log.at[i].grid.y, log.at[i].block.x);
+        if (len > 0) at += (size_t)len;
+    }
+    return NIMBUS_COP_OK;
 }
 
 }  // namespace nimbus
@@ -467,6 +515,43 @@ int nimbus_cop_check_inputs(const uint64_t *X, int m, int k, int x_bits,
     if (rc != NIMBUS_COP_OK) return rc;
     const hipError_t e = launch_cop_check(p, X, ctW, mask, violations, (hipStream_t)stream);
     return e == hipSuccess ? NIMBUS_COP_OK : NIMBUS_COP_ERR_LAUNCH;
+}
+
+// (the addresses below stand for buffers that nothing reads)
+int nimbus_route_prepare(int k, int n, int N, int L, const uint64_t *moduli, char *text, size_t size)
+{
+    if (!text || size == 0) return NIMBUS_COP_ERR_INVALID_ARG;
+    Problem p;
+    const int rc = make_problem(0, k, 0, n, N, L, moduli, false, &p);
+    if (rc != NIMBUS_COP_OK) return rc;
+    return route([&] { return launch_prepare(p, (const uint64_t *)16, (void *)16, nullptr); }, text, size);
+}
+
+int nimbus_route_matmul(int staged, int count, int m, int k, int x_bits, int n, int N, int L,
+                        const uint64_t *moduli, int masked, char *text, size_t size)
+{
+    if (!text || size == 0) return NIMBUS_COP_ERR_INVALID_ARG;
+    if (count < 1 || count > NIMBUS_COP_MAX_BATCH || (!staged && count != 1)) return NIMBUS_COP_ERR_INVALID_ARG;
+    if (count > 1 && x_bits > 32) return NIMBUS_COP_ERR_UNSUPPORTED;
+    Problem p;
+    const int rc = make_problem(m, k, x_bits, n, N, L, moduli, true, &p);
+    if (rc != NIMBUS_COP_OK) return rc;
+    if (!prepared_path_supported(p) || (!staged && !staging_fits(m, k))) return NIMBUS_COP_ERR_UNSUPPORTED;
+    const void *in[NIMBUS_COP_MAX_BATCH];
+    const uint64_t *masks[NIMBUS_COP_MAX_BATCH];
+    uint64_t *outs[NIMBUS_COP_MAX_BATCH];
+    for (int i = 0; i < NIMBUS_COP_MAX_BATCH; ++i) {
+        in[i] = (const void *)16;
+        masks[i] = masked ? (const uint64_t *)16 : nullptr;
+        outs[i] = (uint64_t *)16;
+    }
+    return route(
+        [&] {
+            if (!staged) return stage_and_matmul(p, (const uint64_t *)16, (void *)16, in[0], masks[0], outs[0], nullptr);
+            if (count == 1) return matmul_all(p, in[0], in[0], masks[0], outs[0], nullptr);
+            return launch_cop_mfma_batch(p, count, in, in, masks, nullptr, outs, nullptr);
+        },
+        text, size);
 }
 
 const char *nimbus_cop_strerror(int status)

@@ -89,6 +89,16 @@ hipError_t launch_cop_check(const Problem &p, const uint64_t *X, const uint64_t 
 hipError_t launch_cop_pack(const Problem &p, const uint64_t *rows, const uint64_t *mask,
                            uint64_t *packed, hipStream_t stream);
 
+// The launches of a call, written down instead of made: see include/nimbus_route.h.
+struct LaunchLog {
+    struct {
+        const void *kernel;
+        dim3 grid, block;
+    } at[8];
+    int count;
+};
+extern thread_local LaunchLog *launch_log;      // null but inside nimbus_route_*(), per thread
+
 // Launches a kernel and returns the status of this launch alone.  (The status the runtime
 // keeps per thread would also hand out, and clear, an error that an unrelated earlier call
 // left behind.)
@@ -96,6 +106,11 @@ template <typename... KArgs>
 inline hipError_t launch(void (*kernel)(KArgs...), dim3 grid, dim3 block, hipStream_t stream,
                          std::common_type_t<KArgs>... args)
 {
+    if (LaunchLog *const log = launch_log) {
+        if (log->count < (int)(sizeof(log->at) / sizeof(log->at[0])))
+            log->at[log->count++] = {(const void *)kernel, grid, block};
+        return hipSuccess;
+    }
     void *ptrs[] = {(void *)&args...};
     return hipLaunchKernel((const void *)kernel, grid, block, ptrs, 0, stream);
 }

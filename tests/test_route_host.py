@@ -1,0 +1,56 @@
+"""Which kernels a call launches, asked of the dispatch on the host (include/nimbus_route.h)."""
+import ctypes
+import os
+import re
+
+import pytest
+
+import cop_inputs as ci
+import paper_2411_15707_amd as nc
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+LINE = re.compile(r"(\w+)<([^>]*)> grid=(\d+),(\d+) block=(\d+)$")
+
+
+def moduli_of(q_bits, L):
+    return ci.limb_primes(q_bits, 14, L)
+
+
+def test_header_binding_and_argument_checks():
+    text = open(os.path.join(ROOT, "include", "nimbus_route.h")).read()
+    text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
+    declared = sorted(set(re.findall(r"\b(nimbus_route_\w+)\s*\(", text)))
+    assert declared == sorted(nc.ROUTE_SYMBOLS)
+    lib = nc.load_library()
+    for name in declared:
+        assert hasattr(lib, name), name
+    mods = moduli_of(54, 1)
+    with pytest.raises(nc.NimbusCopError) as e:
+        nc.nimbus_route_prepare(0, 32, 32, 1, mods)
+    assert e.value.status == -1
+    with pytest.raises(nc.NimbusCopError) as e:
+        nc.nimbus_route_matmul(4, 50000, 20, 32, 32, 1, mods)       # k beyond the accumulators' bound
+    assert e.value.status == -2
+    with pytest.raises(nc.NimbusCopError) as e:
+        nc.nimbus_route_matmul(4, 64, 20, 32, 32, 1, mods, count=2)     # a batch is staged
+    assert e.value.status == -1
+    with pytest.raises(nc.NimbusCopError) as e:
+        nc.nimbus_route_matmul(4, 64, 40, 32, 32, 1, mods, staged=True, count=2)    # wide shares: no batch
+    assert e.value.status == -2
+    # a text longer than the buffer is cut off
+    text = ctypes.create_string_buffer(b"x" * 40)
+    mod = (ctypes.c_uint64 * 1)(*mods)
+    assert lib.nimbus_route_matmul(0, 1, 64, 768, 20, 32, 32, 1, mod, 1, text, 20) == 0
+    assert len(text.value) == 19 and text.raw[20:40] == b"x" * 20
+
+
+def test_every_launch_of_a_call_is_named():
+    """a BERT-base up-projection: one staging and one product kernel, the second alone when staged"""
+    cfg = ci.CONFIGS[3]
+    lines = nc.nimbus_route_matmul(cfg.m, cfg.k, cfg.t_bits, cfg.n, cfg.N, cfg.L, cfg.moduli)
+    assert [LINE.match(x).group(1) for x in lines] == ["x_planes_kernel", "cop_mfma_kernel"]
+    assert lines[1] == "cop_mfma_kernel<3, 7, true, true, false, 1> grid=256,1 block=512"
+    assert nc.nimbus_route_matmul(cfg.m, cfg.k, cfg.t_bits, cfg.n, cfg.N, cfg.L, cfg.moduli, staged=True) == lines[1:]
+    assert LINE.match(nc.nimbus_route_prepare(cfg.k, cfg.n, cfg.N, cfg.L, cfg.moduli)[0]).group(1) == "prepare_kernel"
+    # shares of two halves: a pass for each
+    assert len(nc.nimbus_route_matmul(cfg.m, cfg.k, 64, cfg.n, cfg.N, cfg.L, cfg.moduli, staged=True)) == 2
