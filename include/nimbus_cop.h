@@ -45,7 +45,7 @@
  * anything is enqueued: `out` is untouched.  NIMBUS_COP_ERR_LAUNCH means that
  * the HIP runtime refused a kernel launch; an entry point that launches more
  * than one kernel (nimbus_cop_matmul_prepared and its _static variant,
- * nimbus_cop_prepare, nimbus_cop_check_inputs, and the staged entry points
+ * nimbus_cop_check_inputs, and the staged entry points
  * for shares of more than 32 bits) may then already have enqueued the earlier
  * ones, and what its outputs and workspace hold is unspecified.  No C++
  * exception crosses this boundary.

@@ -105,6 +105,11 @@ static hipError_t prepare_impl(const Problem &p, const uint64_t *ctW, void *prep
     // 160.3).  With fewer k-blocks most of them would only meet at the barrier (100 x 65536: 23.8
     // and 20.8 us).
     if (KB >= 16) return go(std::integral_constant<int, 16>{});
+    // Fewer rows than a k-block has: one wave, so that the compute unit's waves all have tiles of their
+    // own (1 x 2^20 residues 58.4 us with 4 waves, 44.1 with 1; 20 x 2^20 87.6 and 60.4).  A whole
+    // k-block has sixteen loads in flight per lane as it is (32 x 2^20: 85.2 and 90.4).  A launch has
+    // fewer than 2^32 threads, so from 2^24 column tiles on it is one wave too.
+    if (p.k < kTile || CT >= (1u << 24)) return go(std::integral_constant<int, 1>{});
     return go(std::integral_constant<int, 4>{});
 }
 

@@ -32,10 +32,11 @@ def prepared_reference(ctW, moduli, N):
     return np.ascontiguousarray(tiles).reshape(-1).view(np.uint8), sums
 
 
-# k on both sides of a k-block, of the sixteen k-blocks from which sixteen waves share a tile, and
-# of two rounds of them; one column tile and several; both plane counts; tiles of two limbs
+# k on both sides of a k-block (one wave per tile below it), of the sixteen k-blocks from which
+# sixteen waves share a tile, and of two rounds of them; one column tile and several; both plane
+# counts; tiles of two limbs
 @pytest.mark.parametrize("k,n,N,L,q_bits", [
-    (1, 32, 32, 1, 50), (31, 40, 32, 2, 54), (33, 64, 64, 1, 62), (480, 32, 32, 1, 54),
+    (32, 96, 32, 2, 54), (17, 2048, 1024, 2, 59), (1, 32, 32, 1, 50), (31, 40, 32, 2, 54), (33, 64, 64, 1, 62), (480, 32, 32, 1, 54),
     (481, 32, 32, 2, 59), (512, 100, 64, 1, 50), (545, 32, 32, 1, 55), (1025, 64, 64, 1, 62),
 ])
 def test_prepared_weights_have_the_documented_layout(k, n, N, L, q_bits):

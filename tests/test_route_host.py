@@ -54,3 +54,15 @@ def test_every_launch_of_a_call_is_named():
     assert LINE.match(nc.nimbus_route_prepare(cfg.k, cfg.n, cfg.N, cfg.L, cfg.moduli)[0]).group(1) == "prepare_kernel"
     # shares of two halves: a pass for each
     assert len(nc.nimbus_route_matmul(cfg.m, cfg.k, 64, cfg.n, cfg.N, cfg.L, cfg.moduli, staged=True)) == 2
+
+
+def test_every_launch_of_the_setup_has_fewer_than_2_to_32_threads():
+    """the runtime refuses larger ones: 2^29 columns of one row (124 GB of planes) are a size that fits
+    the device's memory"""
+    for q_bits, k, n, N, L in [(54, 1, 2**28, 65536, 1), (62, 1, 2**28 + 1, 65536, 1), (54, 32, 2**28, 65536, 1),
+                               (54, 33, 2**28, 65536, 1), (54, 96, 2**27, 65536, 2), (54, 31, 4096, 4096, 1),
+                               (54, 97, 4096, 4096, 1), (54, 511, 4096, 4096, 1), (54, 768, 2**20, 65536, 4)]:
+        line = LINE.match(nc.nimbus_route_prepare(k, n, N, L, ci.limb_primes(q_bits, 17, L))[0])
+        blocks, threads = int(line.group(3)), int(line.group(5))
+        assert blocks * threads < 2**32, (line.group(0), k, n, N, L)
+        assert blocks == -(-n // N) * 2 * L * N // 32 and int(line.group(4)) == 1
