@@ -30,9 +30,10 @@ int nimbus_route_prepare(int k, int n, int N, int L, const uint64_t *moduli, cha
  * staged = 1: nimbus_cop_matmul_staged with count = 1, nimbus_cop_matmul_staged_batch of `count`
  *             problems otherwise.
  * masked: with (1) or without (0) a mask.
+ * units:  the number of compute units the rules are to assume, 0 for the current device's.
  */
 int nimbus_route_matmul(int staged, int count, int m, int k, int x_bits, int n, int N, int L,
-                        const uint64_t *moduli, int masked, char *text, size_t size);
+                        const uint64_t *moduli, int masked, int units, char *text, size_t size);
 
 #ifdef __cplusplus
 }

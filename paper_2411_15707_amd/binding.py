@@ -120,7 +120,7 @@ def load_library():
     lib.nimbus_route_prepare.restype = ci
     lib.nimbus_route_prepare.argtypes = [ci, ci, ci, ci, vp, ctypes.c_char_p, sz]
     lib.nimbus_route_matmul.restype = ci
-    lib.nimbus_route_matmul.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci, vp, ci, ctypes.c_char_p, sz]
+    lib.nimbus_route_matmul.argtypes = [ci, ci, ci, ci, ci, ci, ci, ci, vp, ci, ci, ctypes.c_char_p, sz]
     lib.nimbus_rlwe_tables_bytes.restype = sz
     lib.nimbus_rlwe_tables_bytes.argtypes = [ci, ci]
     lib.nimbus_rlwe_setup.restype = ci
@@ -431,11 +431,12 @@ def nimbus_route_prepare(k, n, N, L, moduli) -> list:
     return text.value.decode().splitlines()
 
 
-def nimbus_route_matmul(m, k, x_bits, n, N, L, moduli, masked=True, staged=False, count=1) -> list:
-    """staged=False: nimbus_cop_matmul_prepared; True: the staged call, or the batch of `count`"""
+def nimbus_route_matmul(m, k, x_bits, n, N, L, moduli, masked=True, staged=False, count=1, units=0) -> list:
+    """staged=False: nimbus_cop_matmul_prepared; True: the staged call, or the batch of `count`;
+    units: compute units to assume (0: the device's)"""
     text = ctypes.create_string_buffer(4096)
     rc = load_library().nimbus_route_matmul(int(bool(staged)), count, m, k, x_bits, n, N, L, _moduli(moduli),
-                                            int(bool(masked)), text, len(text))
+                                            int(bool(masked)), units, text, len(text))
     if rc != 0:
         raise NimbusCopError(rc, "nimbus_route_matmul")
     return text.value.decode().splitlines()

@@ -208,9 +208,10 @@ static void kernel_name(const void *kernel, char *name, size_t size)
 
 // runs the dispatch with its launches written down and prints them
 template <typename F>
-static int route(F &&dispatch, char *text, size_t size)
+static int route(F &&dispatch, int assume_units, char *text, size_t size)
 {
     LaunchLog log{};
+    log.compute_units = assume_units;
     launch_log = &log;
     const hipError_t e = dispatch();
     launch_log = nullptr;
@@ -524,13 +525,13 @@ int nimbus_route_prepare(int k, int n, int N, int L, const uint64_t *moduli, cha
     Problem p;
     const int rc = make_problem(0, k, 0, n, N, L, moduli, false, &p);
     if (rc != NIMBUS_COP_OK) return rc;
-    return route([&] { return launch_prepare(p, (const uint64_t *)16, (void *)16, nullptr); }, text, size);
+    return route([&] { return launch_prepare(p, (const uint64_t *)16, (void *)16, nullptr); }, 0, text, size);
 }
 
 int nimbus_route_matmul(int staged, int count, int m, int k, int x_bits, int n, int N, int L,
-                        const uint64_t *moduli, int masked, char *text, size_t size)
+                        const uint64_t *moduli, int masked, int units, char *text, size_t size)
 {
-    if (!text || size == 0) return NIMBUS_COP_ERR_INVALID_ARG;
+    if (!text || size == 0 || units < 0) return NIMBUS_COP_ERR_INVALID_ARG;
     if (count < 1 || count > NIMBUS_COP_MAX_BATCH || (!staged && count != 1)) return NIMBUS_COP_ERR_INVALID_ARG;
     if (count > 1 && x_bits > 32) return NIMBUS_COP_ERR_UNSUPPORTED;
     Problem p;
@@ -551,7 +552,7 @@ int nimbus_route_matmul(int staged, int count, int m, int k, int x_bits, int n, 
             if (count == 1) return matmul_all(p, in[0], in[0], masks[0], outs[0], nullptr);
             return launch_cop_mfma_batch(p, count, in, in, masks, nullptr, outs, nullptr);
         },
-        text, size);
+        units, text, size);
 }
 
 const char *nimbus_cop_strerror(int status)

@@ -57,6 +57,9 @@ constexpr int kTileBytes = 1024;     // one 32 x 32 int8 operand tile
 // k is padded with zero byte planes to whole 32-value k-blocks
 inline int kblocks(int k) { return (k + kTile - 1) / kTile; }
 
+// compute units of the current device (256 without one)
+int compute_units();
+
 // launchers implemented in the kernel files; all return hipError_t
 hipError_t launch_cop_valu(const Problem &p, const uint64_t *X, const uint64_t *ctW,
                            const uint64_t *mask, uint64_t *out, hipStream_t stream);
@@ -96,6 +99,7 @@ struct LaunchLog {
         dim3 grid, block;
     } at[8];
     int count;
+    int compute_units;          // what the rules are to assume, 0: those of the device
 };
 extern thread_local LaunchLog *launch_log;      // null but inside nimbus_route_*(), per thread
 

@@ -740,9 +740,10 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// compute units of the current device (asked once per device)
-static int compute_units()
+// (asked once per device)
+int compute_units()
 {
+    if (launch_log && launch_log->compute_units > 0) return launch_log->compute_units;
     static std::atomic<int> cached[64];
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;

@@ -366,14 +366,14 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     const uint32_t quads = 16u * ((uint32_t)(KB + 1) / 2u);
     t.quads_magic = (uint32_t)(((1ull << 32) + quads - 1) / quads);     // (items below 2^16, Q below 2^13)
     // Slices of k: a compute unit holds one workgroup, so the launch takes as many rounds as there
-    // are multiples of 256 workgroups, and a round takes the stages of a slice and what starting and
+    // are multiples of that many workgroups, and a round takes the stages of a slice and what starting and
     // ending a workgroup costs, about three stages of eight waves.  (20 x 400 x 12288: two
     // slices in one round 16.0 us, four in two rounds 20.6.)
-    const uint64_t S = (uint64_t)(KB + 1) / 2u, groups = (uint64_t)CT * 2u;
+    const uint64_t S = (uint64_t)(KB + 1) / 2u, groups = (uint64_t)CT * 2u, cus = (uint64_t)compute_units();
     uint64_t least = ~0ull;
     for (uint32_t l = 0; l <= 3 && (1ull << l) <= S; ++l) {
         const uint64_t blocks = (groups + (8u >> l) - 1) / (8u >> l) * (uint64_t)count;
-        const uint64_t cost = (blocks + 255u) / 256u * (((S + (1u << l) - 1) >> l) + 3u);
+        const uint64_t cost = (blocks + cus - 1) / cus * (((S + (1u << l) - 1) >> l) + 3u);
         if (cost < least) {
             least = cost;
             t.log_ks = l;

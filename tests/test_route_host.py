@@ -40,7 +40,7 @@ def test_header_binding_and_argument_checks():
     # a text longer than the buffer is cut off
     text = ctypes.create_string_buffer(b"x" * 40)
     mod = (ctypes.c_uint64 * 1)(*mods)
-    assert lib.nimbus_route_matmul(0, 1, 64, 768, 20, 32, 32, 1, mod, 1, text, 20) == 0
+    assert lib.nimbus_route_matmul(0, 1, 64, 768, 20, 32, 32, 1, mod, 1, 0, text, 20) == 0
     assert len(text.value) == 19 and text.raw[20:40] == b"x" * 20
 
 
@@ -66,3 +66,12 @@ def test_every_launch_of_the_setup_has_fewer_than_2_to_32_threads():
         blocks, threads = int(line.group(3)), int(line.group(5))
         assert blocks * threads < 2**32, (line.group(0), k, n, N, L)
         assert blocks == -(-n // N) * 2 * L * N // 32 and int(line.group(4)) == 1
+
+
+def test_slices_of_few_rows_follow_the_compute_units():
+    """a wave per 16 columns and slice, eight to a workgroup: 1024 column groups are two slices on 256
+    compute units, four where there are twice as many and none on half of them"""
+    mods = moduli_of(54, 2)
+    for units, blocks in ((64, 128), (128, 128), (256, 256), (512, 512)):
+        line = nc.nimbus_route_matmul(1, 768, 20, 4096, 4096, 2, mods, staged=True, units=units)[0]
+        assert line.startswith("cop_thin_kernel") and f"grid={blocks},1 " in line, (units, line)
