@@ -335,7 +335,9 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-bool thin_applies(const Problem &p) { return p.m <= kThinRows; }
+// A launch has fewer than 2^32 threads: 2^30 columns and more (240 GB of planes of one k-block) are left
+// to the tile kernel, whose workgroups walk the tiles.
+bool thin_applies(const Problem &p) { return p.m <= kThinRows && p.C < (1ull << 30); }
 
 // the shares' planes of a workgroup fit the LDS
 static bool thin_planes_fit(const Problem &p)
@@ -346,7 +348,7 @@ static bool thin_planes_fit(const Problem &p)
 
 // With a second 16-row tile the splitting takes as long as the staging launch (m = 32 on 768 x 16384:
 // 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).
-bool thin_raw_applies(const Problem &p) { return p.m <= 16 && thin_planes_fit(p); }
+bool thin_raw_applies(const Problem &p) { return thin_applies(p) && p.m <= 16 && thin_planes_fit(p); }
 
 template <int DX, int DQ>
 static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int half_shift,

@@ -75,3 +75,13 @@ def test_slices_of_few_rows_follow_the_compute_units():
     for units, blocks in ((64, 128), (128, 128), (256, 256), (512, 512)):
         line = nc.nimbus_route_matmul(1, 768, 20, 4096, 4096, 2, mods, staged=True, units=units)[0]
         assert line.startswith("cop_thin_kernel") and f"grid={blocks},1 " in line, (units, line)
+
+
+@pytest.mark.parametrize("staged", [False, True])
+@pytest.mark.parametrize("m", [1, 16, 32])
+def test_every_launch_of_few_rows_has_fewer_than_2_to_32_threads(m, staged):
+    """a row on 2^30 columns: 240 GB of planes, within the device's memory"""
+    for n in (2**28, 2**29 - 65536, 2**29, 2**30 - 65536):
+        for line in nc.nimbus_route_matmul(m, 1, 20, n, 65536, 1, ci.limb_primes(54, 20, 1), staged=staged):
+            line = LINE.match(line)
+            assert int(line.group(3)) * int(line.group(5)) < 2**32, (n, line.group(0))
