@@ -77,7 +77,7 @@ hipError_t launch_cop_mfma(const Problem &p, const void *staged, const void *pre
                            hipStream_t stream);
 bool mfma_supported(const Problem &p);
 // few rows (cop_thin.hip): from staged shares, or (X, half_shift) from the shares themselves
-bool thin_applies(const Problem &p);
+bool thin_applies(const Problem &p, int count);
 bool thin_raw_applies(const Problem &p);
 hipError_t launch_cop_thin(const Problem &p, int count, const uint64_t *X, int half_shift,
                            const void *const *staged, const void *const *prepared,

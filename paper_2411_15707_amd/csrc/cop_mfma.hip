@@ -889,7 +889,7 @@ hipError_t launch_cop_mfma_batch(const Problem &p, int count, const void *const 
 {
     if (count < 1 || count > kMaxBatch) return hipErrorInvalidValue;
     // few rows: a kernel of their own (cop_thin.hip, with both sides measured)
-    if (thin_applies(p)) return launch_cop_thin(p, count, nullptr, 0, staged, prepared, masks, prev, outs, stream);
+    if (thin_applies(p, count)) return launch_cop_thin(p, count, nullptr, 0, staged, prepared, masks, prev, outs, stream);
     const int DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);
 #define NIMBUS_CASE(dx, dq) \
     if (DX == dx && DQ == dq) \

@@ -53,14 +53,19 @@ enum ThinShares {
     kRaw        // the shares themselves, split into planes in LDS once per workgroup
 };
 
+// stages in flight per wave: what 256 registers hold next to the accumulators, four at most
+constexpr int thin_depth(int DX, int DQ, int RT16, ThinShares from)
+{
+    const int accumulators = (DX + DQ - 1) * 4 * RT16;
+    const int stage = DQ * 4 + (from == kDirect ? DX * 4 * RT16 : 0);
+    const int fit = (256 - 40 - accumulators - (from == kDirect ? 0 : 20)) / stage;
+    return fit > 4 ? 4 : fit < 2 ? 2 : fit;
+}
+
 template <int DX, int DQ, int RT16, ThinShares FROM>
 struct Thin {
     static constexpr int ND = DX + DQ - 1;
-    static constexpr int A_REGS = DX * 4 * RT16, B_REGS = DQ * 4, ACC_REGS = ND * 4 * RT16;
-    // stages in flight per wave: what 256 registers hold next to the accumulators, four at most
-    static constexpr int STAGE_REGS = B_REGS + (FROM == kDirect ? A_REGS : 0);
-    static constexpr int FIT = (256 - 40 - ACC_REGS - (FROM == kDirect ? 0 : 20)) / STAGE_REGS;
-    static constexpr int PD = FIT > 4 ? 4 : FIT < 2 ? 2 : FIT;
+    static constexpr int PD = thin_depth(DX, DQ, RT16, FROM);
     // planes of the shares, [stage][16-row tile][plane][64 lanes][16 B]
     static constexpr int A_LDS = FROM == kDirect ? 0 : kThinSharesLds;
     // the slices' sums meet TP tiles at a time: two where eight waves' sums of two fit the LDS
@@ -335,10 +340,6 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-// A launch has fewer than 2^32 threads: 2^30 columns and more (240 GB of planes of one k-block) are left
-// to the tile kernel, whose workgroups walk the tiles.
-bool thin_applies(const Problem &p) { return p.m <= kThinRows && p.C < (1ull << 30); }
-
 // the shares' planes of a workgroup fit the LDS
 static bool thin_planes_fit(const Problem &p)
 {
@@ -346,9 +347,74 @@ static bool thin_planes_fit(const Problem &p)
     return S * tiles * planes_x(p.x_bits) * kTileBytes <= kThinSharesLds;
 }
 
+// How a launch is split, and about what it takes.
+struct ThinPlan {
+    uint32_t log_ks;        // KS = 2^log_ks slices of k
+    uint32_t blocks;        // workgroups of one problem
+    bool copied;            // staged planes through LDS (more than 16 rows)
+    uint64_t cost;          // tenths of a microsecond
+};
+
+static ThinPlan thin_plan(const Problem &p, int count)
+{
+    // Slices of k: a compute unit holds one workgroup, so the launch takes as many rounds as there
+    // are multiples of that many workgroups, and a round takes the stages of a slice and what
+    // starting and ending a workgroup costs, about three stages of eight waves.  (20 x 400 x 12288: two
+    // slices in one round 16.0 us, four in two rounds 20.6.)
+    const uint64_t S = (uint64_t)(kblocks(p.k) + 1) / 2u, groups = p.C / 16u, cus = (uint64_t)compute_units();
+    ThinPlan plan{};
+    uint64_t least = ~0ull, rounds = 0;
+    for (uint32_t l = 0; l <= 3 && (1ull << l) <= S; ++l) {
+        const uint64_t blocks = (groups + (8u >> l) - 1) / (8u >> l);
+        const uint64_t r = (blocks * (uint64_t)count + cus - 1) / cus;
+        const uint64_t cost = r * (((S + (1u << l) - 1) >> l) + 3u);
+        if (cost < least) {
+            least = cost;
+            rounds = r;
+            plan.log_ks = l;
+            plan.blocks = (uint32_t)blocks;
+        }
+    }
+    // The planes of 32 rows weigh nearly as much as the weights of a wave: eight waves that read the
+    // same ones (one slice) read them once, from LDS (32 x 768 x 24576: 31.5 us against 34.4); with
+    // several slices fewer waves share them and nobody waits for the copy (x 8192: 17.8 and 16.0).
+    plan.copied = p.m > 16 && plan.log_ks == 0 && thin_planes_fit(p);
+    // (whole rounds of the stages in flight: what is past the last one costs its products, but no loads)
+    const uint64_t stages = (S + (1u << plan.log_ks) - 1) >> plan.log_ks;
+    const uint64_t depth = (uint64_t)thin_depth(planes_x(p.x_bits), planes_q(p.q_bits_max), p.m <= 16 ? 1 : 2,
+                                                plan.copied ? kCopied : kDirect);
+    const uint64_t padded = (stages + depth - 1) / depth * depth;
+    plan.cost = rounds * ((p.m <= 16 ? 63u : plan.copied ? 107u : 80u) + 9u * (stages + padded)) +
+                13u * plan.blocks * (uint64_t)count / cus;
+    return plan;
+}
+
+// From staged shares: where this kernel's rounds take less than those of the tile kernel, which starts
+// and ends a workgroup faster but shares the chip's tiles out by whole rounds and has no slices of k.
+// Both estimates in tenths of a microsecond, fitted to 5461 sizes on 256 compute units (1 to 32 rows,
+// k from 32 to 3072, 256 to 131072 columns, every plane count, one to sixteen problems): the
+// kernel that they choose is 0.2 % slower than the better of the two on average; this one
+// everywhere 9 %, the tile kernel everywhere 20 %.  (us, this kernel and the tiles, 20-bit
+// shares, 54-bit moduli: 16 x 32 x 4096 9.0 and 5.8, 32 x 32 x 131072 48.5 and 36.2, 32 x 128 x 49152
+// 28.9 and 22.1, 16 x 256 x 16384 11.7 and 10.9; 16 x 256 x 24576 13.5 and 18.5, 32 x 512 x 4096
+// 9.1 and 13.3, 32 x 1024 x 65536 84.8 and 94.3.)
+// A launch has fewer than 2^32 threads: 2^30 columns and more (240 GB of planes of one k-block) are
+// left to the tile kernel in any case; its workgroups walk the tiles.
+static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (1ull << 30); }
+
+bool thin_applies(const Problem &p, int count)
+{
+    if (!thin_possible(p)) return false;
+    const uint64_t cus = (uint64_t)compute_units();
+    const uint64_t rounds = (p.C / (2u * kTile) * (uint64_t)count + cus - 1) / cus;
+    return thin_plan(p, count).cost < 20u + rounds * (47u + 6u * (uint64_t)kblocks(p.k));
+}
+
 // With a second 16-row tile the splitting takes as long as the staging launch (m = 32 on 768 x 16384:
-// 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).
-bool thin_raw_applies(const Problem &p) { return thin_applies(p) && p.m <= 16 && thin_planes_fit(p); }
+// 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).  Up to 16 rows without the staging launch
+// are ahead of staging and tiles at every k (8 x 32 x 4096 7.5 us a call and 8.4; even where a
+// k-block of 32-bit shares is all there is: 8.4 and 8.5, replayed from a graph 9.0 and 8.6).
+bool thin_raw_applies(const Problem &p) { return thin_possible(p) && p.m <= 16 && thin_planes_fit(p); }
 
 template <int DX, int DQ>
 static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int half_shift,
@@ -367,22 +433,9 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     t.half_shift = half_shift;
     const uint32_t quads = 16u * ((uint32_t)(KB + 1) / 2u);
     t.quads_magic = (uint32_t)(((1ull << 32) + quads - 1) / quads);     // (items below 2^16, Q below 2^13)
-    // Slices of k: a compute unit holds one workgroup, so the launch takes as many rounds as there
-    // are multiples of that many workgroups, and a round takes the stages of a slice and what starting and
-    // ending a workgroup costs, about three stages of eight waves.  (20 x 400 x 12288: two
-    // slices in one round 16.0 us, four in two rounds 20.6.)
-    const uint64_t S = (uint64_t)(KB + 1) / 2u, groups = (uint64_t)CT * 2u, cus = (uint64_t)compute_units();
-    uint64_t least = ~0ull;
-    for (uint32_t l = 0; l <= 3 && (1ull << l) <= S; ++l) {
-        const uint64_t blocks = (groups + (8u >> l) - 1) / (8u >> l) * (uint64_t)count;
-        const uint64_t cost = (blocks + cus - 1) / cus * (((S + (1u << l) - 1) >> l) + 3u);
-        if (cost < least) {
-            least = cost;
-            t.log_ks = l;
-        }
-    }
-    const uint32_t cgw = 8u >> t.log_ks;
-    const dim3 grid((uint32_t)((groups + cgw - 1) / cgw), (uint32_t)count), block(512);
+    const ThinPlan plan = thin_plan(p, count);
+    t.log_ks = plan.log_ks;
+    const dim3 grid(plan.blocks, (uint32_t)count), block(512);
     auto go_with = [&](auto rt_c, auto from_c, auto nb_c) {
         constexpr int NB = decltype(nb_c)::value;
         BatchPtrs<NB> b{};
@@ -409,10 +462,7 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     const std::integral_constant<int, 2> two;
     if (X) return go(one, raw);
     if (p.m <= 16) return go(one, direct);
-    // The planes of 32 rows weigh nearly as much as the weights of a wave: eight waves that read the
-    // same ones (one slice) read them once, from LDS (32 x 768 x 24576: 31.5 us against 34.4); with
-    // several slices fewer waves share them and nobody waits for the copy (x 8192: 17.8 and 16.0).
-    return t.log_ks == 0 && thin_planes_fit(p) ? go(two, copied) : go(two, direct);
+    return plan.copied ? go(two, copied) : go(two, direct);
 }
 
 hipError_t launch_cop_thin(const Problem &p, int count, const uint64_t *X, int half_shift,

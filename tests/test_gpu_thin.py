@@ -1,6 +1,10 @@
 """The kernel for few rows (m <= 32) at the edges of its tiles, slices and routes: every output word
 against the oracle, through the call that stages and multiplies (up to 16 rows: from the shares
-themselves), the staged call and the batch; and the workspace that the first one leaves behind."""
+themselves), the staged call and the batch; and the workspace that the first one leaves behind.
+(From staged shares the short inner dimensions among SHAPES are faster with the tile kernel, and go
+there; ROUTED holds sizes that do not, and the instance that each is there for.)"""
+import re
+
 import numpy as np
 import pytest
 
@@ -66,3 +70,69 @@ def test_few_rows(oracle, m, k, n, N, L, x_bits, q_bits):
         for out in outs:
             got = gu.host(out)
             assert np.array_equal(got, want), "batch: " + gu.first_mismatch(got, want)
+
+
+# m, k, n, N, L, x_bits, q_bits, problems: 16-row tiles, where the shares come from (0 staged planes per
+# wave, 1 copied to LDS once), slices of k.  One k-block to several stages in one slice, the last
+# column group alone in its workgroup; two, four and eight slices with and without a remainder;
+# every plane count; the last shape's planes do not fit the LDS
+ROUTED = [
+    (1, 1, 5120, 1024, 2, 20, 54, 1, (1, 0, 1)), (16, 31, 5120, 1024, 2, 16, 50, 1, (1, 0, 1)),
+    (15, 64, 10272, 32, 1, 32, 62, 1, (1, 0, 1)), (16, 65, 6144, 1024, 2, 24, 62, 1, (1, 0, 1)),
+    (9, 129, 5120, 1024, 2, 16, 62, 1, (1, 0, 1)), (7, 769, 3072, 1024, 2, 20, 54, 1, (1, 0, 2)),
+    (16, 257, 32, 32, 1, 32, 54, 1, (1, 0, 4)), (2, 321, 32, 32, 2, 20, 54, 1, (1, 0, 4)),
+    (16, 513, 64, 32, 1, 20, 55, 1, (1, 0, 8)), (16, 1025, 32, 32, 1, 32, 62, 1, (1, 0, 8)),
+    (17, 200, 5120, 1024, 2, 20, 54, 1, (2, 1, 1)), (32, 257, 6144, 1024, 2, 32, 62, 1, (2, 1, 1)),
+    (31, 225, 10272, 32, 1, 16, 62, 1, (2, 1, 1)), (32, 289, 5120, 1024, 2, 24, 62, 1, (2, 1, 1)),
+    (20, 1300, 5120, 1024, 2, 32, 54, 1, (2, 0, 1)), (18, 1400, 3072, 1024, 2, 20, 54, 1, (2, 0, 2)),
+    (17, 321, 32, 32, 1, 16, 50, 1, (2, 0, 4)), (32, 385, 64, 32, 1, 20, 54, 1, (2, 0, 4)),
+    (25, 513, 32, 32, 2, 24, 62, 1, (2, 0, 8)), (32, 1025, 32, 32, 1, 32, 62, 1, (2, 0, 8)),
+    # batches: problems with shares, weights and masks of their own
+    (16, 40, 2048, 1024, 2, 20, 54, 3, (1, 0, 1)), (5, 300, 64, 64, 1, 32, 62, 3, (1, 0, 4)),
+    (17, 460, 2048, 1024, 2, 20, 54, 3, (2, 1, 1)), (32, 300, 2048, 1024, 2, 32, 62, 3, (2, 1, 1)),
+    (32, 400, 64, 64, 1, 20, 54, 3, (2, 0, 4)), (24, 600, 64, 64, 2, 24, 62, 4, (2, 0, 8)),
+]
+
+
+@pytest.mark.parametrize("m,k,n,N,L,x_bits,q_bits,problems,instance", ROUTED)
+def test_few_rows_from_staged_shares(oracle, m, k, n, N, L, x_bits, q_bits, problems, instance):
+    import torch
+    import gpu_util as gu
+    import paper_2411_15707_amd as nc
+    moduli = ci.limb_primes(q_bits, 14, L)
+    Ch = -(-n // N)
+    tiles, source, slices = instance
+    route = nc.nimbus_route_matmul(m, k, x_bits, n, N, L, moduli, staged=True, count=problems)
+    line = re.match(r"cop_thin_kernel<\d, \d, (\d), \(nimbus::ThinShares\)(\d), (\d+)> grid=(\d+),(\d+) ", route[0])
+    assert line, route
+    rt, src, room, blocks, count = map(int, line.groups())
+    assert (rt, src, count) == (tiles, source, problems) and room == (1 if problems == 1 else 16)
+    assert blocks == -(-Ch * 2 * L * N // 16 * slices // 8), route
+    print(f"[thin] m={m} k={k} n={n} N={N} x_bits={x_bits} q_bits={q_bits} problems={problems}: {route[0]}", flush=True)
+    staged, prepared, masks, outs, wants = [], [], [], [], []
+    for b in range(problems):
+        seed = 3000 + 10 * (m + k) + b
+        X = ci.gen_X(seed, m, k, x_bits)
+        X[0, 0] = X[-1, -1] = (1 << x_bits) - 1
+        ctW = ci.gen_ctW_uniform(seed, k, Ch, moduli, N)
+        mask = ci.gen_mask_uniform(seed, m, Ch, moduli, N)
+        for l, q in enumerate(moduli):
+            ctW[:, 0, :, l, :4] = q - 1
+            mask[0, 0, :, l, :4] = q - 1
+        wants.append([oracle.cop_ref(X, ctW, moduli, n, N, msk)[0] for msk in (mask, None)])
+        staged.append(torch.full((nc.nimbus_cop_workspace_bytes(m, k, x_bits),), 85, dtype=torch.uint8, device="cuda"))
+        nc.nimbus_cop_stage_shares(gu.dev(X), m, k, x_bits, staged[-1])
+        prepared.append(gu.prepare(ctW, moduli, n, N))
+        masks.append(gu.dev(mask))
+        outs.append(torch.empty((m, Ch, 2, L, N), dtype=torch.int64, device="cuda"))
+    for which, msks in enumerate((masks, None)):
+        for out in outs:
+            out.fill_(-1)
+        if problems == 1:
+            nc.nimbus_cop_matmul_staged(staged[0], m, k, x_bits, prepared[0], n, N, L, moduli,
+                                        msks[0] if msks else None, outs[0])
+        else:
+            nc.nimbus_cop_matmul_staged_batch(staged, m, k, x_bits, prepared, n, N, L, moduli, msks, outs)
+        for b in range(problems):
+            got = gu.host(outs[b])
+            assert np.array_equal(got, wants[b][which]), f"problem {b}: " + gu.first_mismatch(got, wants[b][which])

@@ -85,3 +85,28 @@ def test_every_launch_of_few_rows_has_fewer_than_2_to_32_threads(m, staged):
         for line in nc.nimbus_route_matmul(m, 1, 20, n, 65536, 1, ci.limb_primes(54, 20, 1), staged=staged):
             line = LINE.match(line)
             assert int(line.group(3)) * int(line.group(5)) < 2**32, (n, line.group(0))
+
+
+def kernels(lines):
+    return [LINE.match(x).group(1) for x in lines]
+
+
+# m, k, C, x_bits, problems, and the kernel from staged shares (measured on 256 compute units, us, the
+# kernel for few rows / the tiles: 9.0 / 5.8, 11.4 / 6.3, 8.3 / 7.2, 12.9 / 7.3, 35.5 / 32.8, 48.5 / 36.2,
+# 28.9 / 22.1, 11.7 / 10.9, 12.5 / 6.8, 377 / 304; 10.2 / 11.8, 13.5 / 18.5, 9.1 / 13.3, 17.4 / 19.2,
+# 84.8 / 94.3, 10.1 / 12.5)
+@pytest.mark.parametrize("m,k,C,x_bits,count,kernel", [
+    (16, 32, 4096, 20, 1, "cop_mfma_kernel"), (32, 32, 4096, 20, 1, "cop_mfma_kernel"),
+    (1, 128, 256, 20, 1, "cop_mfma_kernel"), (32, 64, 8192, 20, 1, "cop_mfma_kernel"),
+    (16, 32, 131072, 20, 1, "cop_mfma_kernel"), (32, 32, 131072, 20, 1, "cop_mfma_kernel"),
+    (32, 128, 49152, 20, 1, "cop_mfma_kernel"), (16, 256, 16384, 20, 1, "cop_mfma_kernel"),
+    (24, 32, 4096, 20, 4, "cop_mfma_kernel"), (24, 64, 262144, 20, 4, "cop_mfma_kernel"),
+    (16, 64, 20480, 20, 1, "cop_thin_kernel"), (16, 256, 24576, 20, 1, "cop_thin_kernel"),
+    (32, 512, 4096, 20, 1, "cop_thin_kernel"), (32, 256, 24576, 20, 1, "cop_thin_kernel"),
+    (32, 1024, 65536, 20, 1, "cop_thin_kernel"), (32, 384, 512, 20, 16, "cop_thin_kernel"),
+])
+def test_few_rows_take_the_faster_kernel(m, k, C, x_bits, count, kernel):
+    n = C // 4                                      # (two limbs)
+    N = min(4096, n & -n)                           # the power of two in it
+    lines = nc.nimbus_route_matmul(m, k, x_bits, n, N, 2, moduli_of(54, 2), staged=True, count=count, units=256)
+    assert kernels(lines) == [kernel]
