@@ -581,12 +581,17 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     // dx is multiplied, and during the last plane every ciphertext plane is refilled from stage
     // s + 1 right behind its last use.  The barrier that makes stage s + 1 visible and frees the
     // slot of stage s stands behind the first NPRE1 products of the last plane; the loads of stage
-    // s + LEAD go out during the first two planes, into the slot that the barrier before has freed.
+    // s + LEAD go out in front of it, into the slot that the barrier before has freed: behind every
+    // fourth product from the third on, so the last of four in the second plane (eight ciphertext
+    // planes) or with the first product of the third (seven).
     // LDS reads come back in order, so every wait is a count of younger reads.
     // (Reading a whole stage behind its barrier, as before, left the matrix cores idle for the
     // reads' latency in every k-block: 128 x 768 x 32768 with 64-bit shares and moduli of 59 bits
     // 194 us, now 184; four problems of 77 x 1001 x 16384 with 32-bit shares 185 us, now 172.)
     constexpr int NPRE1 = 2;
+    constexpr int kIssue0 = 2, kIssueStep = 4;      // load u goes out behind product kIssue0 + u kIssueStep
+    static_assert(PIPELINED || kIssue0 + (P_::MAXU - 1) * kIssueStep < (DX - 1) * DQ,
+                  "every load of a stage goes out in front of its last plane's barrier");
     auto one_set_iteration = [&](int s, auto steady_c) {
         constexpr bool STEADY = decltype(steady_c)::value;      // stage s + LEAD exists
         const uint32_t nextA = bump(rdA, P_::A_BYTES, RING * P_::A_BYTES);
@@ -608,9 +613,9 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             acc[dx + dq] =
                 __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[0][dx], xb[0][dq], acc[dx + dq], 0, 0, 0);
             tie_acc(acc[dx + dq]);
-            // loads of stage s + LEAD, one at a time over the first two planes
-            if constexpr (STEADY && DX > 2 && i % 4 == 2 && i / 4 < P_::MAXU) {
-                constexpr int u = i / 4;
+            // loads of stage s + LEAD, one at a time
+            if constexpr (STEADY && i % kIssueStep == kIssue0 && i / kIssueStep < P_::MAXU) {
+                constexpr int u = i / kIssueStep;
                 if (u < NMIN || u < n_loads) issue_one(std::integral_constant<int, u>{});
             }
             if constexpr (LAST && dq == NPRE1 - 1) {
