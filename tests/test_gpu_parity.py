@@ -1,6 +1,8 @@
 """GPU parity: both C-ABI entry points against the CPU oracle, bit for bit.
 
-Integer work, so the bar is exact equality of every output word.
+Integer work, so the bar is exact equality of every output word.  (On the prepared path which kernel and
+which of its instances a size reaches depends on rows, columns and inner dimension together; the
+instances have tests of their own, by name, in test_gpu_variants.py and test_gpu_thin.py.)
 """
 import sys
 
@@ -56,35 +58,34 @@ SMALL = [
     (1, 1, 32, 32, 1, 16, 50),          # k = 1, m = 1
     (16, 160, 64, 64, 1, 12, 50),       # 12-bit shares: the upper share plane holds unshifted digits
     (7, 33, 64, 64, 1, 7, 30),          # 7-bit shares (no shifted plane at all), 30-bit modulus
-    (9, 128, 64, 64, 2, 20, 62),        # 3 x 8 planes (operands read after the barrier), four k-blocks
+    (9, 128, 64, 64, 2, 20, 62),        # 3 x 8 planes, four k-blocks
     (12, 192, 64, 64, 1, 32, 62),       # 4 x 8 planes, six k-blocks
     (100, 1024, 64, 64, 1, 16, 50),     # 2 x 7 planes, 32 k-blocks
     (6, 50, 32, 32, 3, 20, 54),         # smallest ring with several limbs: a 64-column tile spans two limbs
-    # m a multiple of 128: the builds of the kernel without row tests, one per plane count
+    # m a multiple of 128 on few columns: whole blocks of 64 rows, every plane count
     (128, 64, 64, 64, 1, 16, 50),       # 2 x 7
     (128, 96, 64, 64, 2, 20, 54),       # 3 x 7, two limbs
     (128, 70, 64, 64, 1, 32, 54),       # 4 x 7
     (128, 64, 64, 64, 1, 16, 62),       # 2 x 8
     (128, 65, 64, 64, 2, 24, 62),       # 3 x 8
     (128, 64, 32, 32, 1, 32, 62),       # 4 x 8, smallest ring
-    (256, 100, 64, 64, 2, 20, 54),      # two full row blocks
-    # the mask tile through LDS (m a multiple of 128, at least 13 k-blocks) for the plane counts
-    # the BERT-shaped configs do not reach, alone and with several row blocks per column tile
+    (256, 100, 64, 64, 2, 20, 54),
+    # the same with 13 k-blocks and more
     (128, 512, 64, 64, 1, 16, 50),      # 2 x 7
     (128, 448, 64, 64, 1, 16, 62),      # 2 x 8
-    (256, 480, 64, 64, 1, 16, 50),      # 2 x 7, two row blocks
-    (256, 417, 64, 64, 1, 16, 62),      # 2 x 8, two row blocks, ragged k
-    (384, 512, 128, 128, 2, 20, 54),    # 3 x 7, three row blocks
+    (256, 480, 64, 64, 1, 16, 50),      # 2 x 7
+    (256, 417, 64, 64, 1, 16, 62),      # 2 x 8, ragged k
+    (384, 512, 128, 128, 2, 20, 54),    # 3 x 7
     # row blocks dealt to the XCDs: 8 and 12 column-tile pairs (a whole round, a round and a tail)
     (256, 100, 256, 256, 1, 20, 54),
     (384, 70, 128, 128, 3, 20, 54),
-    (200, 500, 256, 256, 1, 16, 50),    # ragged m with two row blocks, 16 k-blocks
+    (200, 500, 256, 256, 1, 16, 50),    # ragged m, the last row block of 64 with 8 rows, 16 k-blocks
     # more output tiles than compute units: a workgroup walks several tiles, the first stages of
     # the next one in flight under the epilogue of the one before
     (128, 512, 8192, 8192, 3, 20, 54),  # 768 tiles, mask tile through LDS
     (70, 100, 8192, 8192, 3, 20, 54),   # 768 tiles, a wave without rows in every tile
     (200, 70, 4096, 4096, 2, 20, 54),   # 512 tiles in two row blocks, the second ragged
-    (128, 96, 16384, 16384, 1, 32, 62), # 512 tiles, 4 x 8 planes (operands read after the barrier)
+    (128, 96, 16384, 16384, 1, 32, 62), # 512 tiles, 4 x 8 planes (one operand set)
     # the ends of the accepted ranges
     (6, 50, 64, 64, 4, 20, 54),         # four limbs
     (3, 33, 32768, 32768, 2, 20, 54),   # the paper's largest ring degree
@@ -107,13 +108,15 @@ def test_small_and_ragged_shapes(oracle, m, k, n, N, L, t_bits, q_bits):
     _check_both(oracle, X, ctW, moduli, n, N, t_bits, None, f"small/no-mask m={m} k={k}")
 
 
+# the kernel for few rows and the tile kernel
+@pytest.mark.parametrize("m", [8, 40])
 @pytest.mark.parametrize("k", [20, 40, 80])
 @pytest.mark.parametrize("t_bits,q_bits", [(16, 50), (20, 54), (32, 54), (16, 62), (24, 62), (32, 62)])
-def test_one_to_three_k_blocks_per_plane_count(oracle, t_bits, q_bits, k):
+def test_one_to_three_k_blocks_per_plane_count(oracle, t_bits, q_bits, k, m):
     """every plane count with one, two and three k-blocks: the loop's prologue is all there is,
     its first wait covers the load of the column sums, and with shares of t-1 the term
     OFFX * S that needs them is as large as it gets"""
-    m, n, N, L = 8, 32, 32, 1
+    n, N, L = 32, 32, 1
     moduli = ci.limb_primes(q_bits, t_bits, L)
     X, ctW, mask = _inputs(2000 + k + t_bits + q_bits, m, k, n, N, moduli, t_bits)
     X[0, :] = (1 << t_bits) - 1
@@ -121,14 +124,18 @@ def test_one_to_three_k_blocks_per_plane_count(oracle, t_bits, q_bits, k):
     _check_both(oracle, X, ctW, moduli, n, N, t_bits, mask, f"k={k} t={t_bits} q={q_bits}")
 
 
-def test_all_maximal_operands(oracle):
+# the kernel for few rows; the tile kernel with row tests, in blocks of 64 rows, and (8448 columns) in full
+# blocks of 128, the mask tile in LDS where there is one
+@pytest.mark.parametrize("m,n", [(32, 64), (40, 64), (128, 64), (128, 2112)])
+def test_all_maximal_operands(oracle, m, n):
     """every share t-1 and every residue q-1: the largest sums the accumulators can see"""
-    m, k, n, N, L, t_bits = 32, 512, 64, 64, 2, 24
+    k, N, L, t_bits = 512, 64, 2, 24
+    Ch = -(-n // N)
     moduli = ci.limb_primes(55, t_bits, L)
     qv = np.array(moduli, dtype=np.uint64).reshape(1, 1, 1, L, 1)
     X = np.full((m, k), (1 << t_bits) - 1, dtype=np.uint64)
-    ctW = np.broadcast_to(qv - np.uint64(1), (k, 1, 2, L, N)).copy()
-    mask = np.broadcast_to(qv - np.uint64(1), (m, 1, 2, L, N)).copy()
+    ctW = np.broadcast_to(qv - np.uint64(1), (k, Ch, 2, L, N)).copy()
+    mask = np.broadcast_to(qv - np.uint64(1), (m, Ch, 2, L, N)).copy()
     _check_both(oracle, X, ctW, moduli, n, N, t_bits, mask, "maximal")
     # residues just above and below q/2 exercise both branches of the centring
     half = (qv - np.uint64(1)) // np.uint64(2)
@@ -139,16 +146,18 @@ def test_all_maximal_operands(oracle):
     _check_both(oracle, X, ctW, moduli, n, N, t_bits, mask, "zero shares")
 
 
-@pytest.mark.parametrize("q_bits,t_bits", [(54, 24), (62, 16), (50, 20)])
-def test_all_maximal_operands_uncentred_digits(oracle, q_bits, t_bits):
+@pytest.mark.parametrize("m,n", [(32, 64), (40, 64), (128, 64), (128, 2112)])
+@pytest.mark.parametrize("q_bits,t_bits", [(54, 24), (62, 16), (50, 20), (62, 32)])
+def test_all_maximal_operands_uncentred_digits(oracle, q_bits, t_bits, m, n):
     """the same extremes for moduli whose residues the canonical-layout kernel splits into
     digits without centring them first: sums twice as large as with centred digits"""
-    m, k, n, N, L = 32, 512, 64, 64, 2
+    k, N, L = 512, 64, 2
+    Ch = -(-n // N)
     moduli = ci.limb_primes(q_bits, t_bits, L)
     qv = np.array(moduli, dtype=np.uint64).reshape(1, 1, 1, L, 1)
     X = np.full((m, k), (1 << t_bits) - 1, dtype=np.uint64)
-    ctW = np.broadcast_to(qv - np.uint64(1), (k, 1, 2, L, N)).copy()
-    mask = np.broadcast_to(qv - np.uint64(1), (m, 1, 2, L, N)).copy()
+    ctW = np.broadcast_to(qv - np.uint64(1), (k, Ch, 2, L, N)).copy()
+    mask = np.broadcast_to(qv - np.uint64(1), (m, Ch, 2, L, N)).copy()
     _check_both(oracle, X, ctW, moduli, n, N, t_bits, mask, f"maximal {q_bits}")
     X[::2] = 0
     ctW[1::2] = 0
@@ -457,7 +466,7 @@ WIDE = [
     (17, 70, 64, 64, 2, 48, (62, 55)),       # 48-bit shares: upper half has two planes
     (9, 33, 32, 32, 1, 33, (50,)),           # one bit above 32
     (32, 128, 8192, 8192, 2, 64, (59, 55)),  # the paper's ring degree and moduli, one chunk
-    (128, 64, 64, 64, 2, 64, (59, 55)),      # full row block: both passes in the build without row tests
+    (128, 64, 64, 64, 2, 64, (59, 55)),      # whole blocks of 64 rows
     (128, 40, 32, 32, 1, 40, (54,)),         # the same with a one-plane upper half
 ]
 
@@ -487,11 +496,11 @@ def test_wide_shares_two_pass_path(oracle, m, k, n, N, L, x_bits, q_bits):
 
 # m, k, n, N, L, t_bits, q_bits, problems, with masks
 BATCHES = [
-    (128, 416, 64, 64, 2, 20, 54, 5, True),       # mask tile through LDS, 13 k-blocks
+    (128, 416, 64, 64, 2, 20, 54, 5, True),       # whole blocks of 64 rows, 13 k-blocks
     (33, 100, 40, 64, 2, 20, 54, 3, True),        # ragged rows and k
-    (256, 100, 256, 256, 1, 20, 54, 3, True),     # two row blocks per column tile
+    (256, 100, 256, 256, 1, 20, 54, 3, True),     # four blocks of 64 rows per column tile
     (128, 96, 8192, 8192, 3, 20, 54, 2, False),   # 768 tiles each: more tiles than compute units
-    (64, 70, 64, 64, 1, 32, 62, 4, True),         # 4 x 8 planes (operands read after the barrier)
+    (64, 70, 64, 64, 1, 32, 62, 4, True),         # 4 x 8 planes (one operand set)
     (8, 64, 64, 1024, 1, 16, 50, 16, True),       # the largest batch, config 1's shape
     (40, 96, 128, 128, 3, 24, 55, 1, True),       # a batch of one
 ]
@@ -547,14 +556,16 @@ def test_calibration_launches_run():
         nc.nimbus_calib_butterflies(8, 5, 1 << 54, bsink)  # even modulus: refused on the host
 
 
+# few rows; the tile kernel with row tests, and in blocks of 64 rows
+@pytest.mark.parametrize("m", [3, 33, 128])
 @pytest.mark.parametrize("t_bits,q_bits", [(32, 62), (20, 54), (16, 50)])
-def test_longest_inner_dimension_with_extreme_digits(oracle, t_bits, q_bits):
+def test_longest_inner_dimension_with_extreme_digits(oracle, t_bits, q_bits, m):
     """k = 16383, the largest the matrix-core path accepts: 512 k-blocks, int32 accumulators
     closest to their bound.  Shares 0 and t-1 give share digits -128 and 127 in every shifted
     plane; residues around q/2 give ciphertext digits of the largest magnitude the centred
     recoding can produce."""
     import gpu_util as gu
-    m, k, n, N, L = 3, 16383, 32, 32, 1
+    k, n, N, L = 16383, 32, 32, 1
     moduli = ci.limb_primes(q_bits, t_bits, L)
     q = moduli[0]
     X = ci.gen_X(31, m, k, t_bits)
