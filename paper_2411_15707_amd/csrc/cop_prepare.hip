@@ -7,12 +7,12 @@ namespace nimbus {
 
 // One workgroup = one 32-column tile over all of k: wave w re-lays the k-blocks w, w + WAVES, ...
 // and adds up the words on the way, so that ctW is read once (the sums used to be a kernel of their
-// own with one thread per column: 64 workgroups, another pass over ctW, 224-276 us for the
-// 768 x 16384 residues of a BERT-base up-projection next to the 43 us of the planes).
+// own with one thread per column: 64 workgroups and another pass over ctW, five sixths of the time
+// for the 768 x 16384 residues of a BERT-base up-projection).
 // Lane l holds column l % 32 and the 16 k-slots (l / 32) * 16 .. +15 of a block: a load brings 256
 // contiguous bytes of two rows, a store a whole 1 KB operand tile.  Bound by HBM: 8 bytes in and
 // DQ bytes out per residue, 5.1-5.4 TB/s of both together where there are 256 column tiles or more
-// (a copy of 1 GiB reaches 5.2): 35.8 us for those 768 x 16384 residues, 310-325 before.
+// (a copy of 1 GiB reaches 5.2): 35.5 us for those 768 x 16384 residues, 312.6 in two kernels.
 template <int DQ, int WAVES>
 __global__ __launch_bounds__(WAVES * 64) void prepare_kernel(
     const uint64_t *__restrict__ ctW, int k, uint32_t C, int log_n, int L, LimbTable limbs, int KB,

@@ -1,4 +1,4 @@
-// Matrix-core (int8 MFMA) kernel of the COP accumulation for few token rows (m <= 32), gfx950:
+// Matrix-core (int8 MFMA) kernel of the COP accumulation for few token rows (up to 32), gfx950:
 // the same contraction, operand bytes and epilogue as cop_mfma.hip (Algorithm 1 step 2 + step 4
 // of the paper), laid out for a call that is nothing but a pass over the weights.
 //
