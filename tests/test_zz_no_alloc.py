@@ -21,6 +21,8 @@ CALLS = [
     (130, 300, 128, 128, 2, 20, 54),    # two row blocks (one ragged), ten k-blocks with a tail
     (33, 100, 64, 64, 2, 20, 54),       # smaller in both dimensions: stale planes lie behind it
     (20, 70, 64, 64, 1, 40, 54),        # shares of 40 bits: both halves' planes in the buffer
+    (16, 200, 64, 64, 2, 20, 54),       # few rows: no staging launch, the planes are left behind
+    (3, 40, 64, 64, 1, 64, 54),         # the same with two halves
 ]
 
 
