@@ -1,6 +1,6 @@
 // Matrix-core (int8 MFMA) kernel for the COP accumulation on the CANONICAL layout, gfx950:
 // nimbus_cop_matmul without any setup pass.  Same contraction and same epilogue as the kernel
-// for prepared weights (cop_mfma.hip; Algorithm 1 step 2 + step 4 of the paper), but both
+// for prepared weights (cop_mfma_kernel.hpp; Algorithm 1 step 2 + step 4 of the paper), but both
 // operands arrive as 64-bit words and are split into signed byte planes inside the loop:
 //
 //   ciphertext words  ctW[k][C]: a 32 x 64 tile per k-block (16 KB) comes into a ring of raw
@@ -14,8 +14,8 @@
 //       ahead; every thread turns 2 x 4 consecutive k of one row into one word per plane.
 //
 // The operand tiles in LDS have the register order of the instruction, exactly as the setup
-// pass of the other kernel would have left them in memory, so the products are the same
-// v_mfma_i32_32x32x32_i8 sequence: 8 waves, wave (wr, wc) owns 32 rows x 32 columns, DX * DQ
+// pass of the other kernel would have left them in memory; the products run on
+// v_mfma_i32_32x32x32_i8: 8 waves, wave (wr, wc) owns 32 rows x 32 columns, DX * DQ
 // instructions per k-block into DX + DQ - 1 diagonal accumulators.  The column sums S that the
 // share offset OFFX needs (x = x' + OFFX) are gathered on the way: every thread adds up the
 // words it converts, the partial sums meet in LDS after the loop.
@@ -366,8 +366,8 @@ __global__ __launch_bounds__(512, 1) void cop_canon_kernel(const CanonArgs ca)
         add128(hi, lo, highs >> 32, highs << 32);
         colsum_S = barrett128(hi, lo, ca.limbs.limb[limb]);      // k * q < 2^(b+63)
     }
-    cop_epilogue<ND, FULL, false>(acc, a, a.mask, nullptr, a.out, limb, colsum_S, rt * kTile + 4 * (lane >> 5),
-                                  (ct2 * 2u + (uint32_t)wc) * kTile + (uint32_t)(lane & 31), nullptr);
+    cop_epilogue<ND, FULL>(acc, a, a.mask, nullptr, a.out, limb, colsum_S, rt * kTile + 4 * (lane >> 5),
+                                  (ct2 * 2u + (uint32_t)wc) * kTile + (uint32_t)(lane & 31));
 }
 
 // ---------------------------------------------------------------------------

@@ -1,4 +1,4 @@
-// Shared by the matrix-core kernels of the COP accumulation (prepared weights: cop_mfma.hip;
+// Shared by the matrix-core kernels of the COP accumulation (prepared weights: cop_mfma_kernel.hpp, few rows: cop_thin.hip;
 // canonical layout: cop_canon.hip): argument block, small helpers around the instructions the
 // loops are built from, and the epilogue that turns the int32 digit sums into residues.
 #pragma once
@@ -35,7 +35,7 @@ struct MfmaArgs {
     uint32_t log_n;           // N = 2^log_n
     uint32_t l_magic;         // ceil(2^32 / L) for L >= 2: x / L = umulhi(x, l_magic) for x < 2^31
     uint32_t offx;            // OFFX
-    uint32_t block_tiles;     // 32-row tiles of a row block: 4, or 2 (see mfma_impl)
+    uint32_t block_tiles;     // 32-row tiles of a row block, four at most (see mfma_impl())
     uint64_t q[kMaxLimbs];
     double qinv[kMaxLimbs];   // 1 / q_l, rounded
     // q_l << sh
@@ -226,41 +226,41 @@ __device__ __forceinline__ void wait_vmem_n(int n)
         : "s96", "s97", "s98", "scc", "memory");
 }
 
-// Wait until at most W * n of this wave's loads are pending, for n in [NLO, NHI] with
-// NHI - NLO <= 2, n wave-uniform: a short chain of compares in the order the code runs
-// through, instead of the table jump above.
-template <int W, int NHI, int NLO>
-__device__ __forceinline__ void wait_vmem_loads(int n)
+// Wait until at most `pending` of this wave's loads are pending, for a wave-uniform `pending` that is
+// N0, N1 or N2, N2 being the least of them: a chain of compares (anything else waits for N2).
+template <int N0, int N1, int N2>
+__device__ __forceinline__ void wait_vmem_of(int pending)
 {
-    static_assert(NHI - NLO <= 2 && NHI >= NLO, "at most three cases");
-    if constexpr (NHI == NLO) {
-        wait_vmem<W * NHI>();
-    } else if constexpr (NHI - NLO == 1) {
+    static_assert(N2 <= N1 && N2 <= N0, "the last one is the strictest");
+    if constexpr (N0 == N2 && N1 == N2) {
+        wait_vmem<N2>();
+    } else if constexpr (N0 == N1 || N1 == N2 || N0 == N2) {
+        constexpr int N = N0 > N1 ? N0 : N1;
         asm volatile("s_cmp_eq_u32 %0, %1\n\t"
-                     "s_cbranch_scc1 .Lwl_hi_%=\n\t"
-                     "s_waitcnt vmcnt(%2)\n\t"
-                     "s_branch .Lwl_end_%=\n"
-                     ".Lwl_hi_%=:\n\t"
-                     "s_waitcnt vmcnt(%3)\n"
-                     ".Lwl_end_%=:"
+                     "s_cbranch_scc1 .Lwo_hi_%=\n\t"
+                     "s_waitcnt vmcnt(%3)\n\t"
+                     "s_branch .Lwo_end_%=\n"
+                     ".Lwo_hi_%=:\n\t"
+                     "s_waitcnt vmcnt(%2)\n"
+                     ".Lwo_end_%=:"
                      :
-                     : "s"(n), "n"(NHI), "n"(W * NLO), "n"(W * NHI)
+                     : "s"(pending), "n"(N), "n"(N), "n"(N2)
                      : "scc", "memory");
     } else {
         asm volatile("s_cmp_eq_u32 %0, %1\n\t"
-                     "s_cbranch_scc1 .Lwl_hi_%=\n\t"
+                     "s_cbranch_scc1 .Lwo_hi_%=\n\t"
                      "s_cmp_eq_u32 %0, %2\n\t"
-                     "s_cbranch_scc1 .Lwl_mid_%=\n\t"
+                     "s_cbranch_scc1 .Lwo_mid_%=\n\t"
                      "s_waitcnt vmcnt(%3)\n\t"
-                     "s_branch .Lwl_end_%=\n"
-                     ".Lwl_mid_%=:\n\t"
-                     "s_waitcnt vmcnt(%4)\n\t"
-                     "s_branch .Lwl_end_%=\n"
-                     ".Lwl_hi_%=:\n\t"
-                     "s_waitcnt vmcnt(%5)\n"
-                     ".Lwl_end_%=:"
+                     "s_branch .Lwo_end_%=\n"
+                     ".Lwo_mid_%=:\n\t"
+                     "s_waitcnt vmcnt(%2)\n\t"
+                     "s_branch .Lwo_end_%=\n"
+                     ".Lwo_hi_%=:\n\t"
+                     "s_waitcnt vmcnt(%1)\n"
+                     ".Lwo_end_%=:"
                      :
-                     : "s"(n), "n"(NHI), "n"(NHI - 1), "n"(W * NLO), "n"(W * (NHI - 1)), "n"(W * NHI)
+                     : "s"(pending), "n"(N0), "n"(N1), "n"(N2)
                      : "scc", "memory");
     }
 }
@@ -274,11 +274,12 @@ __device__ __forceinline__ void wait_vmem_loads(int n)
 //              output, [m][C] each
 //   limb       limb of the wave's columns;  colsum_S  sum of the column's residues mod q
 //   row0, col  the lane's first row and its column in the whole output
+//   row_end    the rows from here on are not the caller's (FULL: there are none)
 // ---------------------------------------------------------------------------
 template <int ND, int NE, bool FULL, typename Digit, typename RowOf, typename Masks>
 __device__ __forceinline__ void cop_finish(Digit D, RowOf roff, Masks masks, const MfmaArgs &a,
                                            const uint64_t *prev, uint64_t *out, uint32_t limb,
-                                           uint64_t colsum_S, int row0, uint32_t col)
+                                           uint64_t colsum_S, int row0, uint32_t col, int row_end)
 {
     const uint64_t q = a.q[limb];
     const double qinv = a.qinv[limb];
@@ -361,7 +362,7 @@ __device__ __forceinline__ void cop_finish(Digit D, RowOf roff, Masks masks, con
         uint64_t pv[NE];
 #pragma unroll
         for (int r = 0; r < NE; ++r)
-            pv[r] = (FULL || row0 + roff(r) < a.m) ? __builtin_nontemporal_load(&prev0[(size_t)roff(r) * a.C]) : 0;
+            pv[r] = (FULL || row0 + roff(r) < row_end) ? __builtin_nontemporal_load(&prev0[(size_t)roff(r) * a.C]) : 0;
 #pragma unroll
         for (int r = 0; r < NE; ++r) {
             g1_lo[r] += (uint32_t)pv[r];
@@ -424,30 +425,25 @@ __device__ __forceinline__ void cop_finish(Digit D, RowOf roff, Masks masks, con
         const uint64_t res = ((uint64_t)r_hi << 32) | r_lo;
         // (streaming store: the output is not read again by this kernel, and lines that do
         // not sit dirty in L2 need no write-back when the kernel ends)
-        if (FULL || row0 + roff(r) < a.m) __builtin_nontemporal_store(res, &out0[(size_t)roff(r) * a.C]);
+        if (FULL || row0 + roff(r) < row_end) __builtin_nontemporal_store(res, &out0[(size_t)roff(r) * a.C]);
     }
 }
 
-// the same for a wave's 32 x 32 tile:
+// the same for a wave's 32 x 32 tile (the kernel on the canonical layout):
 //   acc        ND accumulator tiles (element r of the lane is row row0 + 8 (r / 4) + r % 4)
 //   mask       the problem's mask (or null)
-//   mask_tile  MASKLDS: the lane's word of row0 in the workgroup's mask tile in LDS
-template <int ND, bool FULL, bool MASKLDS>
+template <int ND, bool FULL>
 __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
                                              const uint64_t *mask, const uint64_t *prev,
                                              uint64_t *out, uint32_t limb, uint64_t colsum_S,
-                                             int row0, uint32_t col, const unsigned char *mask_tile)
+                                             int row0, uint32_t col)
 {
     auto roff = [](int r) -> int { return 8 * (r >> 2) + (r & 3); };
     const uint64_t *const mask0 = mask ? mask + ((size_t)row0 * a.C + col) : nullptr;
     cop_finish<ND, 16, FULL>(
         [&](int d, int r) -> int32_t { return acc[d][r]; }, roff,
         [&](uint64_t (&mk)[16]) {
-            // (read once: from the tile in LDS, row-major [128][64] words, or by streaming loads)
-            if constexpr (MASKLDS) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mk[r] = *(const uint64_t *)(mask_tile + roff(r) * 512);
-            } else if (mask) {
+            if (mask) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r)
                     mk[r] = (FULL || row0 + roff(r) < a.m)
@@ -458,7 +454,7 @@ __device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
                 for (int r = 0; r < 16; ++r) mk[r] = 0;
             }
         },
-        a, prev, out, limb, colsum_S, row0, col);
+        a, prev, out, limb, colsum_S, row0, col, a.m);
 }
 
 }  // namespace nimbus

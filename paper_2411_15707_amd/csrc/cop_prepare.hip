@@ -1,6 +1,6 @@
 // Setup phase of the prepared weights, gfx950: canonical ctW -> signed byte planes of the
 // centred residues in matrix-core operand order, and the column sums (nimbus_cop_prepare; the
-// layout is described at nimbus_cop_prepare in include/nimbus_cop.h and used by cop_mfma.hip).
+// layout is described at nimbus_cop_prepare in include/nimbus_cop.h and used by cop_mfma_kernel.hpp).
 #include "cop_mfma_common.hpp"
 
 namespace nimbus {

@@ -1,5 +1,5 @@
 // Matrix-core (int8 MFMA) kernel of the COP accumulation for few token rows (up to 32), gfx950:
-// the same contraction, operand bytes and epilogue as cop_mfma.hip (Algorithm 1 step 2 + step 4
+// the same contraction, operand bytes and epilogue as cop_mfma_kernel.hpp (Algorithm 1 step 2 + step 4
 // of the paper), laid out for a call that is nothing but a pass over the weights.
 //
 // What bounds it: the bytes of the prepared weights (m = 1, 768 x 16384 residues of 54 bits:
@@ -24,11 +24,11 @@
 // and the staging launch and the gap behind it go away.  The planes are left in the workspace
 // all the same (workgroup b writes the stages b, b + grid, ...), as that entry point promises.
 //
-// Measured against the 128 x 64 tiles of cop_mfma.hip behind a staging launch (us a call, 20-bit
+// Measured against the 128 x 64 tiles of cop_mfma_kernel.hpp behind a staging launch (us a call, 20-bit
 // shares, 54-bit moduli): 1 x 768 x 16384 21.7 -> 17.5, 16 x 768 x 16384 22.1 -> 19.4, 4 x 768 x
 // 49152 57.4 -> 49.4, 32 x 768 x 4096 20.2 -> 12.5, 1 x 3072 x 8192 56.0 -> 29.8; no better with 17
 // to 32 rows and 16384 columns (22.8 and 22.6).  With a third and a fourth 16-row tile the shares'
-// planes cost more than the tiles of cop_mfma.hip (64 x 768 x 16384: 33 us and 28).
+// planes cost more than the tiles of cop_mfma_kernel.hpp (64 x 768 x 16384: 33 us and 28).
 #include "cop_mfma_common.hpp"
 
 namespace nimbus {
@@ -332,7 +332,7 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
                     digit[d] += sums[((((o << log_cgw) + cgl) * ND + d) * (4 * TILES) + e) * 64u + lane];
             cop_finish<ND, 1, false>([&](int d, int) { return digit[d]; }, [](int) { return 0; },
                                      [&](uint64_t (&w)[1]) { w[0] = word; }, a, a.prev, pp.out, limb, colsum_S,
-                                     (int)(16u * (i0 + e / 4u) + 4u * j + e % 4u), col);
+                                     (int)(16u * (i0 + e / 4u) + 4u * j + e % 4u), col, a.m);
         }
     });
 }
