@@ -76,6 +76,11 @@ hipError_t launch_cop_mfma(const Problem &p, const void *staged, const void *pre
                            const uint64_t *mask, const uint64_t *prev, uint64_t *out,
                            hipStream_t stream);
 bool mfma_supported(const Problem &p);
+// the tile kernel's row blocks: how many, of how many 32-row tiles each
+struct TileBlocks {
+    int row_blocks, tiles;
+};
+TileBlocks tile_blocks(const Problem &p, int count);
 // few rows (cop_thin.hip): from staged shares, or (X, half_shift) from the shares themselves
 bool thin_applies(const Problem &p, int count);
 bool thin_raw_applies(const Problem &p);

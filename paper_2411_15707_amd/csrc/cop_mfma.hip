@@ -73,6 +73,23 @@ int compute_units()
     return n;
 }
 
+TileBlocks tile_blocks(const Problem &p, int count)
+{
+    // Row blocks of 64 rows where all of those find a compute unit of their own: half as many products
+    // per workgroup (100 x 768 x 4096 25.0 us a call with blocks of 128 rows, 17.3 with 64; as many
+    // blocks as compute units, 128 x 768 x 8192, 24.5 and 22.3).  With a second round of workgroups
+    // the larger blocks are ahead (100 x 768 x 12288).
+    uint32_t cus = (uint32_t)compute_units();
+    if (cus >= 8) cus &= ~7u;
+    if (p.m > 64 && (uint64_t)(p.C / 64u) * (uint64_t)((p.m + 63) / 64) * (uint32_t)count <= cus)
+        return {(p.m + 63) / 64, 2};
+    // Else of 128 rows at most, and of even size: 130 rows are 96 and 34, not 128 and 2 (a workgroup walks
+    // tiles that lie a multiple of eight apart, so that with two or four row blocks it has the same one
+    // in all of them; 130 x 200 x 16384 27.4 us with 128 and 2, 24.7 with 96 and 34).
+    const int row_blocks = (p.m + 127) / 128, row_tiles = (p.m + kTile - 1) / kTile;
+    return {row_blocks, (row_tiles + row_blocks - 1) / row_blocks};
+}
+
 bool mfma_supported(const Problem &p)
 {
     const int DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);

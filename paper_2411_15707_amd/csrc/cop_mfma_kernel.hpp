@@ -612,18 +612,10 @@ hipError_t mfma_impl(const Problem &p, int count, const void *const *staged,
     // XCD the same on every pass.
     uint32_t cus = (uint32_t)compute_units();
     if (cus >= 8) cus &= ~7u;
-    // Row blocks of even size: 130 rows are 96 and 34, not 128 and 2 (a workgroup walks tiles that lie a
-    // multiple of eight apart, so that with two or four blocks it has the same block in all of them).
-    if (p.m % 128 != 0) a.block_tiles = (uint32_t)(((p.m + kTile - 1) / kTile + a.RB - 1) / a.RB);
-    // Row blocks of 64 rows where all of those find a compute unit of their own: half as many
-    // products per workgroup, one wave per SIMD (128 x 2000 x 2048: 46.8 us a call with blocks of 128
-    // rows, 29.5 with 64; 128 x 768 x 8192, as many blocks as compute units: 24.5 and 22.3).  With
-    // a second round of workgroups the larger blocks are ahead (100 x 768 x 12288).
-    if (p.m > 64 && (uint64_t)(CT / 2u) * (uint64_t)((p.m + 63) / 64) * (uint32_t)count <= cus) {
-        a.block_tiles = 2;
-        a.RB = (p.m + 63) / 64;
-        a.tiles = (CT / 2u) * (uint32_t)a.RB;
-    }
+    const TileBlocks tb = tile_blocks(p, count);
+    a.block_tiles = (uint32_t)tb.tiles;
+    a.RB = tb.row_blocks;
+    a.tiles = (CT / 2u) * (uint32_t)a.RB;
     const uint32_t tiles_each = a.tiles;
     a.tiles *= (uint32_t)count;
     const dim3 grid(a.tiles < cus ? a.tiles : cus);

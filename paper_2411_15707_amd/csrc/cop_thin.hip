@@ -1,4 +1,5 @@
-// Matrix-core (int8 MFMA) kernel of the COP accumulation for few token rows (up to 32), gfx950:
+// Matrix-core (int8 MFMA) kernel of the COP accumulation for few token rows (up to 32), or more of them
+// on few columns (32 at a time), gfx950:
 // the same contraction, operand bytes and epilogue as cop_mfma_kernel.hpp (Algorithm 1 step 2 + step 4
 // of the paper), laid out for a call that is nothing but a pass over the weights.
 //
@@ -50,15 +51,17 @@ constexpr int kThinSharesLds = 144 * 1024;
 enum ThinShares {
     kDirect,    // staged planes, read like the weights, per wave
     kCopied,    // staged planes, brought into LDS once per workgroup
-    kRaw        // the shares themselves, split into planes in LDS once per workgroup
+    kRaw,       // the shares themselves, split into planes in LDS once per workgroup
+    kRows       // as kDirect, for a call of more than 32 rows: a workgroup takes one 32-row tile of them
 };
 
 // stages in flight per wave: what 256 registers hold next to the accumulators, four at most
 constexpr int thin_depth(int DX, int DQ, int RT16, ThinShares from)
 {
+    const bool direct = from == kDirect || from == kRows;
     const int accumulators = (DX + DQ - 1) * 4 * RT16;
-    const int stage = DQ * 4 + (from == kDirect ? DX * 4 * RT16 : 0);
-    const int fit = (256 - 40 - accumulators - (from == kDirect ? 0 : 20)) / stage;
+    const int stage = DQ * 4 + (direct ? DX * 4 * RT16 : 0);
+    const int fit = (256 - 40 - accumulators - (direct ? 0 : 20)) / stage;
     return fit > 4 ? 4 : fit < 2 ? 2 : fit;
 }
 
@@ -67,7 +70,7 @@ struct Thin {
     static constexpr int ND = DX + DQ - 1;
     static constexpr int PD = thin_depth(DX, DQ, RT16, FROM);
     // planes of the shares, [stage][16-row tile][plane][64 lanes][16 B]
-    static constexpr int A_LDS = FROM == kDirect ? 0 : kThinSharesLds;
+    static constexpr int A_LDS = FROM == kDirect || FROM == kRows ? 0 : kThinSharesLds;
     // the slices' sums meet TP tiles at a time: two where eight waves' sums of two fit the LDS
     static constexpr int TP = RT16 > 1 && ND <= 9 ? 2 : 1;
     static constexpr int SUM_LDS = 8 * ND * TP * 1024;
@@ -86,14 +89,30 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
 {
     using T_ = Thin<DX, DQ, RT16, FROM>;
     constexpr int ND = T_::ND, PD = T_::PD;
-    constexpr bool RAW = FROM == kRaw, IN_LDS = FROM != kDirect;
+    constexpr bool RAW = FROM == kRaw, IN_LDS = FROM == kRaw || FROM == kCopied;
     static_assert(RT16 <= 2, "one row tile of the staged planes");
     __shared__ __attribute__((aligned(1024))) unsigned char lds[T_::LDS];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t log_cgw = 3u - t.log_ks;
-    const uint32_t cg = (blockIdx.x << log_cgw) + ((uint32_t)wave & ((1u << log_cgw) - 1u));
+    // (kRows: the row tiles of a column group run on one XCD side by side, so that its weights
+    // cross the fabric once; see map_tile in cop_mfma_kernel.hpp)
+    uint32_t cb = blockIdx.x, row_tile = 0;
+    if constexpr (FROM == kRows) {
+        const uint32_t RB = (uint32_t)a.RB, whole = (gridDim.x / RB) & ~7u;
+        if (cb < whole * RB) {
+            const uint32_t slot = cb >> 3;
+            row_tile = slot % RB;
+            cb = slot / RB * 8u + (cb & 7u);
+        } else {
+            const uint32_t rest = cb - whole * RB;
+            row_tile = rest % RB;
+            cb = whole + rest / RB;
+        }
+    }
+    const uint32_t row_first = row_tile * 32u;
+    const uint32_t cg = (cb << log_cgw) + ((uint32_t)wave & ((1u << log_cgw) - 1u));
     const uint32_t ks = (uint32_t)wave >> log_cgw;
     const bool active = cg < a.CT * 2u;                 // (the last workgroup may have columns to spare)
     const ProblemPtrs pp = b.prob[NB == 1 ? 0 : blockIdx.y];
@@ -118,6 +137,7 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
         return active && ks * ne < 4u * tiles ? ne : 0u;
     };
     auto mask_word = [&](uint32_t row) -> uint64_t {
+        row += row_first;
         return pp.mask != nullptr && (int)row < a.m ? __builtin_nontemporal_load(&pp.mask[(size_t)row * a.C + col]) : 0;
     };
 
@@ -132,7 +152,8 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
         (void *)((const unsigned char *)pp.planes + (size_t)(active ? ct : 0u) * b_bytes), 0, b_bytes, 0x00027000);
     const uint32_t lane_b = (j >> 1) * (DQ * kTileBytes) + ((j & 1u) * 32u + c16 * 16u + r16) * 16u;
     const __amdgpu_buffer_rsrc_t rsrc_a =
-        __builtin_amdgcn_make_buffer_rsrc((void *)pp.xd, 0, a_bytes, 0x00027000);
+        __builtin_amdgcn_make_buffer_rsrc((void *)((const unsigned char *)pp.xd + (size_t)row_tile * a_bytes), 0,
+                                          a_bytes, 0x00027000);
     const uint32_t lane_a = (j >> 1) * (DX * kTileBytes) + ((j & 1u) * 32u + r16) * 16u;
 
     v4i xb[PD][DQ], xs[PD][IN_LDS ? 1 : RT16][DX];
@@ -146,7 +167,7 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
         constexpr int p = decltype(p_c)::value;
         const uint32_t ob = asked < len ? lane_b + s_load * kBStage : kPastEnd;
         static_for<0, DQ>([&](auto d) {
-            xb[p][decltype(d)::value] = load_operand(rsrc_b, ob + decltype(d)::value * kTileBytes, true);
+            xb[p][decltype(d)::value] = load_operand(rsrc_b, ob + decltype(d)::value * kTileBytes, FROM != kRows);
         });
         if constexpr (!IN_LDS) {
             const uint32_t oa = asked < len ? lane_a + s_load * kAStage : kPastEnd;
@@ -332,7 +353,7 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
                     digit[d] += sums[((((o << log_cgw) + cgl) * ND + d) * (4 * TILES) + e) * 64u + lane];
             cop_finish<ND, 1, false>([&](int d, int) { return digit[d]; }, [](int) { return 0; },
                                      [&](uint64_t (&w)[1]) { w[0] = word; }, a, a.prev, pp.out, limb, colsum_S,
-                                     (int)(16u * (i0 + e / 4u) + 4u * j + e % 4u), col, a.m);
+                                     (int)(row_first + 16u * (i0 + e / 4u) + 4u * j + e % 4u), col, a.m);
         }
     });
 }
@@ -350,11 +371,15 @@ static bool thin_planes_fit(const Problem &p)
 // How a launch is split, and about what it takes.
 struct ThinPlan {
     uint32_t log_ks;        // KS = 2^log_ks slices of k
-    uint32_t blocks;        // workgroups of one problem
-    bool copied;            // staged planes through LDS (more than 16 rows)
-    uint64_t cost;          // tenths of a microsecond
+    uint32_t blocks;        // workgroups of one problem and row tile
+    bool copied;            // staged planes through LDS (17 to 32 rows)
+    uint64_t rounds;        // of workgroups on the compute units
+    uint64_t stages;        // of a slice, and those rounded up to whole rounds of the stages in flight
+    uint64_t padded;
+    uint64_t cost;          // tenths of a microsecond (up to 32 rows)
 };
 
+// (more than 32 rows: every 32-row tile by itself)
 static ThinPlan thin_plan(const Problem &p, int count)
 {
     // Slices of k: a compute unit holds one workgroup, so the launch takes as many rounds as there
@@ -362,15 +387,16 @@ static ThinPlan thin_plan(const Problem &p, int count)
     // starting and ending a workgroup costs, about three stages of eight waves.  (20 x 400 x 12288: two
     // slices in one round 16.0 us, four in two rounds 20.6.)
     const uint64_t S = (uint64_t)(kblocks(p.k) + 1) / 2u, groups = p.C / 16u, cus = (uint64_t)compute_units();
+    const uint64_t launches = (uint64_t)count * (uint64_t)((p.m + kThinRows - 1) / kThinRows);  // problems and row tiles
     ThinPlan plan{};
-    uint64_t least = ~0ull, rounds = 0;
+    uint64_t least = ~0ull;
     for (uint32_t l = 0; l <= 3 && (1ull << l) <= S; ++l) {
         const uint64_t blocks = (groups + (8u >> l) - 1) / (8u >> l);
-        const uint64_t r = (blocks * (uint64_t)count + cus - 1) / cus;
+        const uint64_t r = (blocks * launches + cus - 1) / cus;
         const uint64_t cost = r * (((S + (1u << l) - 1) >> l) + 3u);
         if (cost < least) {
             least = cost;
-            rounds = r;
+            plan.rounds = r;
             plan.log_ks = l;
             plan.blocks = (uint32_t)blocks;
         }
@@ -378,14 +404,14 @@ static ThinPlan thin_plan(const Problem &p, int count)
     // The planes of 32 rows weigh nearly as much as the weights of a wave: eight waves that read the
     // same ones (one slice) read them once, from LDS (32 x 768 x 24576: 31.5 us against 34.4); with
     // several slices fewer waves share them and nobody waits for the copy (x 8192: 17.8 and 16.0).
-    plan.copied = p.m > 16 && plan.log_ks == 0 && thin_planes_fit(p);
+    plan.copied = p.m > 16 && p.m <= kThinRows && plan.log_ks == 0 && thin_planes_fit(p);
     // (whole rounds of the stages in flight: what is past the last one costs its products, but no loads)
-    const uint64_t stages = (S + (1u << plan.log_ks) - 1) >> plan.log_ks;
+    plan.stages = (S + (1u << plan.log_ks) - 1) >> plan.log_ks;
     const uint64_t depth = (uint64_t)thin_depth(planes_x(p.x_bits), planes_q(p.q_bits_max), p.m <= 16 ? 1 : 2,
                                                 plan.copied ? kCopied : kDirect);
-    const uint64_t padded = (stages + depth - 1) / depth * depth;
-    plan.cost = rounds * ((p.m <= 16 ? 63u : plan.copied ? 107u : 80u) + 9u * (stages + padded)) +
-                13u * plan.blocks * (uint64_t)count / cus;
+    plan.padded = (plan.stages + depth - 1) / depth * depth;
+    plan.cost = plan.rounds * ((p.m <= 16 ? 63u : plan.copied ? 107u : 80u) + 9u * (plan.stages + plan.padded)) +
+                13u * plan.blocks * launches / cus;
     return plan;
 }
 
@@ -402,8 +428,39 @@ static ThinPlan thin_plan(const Problem &p, int count)
 // left to the tile kernel in any case; its workgroups walk the tiles.
 static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (1ull << 30); }
 
+// More than 32 rows on few columns: where the tile kernel's workgroups leave compute units without a
+// tile, this kernel's row tiles and slices of k fill them (us, tiles and this kernel, 20-bit shares
+// and 54-bit moduli: 128 x 3072 x 1024 43.0 and 13.3, 128 x 1536 x 2048 24.8 and 13.1, 200 x 512 x 256
+// 11.9 and 6.9).  Every row tile reads the
+// weights again, from the L2, so the line is where the chip fills up (64 x 768 x 8192 16.3 and 18.5).
+// Both estimates in hundredths of a microsecond, fitted to 1360 sizes (33 to 512 rows, k from 512 to
+// 3072, 256 to 16384 columns, four pairs of plane counts) on 256 compute units: per round of workgroups
+// its start and end, per k-block or stage the wait for its operands and its products, and the bytes of
+// weights, mask and results.  With six per cent between them the choice is 0.2 % slower than the
+// better kernel on average and 7 % slower than the tiles at worst (96 x 3072 x 4096, 16-bit shares);
+// tiles everywhere would be 28 % slower.  Fewer k-blocks than sixteen, two for each of eight slices,
+// stay with the tiles.
+static bool thin_rows_apply(const Problem &p, int count)
+{
+    const int KB = kblocks(p.k), DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);
+    const TileBlocks tb = tile_blocks(p, count);
+    const double cus = (double)compute_units(), n = (double)count;
+    if (KB < 16 || (double)(p.C / 64u) * tb.row_blocks * n > cus) return false;
+    const ThinPlan plan = thin_plan(p, count);
+    const int row_tiles = (p.m + kThinRows - 1) / kThinRows;
+    if (plan.rounds > 2 || (uint64_t)plan.blocks * (uint64_t)row_tiles * 512u >= (1ull << 32)) return false;
+    const int rows16 = ((tb.tiles * kTile < p.m ? tb.tiles * kTile : p.m) + 15) / 16;
+    const double weights = n * (double)p.C * KB * DQ, results = n * (double)p.m * (double)p.C;
+    const double products = DX * DQ, rounds = (double)plan.rounds;
+    const double tiles = 476 + KB * (10 + 0.66 * products * ((rows16 + 1) / 2)) + 1.5e-4 * weights + 2.8e-4 * results;
+    const double rows = rounds * (584 + 24. * (double)plan.stages + 3.5 * products * (double)plan.padded) +
+                        (3.7e-4 + 1.3e-5 * row_tiles) * weights + 1.5e-4 * results;
+    return 1.06 * rows < tiles;
+}
+
 bool thin_applies(const Problem &p, int count)
 {
+    if (p.m > kThinRows) return thin_rows_apply(p, count);
     if (!thin_possible(p)) return false;
     const uint64_t cus = (uint64_t)compute_units();
     const uint64_t rounds = (p.C / (2u * kTile) * (uint64_t)count + cus - 1) / cus;
@@ -435,7 +492,8 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     t.quads_magic = (uint32_t)(((1ull << 32) + quads - 1) / quads);     // (items below 2^16, Q below 2^13)
     const ThinPlan plan = thin_plan(p, count);
     t.log_ks = plan.log_ks;
-    const dim3 grid(plan.blocks, (uint32_t)count), block(512);
+    a.RB = (p.m + kThinRows - 1) / kThinRows;
+    const dim3 grid(plan.blocks * (uint32_t)a.RB, (uint32_t)count), block(512);
     auto go_with = [&](auto rt_c, auto from_c, auto nb_c) {
         constexpr int NB = decltype(nb_c)::value;
         BatchPtrs<NB> b{};
@@ -462,6 +520,7 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     const std::integral_constant<int, 2> two;
     if (X) return go(one, raw);
     if (p.m <= 16) return go(one, direct);
+    if (p.m > kThinRows) return go(two, std::integral_constant<ThinShares, kRows>{});
     return plan.copied ? go(two, copied) : go(two, direct);
 }
 
