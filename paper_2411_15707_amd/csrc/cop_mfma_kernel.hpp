@@ -408,9 +408,10 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     auto step = [&](int t, auto steady_c) {
         constexpr bool STEADY = decltype(steady_c)::value;
         constexpr int NG = NT * DX, NBAR = NG - AHEAD;      // groups; the barrier stands in front of group NBAR
-        // the loads of two stages, spread over the products in front of the barrier; where the
-        // shares are one step ahead only, over the first of them
-        constexpr int NITEMS = 2 * MAXU, SPAN = NBAR * DQ / (P_::LEAD_B - P_::LEAD_A + 1);
+        // the loads of two stages, over the first quarter of the products in front of the barrier (the
+        // kernel on 128 x 3072 x 16384 104.3 us, spread over all of them 107.3, with the first few
+        // 105.6); over the first half or third where the shares are less far ahead
+        constexpr int NITEMS = 2 * MAXU, SPAN = NBAR * DQ / (P_::LEAD_A == P_::LEAD_B ? 4 : P_::LEAD_B - P_::LEAD_A + 1);
         int issue_n[2] = {n_loads, n_loads};
         if constexpr (!STEADY) {
             if (2 * t + lead >= KB) issue_n[0] = 0;
