@@ -1,56 +1,45 @@
 // Matrix-core (int8 MFMA) kernel for the COP accumulation on the CANONICAL layout, gfx950:
-// nimbus_cop_matmul without any setup pass.  Same contraction and same epilogue as the kernel
+// nimbus_cop_matmul without any setup pass.  Same contraction and same reduction as the kernel
 // for prepared weights (cop_mfma_kernel.hpp; Algorithm 1 step 2 + step 4 of the paper), but both
-// operands arrive as 64-bit words and are split into signed byte planes inside the loop:
+// operands arrive as 64-bit words and are split into signed byte planes inside the loop, 64 k a
+// stage, one stage ahead of the products:
 //
-//   ciphertext words  ctW[k][C]: a 32 x 64 tile per k-block (16 KB) comes into a ring of raw
-//       tiles in LDS by direct-to-LDS loads, three k-blocks ahead; one k-block ahead of its use
-//       every thread takes four words of one column (four consecutive k), recodes them into
-//       signed bytes (digits of the residue c itself: unlike the setup pass of the other
-//       kernel it does not centre first, which would cost five vector instructions a word)
-//       and writes one 32-bit word (four k-slots) into each of the DQ operand tiles of that
-//       column tile;
-//   shares  X[m][k]: a 128 x 32 tile per k-block comes from L2 into registers, one k-block
-//       ahead; every thread turns 2 x 4 consecutive k of one row into one word per plane.
+//   ciphertext words  ctW[k][C]: a 64 x 64 tile per stage comes straight into registers, eight
+//       consecutive k of one column per thread (a wave reads whole rows of 64 columns), asked
+//       for a stage before they are recoded into signed bytes (digits of the residue c itself:
+//       unlike the setup pass of the other kernel it does not centre first where it need
+//       not, which would cost five vector instructions a word), transposed and written as one
+//       8-byte word into each of the DQ operand tiles;
+//   shares  X[m][k]: a 128 x 64 tile per stage from L2, two items of eight consecutive k of one
+//       row per thread, one 8-byte word into each of the DX planes.
 //
-// The operand tiles in LDS have the register order of the instruction, exactly as the setup
-// pass of the other kernel would have left them in memory; the products run on
-// v_mfma_i32_32x32x32_i8: 8 waves, wave (wr, wc) owns 32 rows x 32 columns, DX * DQ
-// instructions per k-block into DX + DQ - 1 diagonal accumulators.  The column sums S that the
-// share offset OFFX needs (x = x' + OFFX) are gathered on the way: every thread adds up the
-// words it converts, the partial sums meet in LDS after the loop.
+// The operand tiles in LDS (two buffers) have the register order of v_mfma_i32_16x16x64_i8; wave w owns
+// 16 columns and half of the 16-row tiles, its operands rotate, and there is one barrier per
+// stage, all as in the kernel for prepared weights.  The column sums S that the share offset OFFX
+// needs (x = x' + OFFX) are gathered on the way: every thread adds up the words it converts,
+// the partial sums meet in LDS after the loop.
 //
-// One barrier per k-block: it publishes the operand tiles of block s (written during block
-// s - 1) and the raw tile of block s + 1, and it frees the operand buffer of block s - 1 and
-// the raw slot of block s for the loads of block s + 3.
-#include "cop_mfma_common.hpp"
+// What bounds it: the conversion's vector instructions (about 124 per thread and stage) next to
+// the products.  Against the kernel before (cop_canon32.hip: 32 k a stage, raw words through LDS,
+// 4-byte writes; still the faster one with three share and eight ciphertext planes): 128 x 768 x 16384,
+// 20-bit shares, 46.9 us -> 41.8; half as many LDS writes and barriers, no words through LDS on the
+// way in, and few rows pay for their own 16-row tiles only (1 x 768 x 16384 1.4 times as fast).
+#include "cop_canon.hpp"
 
 namespace nimbus {
 
-struct CanonArgs {
-    MfmaArgs e;               // sizes, tile mapping, OFFX and the epilogue's constants
-    const uint64_t *X;        // [m][k]
-    const uint64_t *ctW;      // [k][C]
-    int k;
-    LimbTable limbs;          // reduction of the column sums
-};
+
+typedef int v2i __attribute__((ext_vector_type(2)));
 
 template <int OFF>
-__device__ __forceinline__ uint64_t lds_read_b64(uint32_t addr)
+__device__ __forceinline__ void lds_write_b64(uint32_t addr, uint32_t lo, uint32_t hi)
 {
-    uint64_t r;
-    asm volatile("ds_read_b64 %0, %1 offset:%2" : "=v"(r) : "v"(addr), "n"(OFF) : "memory");
-    return r;
+    const uint64_t v = (uint64_t)hi << 32 | lo;
+    asm volatile("ds_write_b64 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory");
 }
-template <int OFF>
-__device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v)
-{
-    asm volatile("ds_write_b32 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory");
-}
-__device__ __forceinline__ void tie64(uint64_t &x) { asm volatile("" : "+v"(x)); }
 
 // FULL: m is a multiple of 128.  SHARED: several row blocks per column tile (m > 128); they
-// start at the same k-block and load the ciphertext without the streaming hint, so that the
+// start at the same k and load the ciphertext without the streaming hint, so that the
 // tile is found in the L2 of their XCD by all but the first.
 // CENTRE: the ciphertext digits are those of the centred residue (c or c - q) instead of the
 // residue itself.  Needed when a residue can exceed what DQ signed digits express,
@@ -61,23 +50,16 @@ __global__ __launch_bounds__(512, 1) void cop_canon_kernel(const CanonArgs ca)
 {
     const MfmaArgs &a = ca.e;
     constexpr int ND = DX + DQ - 1;
-    constexpr int A_BYTES = 4 * DX * kTileBytes, B_BYTES = 2 * DQ * kTileBytes;
-    constexpr int STAGE = A_BYTES + B_BYTES;            // operand tiles of one k-block
-    // raw ciphertext tile: 16 loads of 1 KB (two k-rows of 64 words each); the four k-rows
-    // 4g .. 4g+3 of k-group g take 2 KB, followed by 128 bytes of padding, so that
-    // neighbouring k-groups, which the two halves of a wave read at once, start in different
-    // halves of the banks
-    constexpr int RAW_GROUP = 2 * kTileBytes + 128;
-    constexpr int RAW_SLOT = 8 * RAW_GROUP, RAW_RING = 3;
-    constexpr int RAW0 = 2 * STAGE;
-    constexpr int LDS_BYTES = RAW0 + RAW_RING * RAW_SLOT;
-    static_assert(LDS_BYTES <= 160 * 1024, "LDS");
-    static_assert(64 * 8 * 16 <= RAW_RING * RAW_SLOT, "the column sums reuse the raw ring");
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[LDS_BYTES];
+    // operand tiles of one stage, 16 rows (or columns) x 64 k of one plane in 1 KB: 8 DX of the
+    // shares, 4 DQ of the ciphertext, twice
+    constexpr int A_BYTES = 8 * DX * kTileBytes, B_BYTES = 4 * DQ * kTileBytes, STAGE = A_BYTES + B_BYTES;
+    static_assert(2 * STAGE <= 160 * 1024, "LDS");
+    static_assert(64 * 8 * 16 <= STAGE, "the column sums reuse the operand tiles");
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[2 * STAGE];
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // 0..7
-    const int wr = wave >> 1, wc = wave & 1;
+    const int wh = wave >> 2, wc = wave & 3;        // 16-row tiles wh, wh + 2, ...; 16-column group
 
     // workgroup -> (64-column tile, row block), as in the kernel for prepared weights
     uint32_t ct2, rb;
@@ -98,45 +80,36 @@ __global__ __launch_bounds__(512, 1) void cop_canon_kernel(const CanonArgs ca)
             ct2 = CT2a + t / RB;
         }
     }
-    const int RT = (a.m + kTile - 1) / kTile;
-    const int rt = (int)rb * 4 + wr;
-    const bool active = FULL || rt < RT;            // this wave has rows (wave-uniform)
-    const int KB = a.KB;
+    const int block_rows = FULL ? 128 : (int)a.block_tiles * kTile;
+    const int row_first = (int)rb * block_rows;
+    const int row_end = FULL || row_first + block_rows < a.m ? row_first + block_rows : a.m;
+    const int S = (a.KB + 1) >> 1;                  // stages of 64 k
     const uint32_t K = (uint32_t)ca.k, C = a.C;
     const uint32_t lds0 = (uint32_t)(uintptr_t)(NIMBUS_AS3 void *)&lds[0];
 
-    // ---- ciphertext side: raw tile loads and this thread's conversion item ----
-    // load p of a stage (0 <= p < 16) moves k-rows 2p and 2p+1 of the tile: lanes 0-31 the 64
-    // words of row 2p (16 bytes = two columns per lane), lanes 32-63 those of row 2p+1.  Wave w
-    // issues loads w and w + 8.  Rows past k read as zero (the descriptor ends with ctW), and a
-    // zero word recodes to zero digits: the padding of the last k-block costs nothing.
+    // stage s is the 64 k from 64 ((s + s_start) mod S) on (column tiles start at different k)
+    uint32_t s_start = ct2 % (uint32_t)S;
+    auto next_stage = [&](uint32_t s) -> uint32_t { return s + 1 == (uint32_t)S ? 0u : s + 1; };
+
+    // ---- ciphertext: wave w converts the k 8 w .. 8 w + 7 of the stage, lane l column l ----
+    // Rows past k read as zero, from an offset that lies behind the end of every descriptor (ctW is a
+    // multiple of 512 bytes and smaller than 4 GB), and a zero word recodes to zero digits.
+    constexpr uint32_t kPastEnd = 0xfffffe00u;
     const uint64_t ct_first = (uint64_t)ct2 * 64u * 8u;
     const __amdgpu_buffer_rsrc_t rsrc_ct = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const unsigned char *)ca.ctW + ct_first), 0,
         (uint32_t)((uint64_t)K * C * 8u - ct_first), 0x00027000);
-    const uint32_t voff_ct = (uint32_t)(lane >> 5) * C * 8u + (uint32_t)(lane & 31) * 16u;
     const uint32_t row_bytes = C * 8u;
-    uint32_t ct_src[2], ct_dst[2];                  // wave-uniform: source offset in the k-block, place in the slot
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const uint32_t p = (uint32_t)wave + 8u * (uint32_t)i;
-        ct_src[i] = 2u * p * row_bytes;
-        ct_dst[i] = (uint32_t)RAW0 + (p >> 1) * RAW_GROUP + (p & 1u) * kTileBytes;
-    }
-    // conversion item: column c of the tile (16 columns per wave), k-group g (k = 4g .. 4g+3)
-    const uint32_t cv_c = 16u * ((uint32_t)wave & 3u) + ((uint32_t)lane & 15u);
-    const uint32_t cv_g = 4u * ((uint32_t)wave >> 2) + ((uint32_t)lane >> 4);
-    const uint32_t cv_raw = lds0 + (uint32_t)RAW0 + cv_g * RAW_GROUP + cv_c * 8u;
-    // its word in the operand tiles: column tile cv_c / 32, lane slot (cv_c % 32) + 32 (g / 4),
-    // word g % 4; plane b follows at b KB
-    const uint32_t cv_out = lds0 + (uint32_t)A_BYTES + (cv_c >> 5) * (DQ * kTileBytes) +
-                            ((cv_c & 31u) + 32u * (cv_g >> 2)) * 16u + (cv_g & 3u) * 4u;
-    // modulus of the item's column (16 aligned columns lie in one limb: N >= 32)
-    uint64_t cv_q = 0;
+    // its place in the operand tiles (slot j 16 + column % 16 of the tile, half of the 16 bytes);
+    // plane b follows at b KB.  Share tiles rotate the rows of a k-quarter j by 4 j, so that the
+    // eight lanes of a row (below) write to different banks; so do these.
+    const uint32_t cv_j = (uint32_t)wave >> 1;
+    const uint32_t cv_out = lds0 + A_BYTES + ((uint32_t)lane >> 4) * (DQ * kTileBytes) +
+                            (cv_j * 16u + (((uint32_t)lane + 4u * cv_j) & 15u)) * 16u + ((uint32_t)wave & 1u) * 8u;
+    uint64_t cv_q = 0;                              // modulus of the lane's column (N >= 32)
     if constexpr (CENTRE) {
-        const uint32_t blk = ((ct2 * 2u + (((uint32_t)wave & 3u) >> 1)) * kTile) >> a.log_n;
-        uint32_t l = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
-        l = __builtin_amdgcn_readfirstlane(l);
+        const uint32_t blk = (ct2 * 64u + (uint32_t)(lane & 32)) >> a.log_n;
+        const uint32_t l = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
         cv_q = a.q[l];
     }
     const uint64_t cv_half = (cv_q - 1) >> 1;
@@ -147,227 +120,266 @@ __global__ __launch_bounds__(512, 1) void cop_canon_kernel(const CanonArgs ca)
     // 32 x 32 + 64-bit multiply-add by one each: k / 8 words of 32 bits cannot overflow 64)
     uint64_t sum_lo = 0, sum_hi = 0;
 
-    // ---- share side: two items per thread, item i: 16 rows x 4 k-quads per wave ----
-    // item t = 2 wave + i: rows 16 (t % 8) + lane / 4, k-quad 4 (t / 8) + lane % 4 (k = 4 kq .. +3)
-    const uint64_t x_first = (uint64_t)rb * 128u * K * 8u;
+    // ---- shares: item i of a thread is eight k of row 16 w + 8 i + l / 8, octet l % 8 ----
+    const uint64_t x_first = (uint64_t)row_first * K * 8u;
     const uint64_t x_left = (uint64_t)a.m * K * 8u - x_first;
     const __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
         (void *)((const unsigned char *)ca.X + x_first), 0,
         x_left > 0xffffffffull ? 0xffffffffu : (uint32_t)x_left, 0x00027000);
-    uint32_t voff_x[2], x_out[2];
+    uint32_t x_off[2], x_out[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        const uint32_t t = 2u * (uint32_t)wave + (uint32_t)i;
-        const uint32_t r = 16u * (t & 7u) + ((uint32_t)lane >> 2);
-        const uint32_t kq = 4u * (t >> 3) + ((uint32_t)lane & 3u);
-        voff_x[i] = r * K * 8u + kq * 32u;
-        // row tile r / 32, lane slot (r % 32) + 32 (kq / 4), word kq % 4; plane a at a KB
-        x_out[i] = lds0 + (r >> 5) * (DX * kTileBytes) + ((r & 31u) + 32u * (kq >> 2)) * 16u +
-                   (kq & 3u) * 4u;
+        const uint32_t r = 16u * (uint32_t)wave + 8u * (uint32_t)i + ((uint32_t)lane >> 3), o = (uint32_t)lane & 7u;
+        x_off[i] = r * K * 8u + o * 64u;
+        x_out[i] = lds0 + (r >> 4) * (DX * kTileBytes) + ((o >> 1) * 16u + ((r + 4u * (o >> 1)) & 15u)) * 16u + (o & 1u) * 8u;
     }
 
-    // stage s is k-block (s + k_start) mod KB (column tiles start at different k-blocks)
-    uint32_t k_start = ct2 - __umulhi(ct2, a.kb_magic) * (uint32_t)KB;
-    if (k_start >= (uint32_t)KB) k_start -= (uint32_t)KB;
-    uint32_t kb_issue = k_start;                    // k-block of the next stage whose loads go out
-    auto next_kb = [&](uint32_t kb) -> uint32_t { return kb + 1 == (uint32_t)KB ? 0u : kb + 1; };
-    uint32_t raw_issue = 0;                         // raw slot of that stage (0 .. RAW_RING-1)
-    auto issue_raw = [&]() {                        // both loads of this wave for the stage
+    v2i cw[8];                                      // raw words of the stage after the one at hand
+    auto load_ct = [&](uint32_t s) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i)
-            // (the whole offset goes into the per-lane operand: that is the one the range
-            // check of the descriptor looks at, and rows past k must read as zero)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rsrc_ct, (NIMBUS_AS3 void *)(lds + (ct_dst[i] + raw_issue * RAW_SLOT)), 16,
-                voff_ct + (ct_src[i] + kb_issue * 32u * row_bytes), 0, 0, SHARED ? 0 : 2);
-        kb_issue = next_kb(kb_issue);
-        raw_issue = raw_issue + 1 == RAW_RING ? 0u : raw_issue + 1;
-    };
-    uint32_t kb_x = k_start;                        // k-block of the next share loads
-    v4i xr[2][2];                                   // raw shares: [item][half of the 32 bytes]
-    auto load_x = [&]() {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t at = voff_x[i] + kb_x * 256u;
-            xr[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, at, 0, 0);
-            xr[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, at + 16u, 0, 0);
+        for (int i = 0; i < 8; ++i) {
+            const uint32_t row = s * 64u + (uint32_t)wave * 8u + (uint32_t)i;
+            cw[i] = __builtin_amdgcn_raw_buffer_load_b64(
+                rsrc_ct, (row < K ? row * row_bytes : kPastEnd) + (uint32_t)lane * 8u, 0, SHARED ? 0 : 2);
         }
-        kb_x = next_kb(kb_x);
     };
-
-    // conversion of one stage, in pieces that the loop places between its matrix-core
-    // instructions: raw slot `rs`, operand buffer `ob`
-    uint64_t cw[4];
-    auto ct_read = [&](uint32_t rs) {
-        const uint32_t base = cv_raw + rs * RAW_SLOT;
-        cw[0] = lds_read_b64<0>(base);
-        cw[1] = lds_read_b64<512>(base);
-        cw[2] = lds_read_b64<1024>(base);
-        cw[3] = lds_read_b64<1536>(base);
-    };
-    auto ct_recode = [&]() {                        // after the LDS wait
+    auto load_x = [&](v4i (&x)[4], int i, uint32_t s) {
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            tie64(cw[j]);
-            const uint64_t c = cw[j];
+        for (int u = 0; u < 4; ++u)
+            x[u] = __builtin_amdgcn_raw_buffer_load_b128(rsrc_x, x_off[i] + s * 512u + (uint32_t)u * 16u, 0, 0);
+    };
+    // words 4 h .. 4 h + 3: the sums, and the signed base-256 digits of the residue (centred first where
+    // it has to be): c' + 0x80..80 has the bytes digit + 128, and flipping bit 7 of each gives
+    // the digits as signed bytes
+    auto ct_recode = [&](int h) {
+#pragma unroll
+        for (int i = 4 * h; i < 4 * h + 4; ++i) {
+            const uint64_t c = (uint64_t)(uint32_t)cw[i].y << 32 | (uint32_t)cw[i].x;
             asm("v_mad_u64_u32 %0, vcc, %1, 1, %0" : "+v"(sum_lo) : "v"((uint32_t)c) : "vcc");
             asm("v_mad_u64_u32 %0, vcc, %1, 1, %0" : "+v"(sum_hi) : "v"((uint32_t)(c >> 32)) : "vcc");
-            // signed base-256 digits of the residue, centred first where it has to be:
-            // c' + 0x80..80 has the bytes digit + 128, and flipping bit 7 of each gives the
-            // digits as signed bytes
             const uint64_t cc = CENTRE && c > cv_half ? c - cv_q : c;  // two's complement of c'
-            cw[j] = (cc + bias) ^ bias;
+            const uint64_t d = (cc + bias) ^ bias;
+            cw[i] = v2i{(int)(uint32_t)d, (int)(uint32_t)(d >> 32)};
         }
     };
-    auto ct_write = [&](uint32_t ob) {
-        const uint32_t base = cv_out + ob * STAGE;
-        uint32_t t[4];
-        transpose4((uint32_t)cw[0], (uint32_t)cw[1], (uint32_t)cw[2], (uint32_t)cw[3], t);
-        lds_write_b32<0 * kTileBytes>(base, t[0]);
-        lds_write_b32<1 * kTileBytes>(base, t[1]);
-        lds_write_b32<2 * kTileBytes>(base, t[2]);
-        lds_write_b32<3 * kTileBytes>(base, t[3]);
-        transpose4((uint32_t)(cw[0] >> 32), (uint32_t)(cw[1] >> 32), (uint32_t)(cw[2] >> 32),
-                   (uint32_t)(cw[3] >> 32), t);
-        lds_write_b32<4 * kTileBytes>(base, t[0]);
-        lds_write_b32<5 * kTileBytes>(base, t[1]);
-        lds_write_b32<6 * kTileBytes>(base, t[2]);
-        if constexpr (DQ == 8) lds_write_b32<7 * kTileBytes>(base, t[3]);
+    auto ct_write = [&](auto half_c, uint32_t buf) {     // planes 0-3, or 4 .. DQ-1
+        constexpr int half = decltype(half_c)::value;
+        const uint32_t at = cv_out + buf;
+        uint32_t lo[4], hi[4];
+        transpose4((uint32_t)cw[0][half], (uint32_t)cw[1][half], (uint32_t)cw[2][half], (uint32_t)cw[3][half], lo);
+        transpose4((uint32_t)cw[4][half], (uint32_t)cw[5][half], (uint32_t)cw[6][half], (uint32_t)cw[7][half], hi);
+        static_for<0, half ? DQ - 4 : 4>([&](auto d_c) {
+            constexpr int d = decltype(d_c)::value;
+            lds_write_b64<(4 * half + d) * kTileBytes>(at, lo[d], hi[d]);
+        });
     };
-    auto x_write = [&](uint32_t ob, auto i_c) {     // item i: regs -> DX plane words
-        constexpr int i = decltype(i_c)::value;
-        const uint32_t base = x_out[i] + ob * STAGE;
-        uint32_t t[4];
+    auto x_write = [&](const v4i (&x)[4], int i, uint32_t buf) {
+        const uint32_t at = x_out[i] + buf;
+        uint32_t lo[4], hi[4];
         // flipping bit 7 of the shifted bytes turns them into the digits byte - 128
-        transpose4((uint32_t)xr[i][0].x ^ a.offx, (uint32_t)xr[i][0].z ^ a.offx,
-                   (uint32_t)xr[i][1].x ^ a.offx, (uint32_t)xr[i][1].z ^ a.offx, t);
-        lds_write_b32<0 * kTileBytes>(base, t[0]);
-        lds_write_b32<1 * kTileBytes>(base, t[1]);
-        if constexpr (DX >= 3) lds_write_b32<2 * kTileBytes>(base, t[2]);
-        if constexpr (DX >= 4) lds_write_b32<3 * kTileBytes>(base, t[3]);
+        transpose4((uint32_t)x[0].x ^ a.offx, (uint32_t)x[0].z ^ a.offx, (uint32_t)x[1].x ^ a.offx,
+                   (uint32_t)x[1].z ^ a.offx, lo);
+        transpose4((uint32_t)x[2].x ^ a.offx, (uint32_t)x[2].z ^ a.offx, (uint32_t)x[3].x ^ a.offx,
+                   (uint32_t)x[3].z ^ a.offx, hi);
+        static_for<0, DX>([&](auto d_c) {
+            constexpr int d = decltype(d_c)::value;
+            lds_write_b64<d * kTileBytes>(at, lo[d], hi[d]);
+        });
     };
 
-    // ---- prologue: raw tiles of stages 0 .. 2 and the shares of stage 0 on their way,
-    // accumulators cleared, stage 0 converted into operand buffer 0 ----
-    issue_raw();
-    load_x();
-    if (KB > 1) issue_raw();
-    if (KB > 2) issue_raw();
-    v16i acc[ND];
-#pragma unroll
-    for (int d = 0; d < ND; ++d) {
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[d][r] = 0;
-        tie_acc(acc[d]);
-    }
-    // this wave's raw loads of stage 0 are older than its 4 share loads and 2 loads per later stage
-    wait_vmem_n(4 + 2 * (KB > 2 ? 2 : KB - 1));
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    ct_read(0);
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    ct_recode();
-    ct_write(0);
-    x_write(0, std::integral_constant<int, 0>{});
-    x_write(0, std::integral_constant<int, 1>{});
+    // ---- operands out of LDS: 16-row tile t is rows 16 t .. of the block, this wave has wh + 2 i ----
+    const uint32_t slot = ((uint32_t)lane & 48u) + (((uint32_t)lane + 4u * ((uint32_t)lane >> 4)) & 15u);
+    const uint32_t laneA = lds0 + (uint32_t)(wh * DX) * kTileBytes + slot * 16u;
+    const uint32_t laneB = lds0 + A_BYTES + (uint32_t)(wc * DQ) * kTileBytes + slot * 16u;
 
-    // ---- the loop ----
-    const uint32_t laneA = lds0 + (uint32_t)(wr * DX) * kTileBytes + (uint32_t)lane * 16u;
-    const uint32_t laneB = lds0 + (uint32_t)A_BYTES + (uint32_t)(wc * DQ) * kTileBytes +
-                           (uint32_t)lane * 16u;
-    constexpr int NPOS = DX * DQ;
-    uint32_t ob = 0, rs = 1;                        // operand buffer of stage s, raw slot of stage s + 1
-    for (int s = 0; s < KB; ++s) {
-        const bool more = s + 1 < KB;               // stage s + 1 exists: convert it during this block
-        // operand words of stage s written, raw tile of stage s + 1 landed (younger: the two
-        // loads of stage s + 2), then the barrier
+    // the stages for a wave of NT 16-row tiles, then its part of the epilogue
+    auto pass = [&](auto nt_c) {
+        constexpr int NT = decltype(nt_c)::value, NA = NT > 0 ? NT : 1;
+        constexpr int NG = NT * DX;                 // groups of DQ products, one share operand each
+        // Both items of the shares a stage ahead where the registers allow it, else the second is asked
+        // for when the first is converted (128 x 768 x 16384, 20-bit shares: 41.8 us and 45.1; with
+        // spills 36 bytes a thread cost a tenth).
+        constexpr bool BOTH = ND * NT * 4 + DQ * 4 <= (FULL && !CENTRE ? 176 : 160);
+        v4i xw[BOTH ? 2 : 1][4];
+        uint32_t s_load = s_start;                  // next stage to ask for
+        load_x(xw[0], 0, s_load);
+        if constexpr (BOTH) load_x(xw[1], 1, s_load);
+        load_ct(s_load);
+        v4i acc[ND][NA];
+#pragma unroll
+        for (int d = 0; d < ND; ++d)
+#pragma unroll
+            for (int i = 0; i < NT; ++i) {
+                acc[d][i] = v4i{0, 0, 0, 0};
+                tie(acc[d][i]);
+            }
+        // stage 0 converted, stage 1 asked for
+        x_write(xw[0], 0, 0);
+        if constexpr (!BOTH) load_x(xw[0], 1, s_load);
+        s_load = next_stage(s_load);
+        if constexpr (BOTH) {
+            x_write(xw[1], 1, 0);
+            if (S > 1) {
+                load_x(xw[0], 0, s_load);
+                load_x(xw[1], 1, s_load);
+            }
+        }
+        ct_recode(0);
+        ct_recode(1);
+        ct_write(std::integral_constant<int, 0>{}, 0);
+        ct_write(std::integral_constant<int, 1>{}, 0);
+        if constexpr (!BOTH) {
+            x_write(xw[0], 1, 0);
+            if (S > 1) load_x(xw[0], 0, s_load);
+        }
+        if (S > 1) load_ct(s_load);
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (s + 3 < KB) wait_vmem<2>();             // steady state: stage s + 2 may be in flight
-        else wait_vmem<0>();
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
-        v4i xa[DX], xb[DQ];
-        if (active) {
-            const uint32_t pa = laneA + ob * STAGE, pb = laneB + ob * STAGE;
-            static_for<0, DX>([&](auto d_c) {
-                constexpr int d = decltype(d_c)::value;
-                xa[d] = lds_read_b128<d * kTileBytes>(pa);
-            });
-            static_for<0, DQ>([&](auto d_c) {
-                constexpr int d = decltype(d_c)::value;
-                xb[d] = lds_read_b128<d * kTileBytes>(pb);
-            });
-        }
-        if (more) {
-            load_x();                               // shares of stage s + 1 (from L2)
-            ct_read(rs);                            // raw words of stage s + 1
-        }
-        if (s + 3 < KB) issue_raw();                // stage s + 3 into the slot stage s has left
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-        if (active) {
-#pragma unroll
-            for (int d = 0; d < DX; ++d) tie(xa[d]);
-#pragma unroll
-            for (int d = 0; d < DQ; ++d) tie(xb[d]);
-        }
-        const uint32_t nb = ob ^ 1u;                // operand buffer of stage s + 1
-        static_for<0, NPOS>([&](auto i_c) {
-            constexpr int i = decltype(i_c)::value;
-            constexpr int dx = i / DQ, dq = i % DQ;
-            if (active) {
-                tie(xa[dx]);
-                tie(xb[dq]);
-                acc[dx + dq] = __builtin_amdgcn_mfma_i32_32x32x32_i8(xa[dx], xb[dq], acc[dx + dq],
-                                                                     0, 0, 0);
-                tie_acc(acc[dx + dq]);
-            }
-            if constexpr (i == NPOS / 8) { if (more) ct_recode(); }
-            if constexpr (i == NPOS / 2) { if (more) ct_write(nb); }
-            if constexpr (i == (3 * NPOS) / 4) { if (more) x_write(nb, std::integral_constant<int, 0>{}); }
-            if constexpr (i == (7 * NPOS) / 8) { if (more) x_write(nb, std::integral_constant<int, 1>{}); }
-        });
-        asm volatile("" ::: "memory");
-        ob = nb;
-        rs = rs + 1 == RAW_RING ? 0u : rs + 1;
-    }
-
-    // ---- column sums: the eight k-groups of a column meet in LDS (over the raw ring, which
-    // nobody reads any more once every wave is past the loop) ----
-    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    {
-        const uint32_t at = lds0 + (uint32_t)RAW0 + (cv_c * 8u + cv_g) * 16u;
-        asm volatile("ds_write_b64 %0, %1\n\tds_write_b64 %0, %2 offset:8"
-                     ::"v"(at), "v"(sum_lo), "v"(sum_hi) : "memory");
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    if (!active) return;
-    uint32_t limb;
-    {
-        const uint32_t blk = ((ct2 * 2u + (uint32_t)wc) * kTile) >> a.log_n;
-        limb = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
-        limb = __builtin_amdgcn_readfirstlane(limb);
-    }
-    uint64_t colsum_S;
-    {
-        const uint32_t at = lds0 + (uint32_t)RAW0 + ((uint32_t)(wc * kTile + (lane & 31)) * 8u) * 16u;
-        uint64_t lows = 0, highs = 0;               // each below 2^32 k
-        static_for<0, 8>([&](auto g_c) {
+        v4i xa[2], xb[DQ];
+        uint32_t rd = 0;                            // buffer that is read next
+        auto read_a = [&](auto g_c) {
             constexpr int g = decltype(g_c)::value;
-            uint64_t plo, phi;
-            asm volatile("ds_read_b64 %0, %2 offset:%3\n\tds_read_b64 %1, %2 offset:%4\n\t"
-                         "s_waitcnt lgkmcnt(0)"
-                         : "=&v"(plo), "=&v"(phi) : "v"(at), "n"(g * 16), "n"(g * 16 + 8) : "memory");
-            lows += plo;
-            highs += phi;
-        });
-        uint64_t lo = lows, hi = 0;                 // lows + 2^32 highs in 128 bits
-        add128(hi, lo, highs >> 32, highs << 32);
-        colsum_S = barrett128(hi, lo, ca.limbs.limb[limb]);      // k * q < 2^(b+63)
+            xa[g & 1] = lds_read_b128<(g / DX * 2 * DX + g % DX) * kTileBytes>(laneA + rd);
+        };
+        auto read_b = [&](auto d_c) {
+            xb[decltype(d_c)::value] = lds_read_b128<decltype(d_c)::value * kTileBytes>(laneB + rd);
+        };
+        if constexpr (NT > 0) {
+            read_a(std::integral_constant<int, 0>{});
+            static_for<0, DQ>([&](auto d_c) { read_b(d_c); });
+        }
+        for (int s = 0; s < S; ++s) {
+            const uint32_t nb = rd ? 0u : (uint32_t)STAGE;
+            // conversion of stage s + 1, in pieces between the products; what it frees asks for stage s + 2
+            const bool more = s + 1 < S, ask = s + 2 < S;
+            auto piece = [&](auto n_c) {
+                constexpr int n = decltype(n_c)::value;
+                if (!more) return;
+                if constexpr (n == 0) {
+                    x_write(xw[0], 0, nb);
+                    if constexpr (!BOTH) load_x(xw[0], 1, s_load);
+                    s_load = next_stage(s_load);
+                    if (BOTH && ask) load_x(xw[0], 0, s_load);
+                } else if constexpr (n == (BOTH ? 1 : 5)) {
+                    x_write(xw[BOTH], 1, nb);
+                    if (ask) load_x(xw[BOTH], BOTH, s_load);
+                } else if constexpr (n == (BOTH ? 2 : 1)) {
+                    ct_recode(0);
+                } else if constexpr (n == (BOTH ? 3 : 2)) {
+                    ct_recode(1);
+                } else if constexpr (n == (BOTH ? 4 : 3)) {
+                    ct_write(std::integral_constant<int, 0>{}, nb);
+                } else if constexpr (n == (BOTH ? 5 : 4)) {
+                    ct_write(std::integral_constant<int, 1>{}, nb);
+                }
+                if constexpr (n == 5)
+                    if (ask) load_ct(s_load);
+            };
+            constexpr int PIECES = 6;
+            auto meet = [&]() {
+                asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                __builtin_amdgcn_s_barrier();
+                asm volatile("" ::: "memory");
+                rd = nb;
+            };
+            if constexpr (NT == 0) {
+                static_for<0, PIECES>([&](auto n_c) { piece(n_c); });
+                meet();
+            } else {
+                constexpr int SPAN = (NG - 1) * DQ;
+                static_for<0, NG>([&](auto g_c) {
+                    constexpr int g = decltype(g_c)::value, i = g / DX, dx = g % DX;
+                    if constexpr (g == NG - 1) meet();
+                    if constexpr (g + 1 < NG) read_a(std::integral_constant<int, g + 1>{});
+                    else xa[(g + 1) & 1] = lds_read_b128<0>(laneA + rd);
+                    static_for<0, DQ>([&](auto d_c) {
+                        constexpr int dq = decltype(d_c)::value, pos = g * DQ + dq;
+                        if constexpr (g == 0) wait_lds<DQ - dq>(xb[dq]);
+                        else if constexpr (dq == 0 && g < NG - 1) wait_lds<1>(xa[g & 1]);
+                        tie(xa[g & 1]);
+                        tie(xb[dq]);
+                        acc[dx + dq][i] =
+                            __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[g & 1], xb[dq], acc[dx + dq][i], 0, 0, 0);
+                        tie(acc[dx + dq][i]);
+                        static_for<0, PIECES>([&](auto n_c) {
+                            if constexpr (decltype(n_c)::value * SPAN / PIECES == pos) piece(n_c);
+                        });
+                        if constexpr (g == NG - 1) read_b(d_c);
+                    });
+                });
+                if constexpr (NG % 2 == 1) {        // an odd number of groups: the next stage starts from set 0
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    tie(xa[1]);
+                    xa[0] = xa[1];
+                }
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        {
+            const uint32_t at = lds0 + ((uint32_t)lane * 8u + (uint32_t)wave) * 16u;
+            asm volatile("ds_write_b64 %0, %1\n\tds_write_b64 %0, %2 offset:8"
+                         ::"v"(at), "v"(sum_lo), "v"(sum_hi) : "memory");
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        if constexpr (NT > 0) {
+            uint32_t limb;
+            {
+                const uint32_t blk = (ct2 * 64u + (uint32_t)wc * 16u) >> a.log_n;
+                limb = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
+                limb = __builtin_amdgcn_readfirstlane(limb);
+            }
+            // column sums: the eight waves' parts meet in LDS (over the operand tiles)
+            uint64_t colsum_S;
+            {
+                const uint32_t at = lds0 + ((uint32_t)(wc * 16 + (lane & 15)) * 8u) * 16u;
+                uint64_t lows = 0, highs = 0;       // each below 2^32 k
+                static_for<0, 8>([&](auto g_c) {
+                    constexpr int g = decltype(g_c)::value;
+                    uint64_t plo, phi;
+                    asm volatile("ds_read_b64 %0, %2 offset:%3\n\tds_read_b64 %1, %2 offset:%4\n\t"
+                                 "s_waitcnt lgkmcnt(0)"
+                                 : "=&v"(plo), "=&v"(phi) : "v"(at), "n"(g * 16), "n"(g * 16 + 8) : "memory");
+                    lows += plo;
+                    highs += phi;
+                });
+                uint64_t lo = lows, hi = 0;         // lows + 2^32 highs in 128 bits
+                add128(hi, lo, highs >> 32, highs << 32);
+                colsum_S = barrett128(hi, lo, ca.limbs.limb[limb]);      // k * q < 2^(b+63)
+            }
+            constexpr int NE = 4 * NT;
+            const int row0 = row_first + 16 * wh + 4 * (lane >> 4);
+            const uint32_t col = ct2 * 64u + (uint32_t)wc * 16u + (uint32_t)(lane & 15);
+            auto roff = [](int r) -> int { return 32 * (r >> 2) + (r & 3); };
+            cop_finish<ND, NE, FULL>(
+                [&](int d, int r) -> int32_t { return acc[d][r >> 2][r & 3]; }, roff,
+                [&](uint64_t (&w)[NE]) {
+#pragma unroll
+                    for (int r = 0; r < NE; ++r) w[r] = 0;
+                    if (!a.mask) return;
+                    const uint64_t *const mask0 = a.mask + ((size_t)row0 * C + col);
+#pragma unroll
+                    for (int r = 0; r < NE; ++r)
+                        if (FULL || row0 + roff(r) < row_end)
+                            w[r] = __builtin_nontemporal_load(&mask0[(size_t)roff(r) * C]);
+                },
+                a, nullptr, a.out, limb, colsum_S, row0, col, row_end);
+        }
+    };
+    if constexpr (FULL) {
+        pass(std::integral_constant<int, 4>{});
+    } else {
+        const int nt = ((row_end - row_first + 15) / 16 + 1 - wh) >> 1;
+        switch (nt) {
+        case 3:
+        case 4: pass(std::integral_constant<int, 4>{}); break;
+        case 2: pass(std::integral_constant<int, 2>{}); break;
+        case 1: pass(std::integral_constant<int, 1>{}); break;
+        default: pass(std::integral_constant<int, 0>{});
+        }
     }
-    cop_epilogue<ND, FULL>(acc, a, a.mask, nullptr, a.out, limb, colsum_S, rt * kTile + 4 * (lane >> 5),
-                                  (ct2 * 2u + (uint32_t)wc) * kTile + (uint32_t)(lane & 31));
 }
 
 // ---------------------------------------------------------------------------
@@ -401,19 +413,27 @@ bool canon_supported(const Problem &p)
     return true;
 }
 
-template <int DX, int DQ>
-static hipError_t canon_impl(const Problem &p, const uint64_t *X, const uint64_t *ctW,
-                             const uint64_t *mask, uint64_t *out, hipStream_t stream)
+static CanonArgs canon_args(const Problem &p, int DX, int DQ, const uint64_t *X, const uint64_t *ctW,
+                            const uint64_t *mask, uint64_t *out)
 {
     CanonArgs ca{};
-    const bool centre = needs_centring(p, DQ);
-    fill_common_args(p, DX, mask, nullptr, out, &ca.e, centre ? 0 : 1);
+    fill_common_args(p, DX, mask, nullptr, out, &ca.e, needs_centring(p, DQ) ? 0 : 1);
     ca.X = X;
     ca.ctW = ctW;
     ca.k = p.k;
     ca.limbs = p.limbs;
+    return ca;
+}
+
+template <int DX, int DQ>
+static hipError_t canon_impl(const Problem &p, const uint64_t *X, const uint64_t *ctW,
+                             const uint64_t *mask, uint64_t *out, hipStream_t stream)
+{
+    const bool centre = needs_centring(p, DQ);
+    CanonArgs ca = canon_args(p, DX, DQ, X, ctW, mask, out);
     const dim3 grid((ca.e.CT / 2) * (uint32_t)ca.e.RB);
     const bool full = p.m % 128 == 0, shared = ca.e.RB > 1;
+    ca.e.block_tiles = (uint32_t)(((p.m + kTile - 1) / kTile + ca.e.RB - 1) / ca.e.RB);     // row blocks of even size
     auto go = [&](auto full_c, auto shared_c, auto centre_c) {
         return launch(cop_canon_kernel<DX, DQ, decltype(full_c)::value, decltype(shared_c)::value,
                                        decltype(centre_c)::value>,
@@ -441,8 +461,8 @@ hipError_t launch_cop_canon(const Problem &p, const uint64_t *X, const uint64_t 
     NIMBUS_CASE(3, 7)
     NIMBUS_CASE(4, 7)
     NIMBUS_CASE(2, 8)
-    NIMBUS_CASE(3, 8)
 #undef NIMBUS_CASE
+    if (DX == 3 && DQ == 8) return launch_cop_canon32(p, canon_args(p, DX, DQ, X, ctW, mask, out), stream);
     return hipErrorInvalidValue;
 }
 
