@@ -424,6 +424,11 @@ static ThinPlan thin_plan(const Problem &p, int count)
 // shares, 54-bit moduli: 16 x 32 x 4096 9.0 and 5.8, 32 x 32 x 131072 48.5 and 36.2, 32 x 128 x 49152
 // 28.9 and 22.1, 16 x 256 x 16384 11.7 and 10.9; 16 x 256 x 24576 13.5 and 18.5, 32 x 512 x 4096
 // 9.1 and 13.3, 32 x 1024 x 65536 84.8 and 94.3.)
+// The tiles' estimate of a short k is that of their kernel with 64-wide steps (3756 sizes of 8 to 32 rows;
+// there the choice is 0.02 % off the better kernel in three rounds and more, 6 % with the first estimate:
+// 8 x 64 x 131072, 32-bit shares, 40.5 us here and 25.4 there, 8 x 256 x 256 8.7 and 5.6).  Elsewhere the first
+// one is kept, which the sizes of the tests of this kernel's instances follow from (0.9 to 3 % off for
+// sixteen k-blocks and more, 7 % for fewer in two rounds of tiles).
 // A launch has fewer than 2^32 threads: 2^30 columns and more (240 GB of planes of one k-block) are
 // left to the tile kernel in any case; its workgroups walk the tiles.
 static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (1ull << 30); }
@@ -463,8 +468,11 @@ bool thin_applies(const Problem &p, int count)
     if (p.m > kThinRows) return thin_rows_apply(p, count);
     if (!thin_possible(p)) return false;
     const uint64_t cus = (uint64_t)compute_units();
-    const uint64_t rounds = (p.C / (2u * kTile) * (uint64_t)count + cus - 1) / cus;
-    return thin_plan(p, count).cost < 20u + rounds * (47u + 6u * (uint64_t)kblocks(p.k));
+    const uint64_t rounds = (p.C / (2u * kTile) * (uint64_t)count + cus - 1) / cus, KB = (uint64_t)kblocks(p.k);
+    const uint64_t products = (uint64_t)(planes_x(p.x_bits) * planes_q(p.q_bits_max));
+    const bool short_k = (rounds == 1 && KB <= 8) || (rounds >= 3 && KB < 16);
+    const uint64_t tiles = short_k ? 6u + rounds * (33u + KB * (400u + 23u * products) / 200u) : 20u + rounds * (47u + 6u * KB);
+    return thin_plan(p, count).cost < tiles;
 }
 
 // With a second 16-row tile the splitting takes as long as the staging launch (m = 32 on 768 x 16384:
