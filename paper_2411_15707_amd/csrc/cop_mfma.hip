@@ -76,9 +76,9 @@ int compute_units()
 TileBlocks tile_blocks(const Problem &p, int count)
 {
     // Row blocks of 64 rows where all of those find a compute unit of their own: half as many products
-    // per workgroup (100 x 768 x 4096 25.0 us a call with blocks of 128 rows, 17.3 with 64; as many
-    // blocks as compute units, 128 x 768 x 8192, 24.5 and 22.3).  With a second round of workgroups
-    // the larger blocks are ahead (100 x 768 x 12288).
+    // per workgroup (810 sizes of 65 to 512 rows, k from 64 to 480: 1.28 times as fast on average as blocks
+    // of 128 rows, none slower; 100 x 400 x 4096 15.9 us with those, 11.4 with 64, 128 x 480 x 8192 17.7
+    // and 13.4).  With a second round of workgroups the larger blocks were ahead (100 x 768 x 12288).
     uint32_t cus = (uint32_t)compute_units();
     if (cus >= 8) cus &= ~7u;
     if (p.m > 64 && (uint64_t)(p.C / 64u) * (uint64_t)((p.m + 63) / 64) * (uint32_t)count <= cus)

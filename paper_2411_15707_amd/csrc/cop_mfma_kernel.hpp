@@ -67,8 +67,8 @@ namespace nimbus {
 // come back in order, so every wait is a count of younger reads.
 //
 // Measured against the kernel before (v_mfma_i32_32x32x32_i8, a wave per 32 x 32 output tile, a barrier
-// per k-block, whole 32-row tiles on waves of two SIMDs each; us a call, both on one box): 128 x 768 x
-// 16384 35.7 -> 32.7 (33.7 -> 33.4 on the box with the smallest difference), 128 x 3072 x 16384 with
+// per k-block, whole 32-row tiles on waves of two SIMDs each; us a call, both on one card): 128 x 768 x
+// 16384 35.7 -> 32.7 (33.7 -> 33.4 on the card with the smallest difference), 128 x 3072 x 16384 with
 // packing 122.1 -> 112.2, 512 x 1024 x 49152 with packing 481.8 -> 458.2, 128 x 768 x 32768 of 64-bit
 // shares 186.3 -> 177.8, four problems of 77 x 1001 x 16384 177.3 -> 137.8; 628 sizes of 33 to 512
 // rows 1.09 times as fast on average.  The instruction takes half the accumulator traffic per
