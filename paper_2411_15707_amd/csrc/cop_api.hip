@@ -140,15 +140,6 @@ static bool prepared_path_supported(const Problem &p)
     return mfma_supported(half_problem(p, 32)) && mfma_supported(half_problem(p, p.x_bits - 32));
 }
 
-static hipError_t stage_all(const Problem &p, const uint64_t *X, void *workspace, hipStream_t stream)
-{
-    if (p.x_bits <= 32) return launch_stage_shares(p, X, 0, workspace, stream);
-    hipError_t e = launch_stage_shares(half_problem(p, 32), X, 0, workspace, stream);
-    if (e != hipSuccess) return e;
-    return launch_stage_shares(half_problem(p, p.x_bits - 32), X, 32,
-                               (char *)workspace + half_bytes(p.m, p.k, 32), stream);
-}
-
 // x = x_lo + 2^32 x_hi: the pass over the upper halves writes its reduced result to out,
 // the pass over the lower halves adds 2^32 times it (and the mask) and overwrites it
 static hipError_t matmul_all(const Problem &p, const void *staged, const void *prepared,
@@ -171,7 +162,7 @@ static hipError_t stage_and_matmul(const Problem &p, const uint64_t *X, void *wo
     const bool wide = p.x_bits > 32;
     const Problem lo = half_problem(p, wide ? 32 : p.x_bits), hi = half_problem(p, p.x_bits - 32);
     if (!thin_raw_applies(lo) || (wide && !thin_raw_applies(hi))) {
-        const hipError_t e = stage_all(p, X, workspace, stream);
+        const hipError_t e = launch_stage_shares(p, X, workspace, stream);
         return e == hipSuccess ? matmul_all(p, workspace, prepared, mask, out, stream) : e;
     }
     const void *const staged_lo = workspace;
@@ -322,7 +313,7 @@ int nimbus_cop_stage_shares(const uint64_t *X, int m, int k, int x_bits,
     p.m = m;
     p.k = k;
     p.x_bits = x_bits;
-    const hipError_t e = stage_all(p, X, workspace, (hipStream_t)stream);
+    const hipError_t e = launch_stage_shares(p, X, workspace, (hipStream_t)stream);
     return e == hipSuccess ? NIMBUS_COP_OK : NIMBUS_COP_ERR_LAUNCH;
 }
 
@@ -349,7 +340,7 @@ int nimbus_cop_stage_shares_batch(int count, const uint64_t *const *X, int m, in
     p.m = m;
     p.k = k;
     p.x_bits = x_bits;
-    const hipError_t e = launch_stage_shares_batch(p, count, X, 0, workspaces, (hipStream_t)stream);
+    const hipError_t e = launch_stage_shares_batch(p, count, X, workspaces, (hipStream_t)stream);
     return e == hipSuccess ? NIMBUS_COP_OK : NIMBUS_COP_ERR_LAUNCH;
 }
 
