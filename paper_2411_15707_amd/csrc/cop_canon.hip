@@ -315,7 +315,12 @@ __global__ __launch_bounds__(512, 1) void cop_canon_kernel(const CanonArgs ca)
                 }
             }
         }
+        // (the last stage has read operands ahead: nothing may copy or reuse their registers before they are back)
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        if constexpr (NT > 0) {
+            tie(xa[NG & 1]);
+            static_for<0, DQ>([&](auto d_c) { tie(xb[decltype(d_c)::value]); });
+        }
         __builtin_amdgcn_s_barrier();
         {
             const uint32_t at = lds0 + ((uint32_t)lane * 8u + (uint32_t)wave) * 16u;

@@ -511,9 +511,11 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             asm volatile("" ::: "memory");
         }
         for (; 2 * t + 1 < KB; ++t) step(t, std::false_type{});
-        // the last step has read operands of a step that does not exist; nothing may reuse those
+        // the last step has read operands of a step that does not exist; nothing may copy or reuse those
         // registers before the reads are back
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        static_for<0, AHEAD>([&](auto s_c) { tie(xa[decltype(s_c)::value]); });
+        static_for<0, DQ>([&](auto d_c) { tie(xb[decltype(d_c)::value]); });
         if constexpr (!MASKAHEAD)
             if (KB & 1) last_stage();
     } else {
