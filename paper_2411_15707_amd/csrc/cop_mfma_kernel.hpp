@@ -117,19 +117,19 @@ struct Pipe {
 // fewer and the row tests around the loads and stores of the epilogue (a compare, an exec
 // update and a branch each) are left out.
 //
-// MASKAHEAD: the wave's mask words are asked for two steps before the end of the loop, when no
-// stage is left to ask for, into registers that the operands leave free, instead of when the
-// loop is over: the 16 B per output that mask and result move would otherwise all fall into
-// the last microseconds of the launch, where they are the only traffic and every workgroup
-// asks at once.  Needs a mask, m a multiple of 128, at most nine accumulators per output and
-// an even number of k-blocks (the last stage of an odd one has more operands at hand), at least
-// kMaskMinKB.
+// The wave's mask words are asked for when the loop has no stage left to ask for, or one, about two steps
+// before its end, into registers that the operands leave free, instead of when the loop is over:
+// the 16 B per output that mask and result move would otherwise all fall into the last microseconds of
+// a tile, where they are the only traffic and every workgroup asks at once.  MASKAHEAD: in the instances
+// without row tests, given a mask and at most nine accumulators per output.  With row tests it is
+// decided at run time, where the registers hold them: at most nine accumulators, or three 16-row tiles.
+// Before, only without row tests and for 14 k-blocks and more of an even number (us, 20-bit shares, 54-bit
+// moduli: 64 x 125 x 32768 19.2 -> 17.0, 256 x 95 x 98304 119.0 -> 109.1, 512 x 190 x 16384 51.7 -> 43.4, 400 x
+// 160 x 98304, 16-bit shares, 222.8 -> 209.4; 1000 sizes of up to 415 k 5 % faster on average).
 //
 // SHARED: the launch has several row blocks per column tile (m > 128).  They run on one XCD
 // at the same time, start at the same k-block and load without the streaming hint, so the
 // ciphertext tile comes over the fabric once and the other row blocks find it in the L2.
-constexpr int kMaskMinKB = 13;
-
 template <int DX, int DQ, bool FULL, bool MASKAHEAD, bool SHARED, int NB>
 __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, const BatchPtrs<NB> b)
 {
@@ -397,12 +397,43 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     }
-    uint64_t mk[MASKAHEAD ? 16 : 4 * NA];           // MASKAHEAD: the lane's mask words
+    // the lane's mask words, where they are asked for ahead: MASKAHEAD, and with row tests where the
+    // registers hold them
+    constexpr bool MASKREGS = MASKAHEAD || (!FULL && NT > 0 && (ND <= 9 || NT < 4));
+    uint64_t mk[4 * NA];
+    // (128 rows of the mask in one descriptor)
+    const bool ahead = MASKAHEAD || (MASKREGS && mask_p != nullptr && a.C < (1u << 22));
+    if constexpr (MASKREGS && !MASKAHEAD) {
+#pragma unroll
+        for (int r = 0; r < 4 * NT; ++r) mk[r] = 0;
+    }
     const uint32_t col = ct2 * 64u + (uint32_t)wc * 16u + (uint32_t)(lane & 15);
     const int row0 = row_first + 16 * wh + 4 * (lane >> 4);
     auto roff = [](int r) -> int { return 32 * (r >> 2) + (r & 3); };
 
-    int mask_step = -1;                             // MASKAHEAD: the step the mask words were asked for in front of
+    // the step in front of which they were asked for; its wait need not cover them where every stage that
+    // it needs is older (where the shares are less far ahead than the ciphertext some are asked for in it)
+    int mask_step = -1;
+    constexpr int MASKLOADS = MASKREGS && P_::LEAD_A == P_::LEAD_B ? 4 * NT : 0;
+    auto ask_mask = [&]() {
+        if constexpr (MASKAHEAD) {
+            const uint64_t *const mask0 = mask_p + ((size_t)row0 * a.C + col);
+#pragma unroll
+            for (int r = 0; r < 4 * NT; ++r) mk[r] = __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C]);
+        } else if constexpr (MASKREGS) {
+            // (a load for every row, there or not: the wait of the step counts them)
+            const __amdgpu_buffer_rsrc_t rsrc_m = __builtin_amdgcn_make_buffer_rsrc(
+                (void *)(mask_p + (size_t)row_first * a.C), 0, (uint32_t)(row_end - row_first) * a.C * 8u, 0x00027000);
+            uint32_t at = ((uint32_t)(row0 - row_first) * a.C + col) * 8u;
+#pragma unroll
+            for (int r = 0; r < 4 * NT; ++r) {
+                mk[r] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc_m, at, 0, 2));
+                at += (r % 4 == 3 ? 29u : 1u) * 8u * a.C;
+                asm volatile("" : "+v"(at));
+            }
+        }
+        asm volatile("" ::: "memory");
+    };
 
     // Step t.  STEADY: every stage up to 2t + LEAD_B + 1 exists.
     auto step = [&](int t, auto steady_c) {
@@ -424,7 +455,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
                 // every operand of this step is in registers but the ciphertext's last group reads on
                 asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
                 if constexpr (STEADY) wait_steady();
-                else wait_vmem_n(younger(t) + (MASKAHEAD && younger(t) < 63 - 16 && t == mask_step ? 16 : 0));
+                else wait_vmem_n(younger(t) + (MASKLOADS && younger(t) < 63 - 16 && t == mask_step ? MASKLOADS : 0));
                 __builtin_amdgcn_s_barrier();
                 asm volatile("" ::: "memory");
                 next_read();
@@ -459,24 +490,23 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
     // before, two products of one diagonal: lanes 0-31 hold the planes dx and d, lanes 32-63 dx + 1
     // and d - 1 (none for d = 0, for lanes 0-31 none for d = DQ, and none beyond the last share plane).
     // 15 products instead of 21 for <3, 7>, 16 instead of 28 for <4, 7>.
-    // Nothing is read ahead of it, and its reads end behind the last barrier: the next tile's
-    // loads wait for one more.
+    // (What the upper lanes find in front of the first ciphertext plane and behind the last share
+    // plane is some other operand tile, and set to zero.)  Nothing is read ahead of it, and its reads
+    // end behind the last barrier: the next tile's loads wait for one more.
     auto last_stage = [&]() {
         constexpr int NP = (DX + 1) / 2;            // pairs of share planes
-        const uint32_t slotA = __builtin_amdgcn_readfirstlane(rdA), slotB = __builtin_amdgcn_readfirstlane(rdB);
-        const uint32_t upper = (uint32_t)lane >> 5;
-        const uint32_t atA = laneA + slotA, atB = laneB + slotB;
+        int lane_l = lane;                          // (opaque: see the epilogue)
+        asm volatile("" : "+v"(lane_l));
+        const uint32_t upper = (uint32_t)lane_l >> 5;
         const int lower_only = upper ? 0 : -1;
-        v4i yb[DQ + 1], ya[2];
-        yb[0] = lds_read_b128<0>(atB);
-        static_for<1, DQ>([&](auto d_c) {
-            yb[decltype(d_c)::value] = lds_read_b128<decltype(d_c)::value * kTileBytes>(atB - upper * kTileBytes);
-        });
-        yb[DQ] = lds_read_b128<(DQ - 1) * kTileBytes>(atB);
-        auto read_pair = [&](auto n_c) {            // pair n % NP of 16-row tile n / NP
-            constexpr int n = decltype(n_c)::value, at = (n / NP * DX + n % NP * 2) * kTileBytes;
-            constexpr bool two = n % NP * 2 + 1 < DX;
-            ya[n & 1] = lds_read_b128<at>(two ? atA + upper * kTileBytes : atA);
+        rdA = __builtin_amdgcn_readfirstlane(rdA) + upper * kTileBytes;
+        rdB = __builtin_amdgcn_readfirstlane(rdB);
+        v4i xe = lds_read_b128<(DQ - 1) * kTileBytes>(laneB + rdB);
+        rdB -= upper * kTileBytes;
+        static_for<0, DQ>([&](auto d_c) { read_b(d_c); });
+        auto read_pair = [&](auto n_c) {            // pair n % NP of 16-row tile n / NP, into operand set n % 2
+            constexpr int n = decltype(n_c)::value;
+            read_a(std::integral_constant<int, n / NP * DX + n % NP * 2>{}, std::integral_constant<int, n & 1>{});
         };
         read_pair(std::integral_constant<int, 0>{});
         static_for<0, NT * NP>([&](auto n_c) {
@@ -484,31 +514,32 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             constexpr bool two = dx + 1 < DX;
             if constexpr (n + 1 < NT * NP) read_pair(std::integral_constant<int, n + 1>{});
             if constexpr (n == 0) {
-                static_for<0, DQ + 1>([&](auto d_c) { wait_lds<(NT * NP > 1)>(yb[decltype(d_c)::value]); });
-                yb[0] &= lower_only;
-                yb[DQ] &= ~lower_only;
+                wait_lds<(NT * NP > 1)>(xe);
+                static_for<0, DQ>([&](auto d_c) { tie(xb[decltype(d_c)::value]); });
+                xb[0] &= lower_only;
+                xe &= ~lower_only;
             }
-            wait_lds<(n + 1 < NT * NP)>(ya[n & 1]);
-            if constexpr (!two) ya[n & 1] &= lower_only;
-            static_for<0, two ? DQ + 1 : DQ>([&](auto d_c) {
-                constexpr int d = decltype(d_c)::value;
-                acc[dx + d][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(ya[n & 1], yb[d], acc[dx + d][i], 0, 0, 0);
-            });
-            tie(ya[n & 1]);
+            wait_lds<(n + 1 < NT * NP)>(xa[n & 1]);
+            if constexpr (!two) xa[n & 1] &= lower_only;
+            auto product = [&](int d, v4i &y) {
+                tie(y);
+                acc[dx + d][i] = __builtin_amdgcn_mfma_i32_16x16x64_i8(xa[n & 1], y, acc[dx + d][i], 0, 0, 0);
+                tie(acc[dx + d][i]);
+            };
+#pragma unroll
+            for (int d = 0; d < DQ; ++d) product(d, xb[d]);
+            if constexpr (two) product(DQ, xe);
+            tie(xa[n & 1]);
         });
-        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
     };
     if constexpr (NT > 0) {
         static_for<0, AHEAD>([&](auto g_c) { read_a(g_c, g_c); });
         static_for<0, DQ>([&](auto d_c) { read_b(d_c); });
         int t = 0;
         for (; 2 * t + P_::LEAD_B + 1 < KB; ++t) step(t, std::true_type{});
-        if constexpr (MASKAHEAD) {
+        if (ahead) {
             mask_step = t;
-            const uint64_t *const mask0 = mask_p + ((size_t)row0 * a.C + col);
-#pragma unroll
-            for (int r = 0; r < 16; ++r) mk[r] = __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C]);
-            asm volatile("" ::: "memory");
+            ask_mask();
         }
         for (; 2 * t + 1 < KB; ++t) step(t, std::false_type{});
         // the last step has read operands of a step that does not exist; nothing may copy or reuse those
@@ -516,8 +547,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         static_for<0, AHEAD>([&](auto s_c) { tie(xa[decltype(s_c)::value]); });
         static_for<0, DQ>([&](auto d_c) { tie(xb[decltype(d_c)::value]); });
-        if constexpr (!MASKAHEAD)
-            if (KB & 1) last_stage();
+        if (KB & 1) last_stage();
     } else {
         for (int t = 0; 2 * t + 1 < KB; ++t) {
             static_for<0, 2>([&](auto h_c) {
@@ -533,7 +563,7 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
         }
     }
     const bool more = tile + gridDim.x < a.tiles;
-    if (!MASKAHEAD && (KB & 1) && more) {                         // (the last stage's reads: see last_stage)
+    if ((KB & 1) && more) {                         // (the last stage's reads: see last_stage)
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
     }
@@ -567,10 +597,10 @@ __global__ __launch_bounds__(512, 1) void cop_mfma_kernel(const MfmaArgs a, cons
             [&](uint64_t (&w)[NE]) {
 #pragma unroll
                 for (int r = 0; r < NE; ++r) {
-                    if constexpr (MASKAHEAD) w[r] = mk[r];
+                    if constexpr (MASKREGS) w[r] = mk[r];
                     else w[r] = 0;
                 }
-                if (MASKAHEAD || !mask_p) return;
+                if (ahead || !mask_p) return;
                 const uint64_t *const mask0 = mask_p + ((size_t)row_e * a.C + col_e);
 #pragma unroll
                 for (int r = 0; r < NE; ++r)
@@ -624,9 +654,9 @@ hipError_t mfma_impl(const Problem &p, int count, const void *const *staged,
     const dim3 grid(a.tiles < cus ? a.tiles : cus);
     using P_ = Pipe<DX, DQ>;
     constexpr bool kCanMaskAhead = P_::ND <= 9;
-    // mask words ahead: see the kernel
-    const bool mask_ahead = kCanMaskAhead && mask != nullptr && p.m % 128 == 0 && a.block_tiles == 4 && KB >= kMaskMinKB && KB % 2 == 0;
     const bool full = p.m % 128 == 0 && a.block_tiles == 4;
+    // mask words ahead: see the kernel
+    const bool mask_ahead = kCanMaskAhead && mask != nullptr && full;
     auto launch_with = [&](auto full_c, auto maskahead_c, auto shared_c, auto nb_c) {
         constexpr int NB = decltype(nb_c)::value;
         BatchPtrs<NB> b{};

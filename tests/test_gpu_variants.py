@@ -10,15 +10,17 @@ pytestmark = pytest.mark.gpu
 
 # share and ciphertext planes: the widths that give them
 PLANES = {(2, 7): (16, 50), (3, 7): (20, 54), (4, 7): (32, 54), (2, 8): (16, 62), (3, 8): (24, 62), (4, 8): (32, 62)}
-MASK_IN_LDS = [(2, 7), (3, 7), (2, 8)]          # where the mask tile fits next to two operand sets
-# rows, columns of one problem and of each of two, inner dimension, mask; (no row tests, mask tile in LDS,
+MASK_AHEAD = [(2, 7), (3, 7), (2, 8)]           # nine accumulators at most: the mask words fit next to them
+# rows, columns of one problem and of each of two, inner dimension, mask; (no row tests, mask words ahead,
 # several row blocks) and rows of a block.  More than 256 blocks of 64 rows, but for the last form.
 FORMS = {
-    "full": (128, 8320, 4224, 70, True, (True, False, False), 128),
+    "full": (128, 8320, 4224, 70, True, (True, True, False), 128),
     "full, no mask": (128, 8320, 4224, 417, False, (True, False, False), 128),
-    "full, mask in LDS": (128, 8320, 4224, 417, True, (True, True, False), 128),
-    "two full blocks": (256, 4224, 2176, 70, True, (True, False, True), 128),
-    "two full blocks, mask in LDS": (256, 4224, 2176, 448, True, (True, True, True), 128),
+    "full, long": (128, 8320, 4224, 417, True, (True, True, False), 128),
+    "full, long, odd": (128, 8320, 4224, 450, True, (True, True, False), 128),
+    "two full blocks": (256, 4224, 2176, 70, True, (True, True, True), 128),
+    "two full blocks, no mask": (256, 4224, 2176, 70, False, (True, False, True), 128),
+    "two full blocks, long": (256, 4224, 2176, 448, True, (True, True, True), 128),
     "rows": (40, 256, 256, 100, True, (False, False, False), 128),
     "rows, two blocks": (130, 5504, 2816, 100, True, (False, False, True), 128),
     "blocks of 64": (128, 1024, 1024, 450, True, (False, False, True), 64),
@@ -34,15 +36,15 @@ def test_every_instance_of_the_tile_kernel(oracle, form, planes, problems):
     m, alone, each, k, masked, flags, block = FORMS[form]
     C = alone if problems == 1 else each
     x_bits, q_bits = PLANES[planes]
-    full, in_lds, shared = flags
-    in_lds = in_lds and planes in MASK_IN_LDS
+    full, ahead, shared = flags
+    ahead = ahead and planes in MASK_AHEAD
     N, L = 64, 1
     n = C // (2 * N) * N
     moduli = ci.limb_primes(q_bits, 14, L)
     route = nc.nimbus_route_matmul(m, k, x_bits, n, N, L, moduli, masked=masked, staged=True, count=problems)
     flag = lambda b: "true" if b else "false"
     tiles = C // 64 * -(-m // block) * problems
-    assert route == [f"cop_mfma_kernel<{planes[0]}, {planes[1]}, {flag(full)}, {flag(in_lds)}, {flag(shared)}, "
+    assert route == [f"cop_mfma_kernel<{planes[0]}, {planes[1]}, {flag(full)}, {flag(ahead)}, {flag(shared)}, "
                      f"{1 if problems == 1 else 16}> grid={min(tiles, 256)},1 block=512"]
     print(f"[variants] {form} x {problems}: {route[0]}", flush=True)
     staged, prepared, masks, outs, wants = [], [], [], [], []
