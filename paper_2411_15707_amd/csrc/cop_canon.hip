@@ -20,10 +20,11 @@
 // the partial sums meet in LDS after the loop.
 //
 // What bounds it: the conversion's vector instructions (about 124 per thread and stage) next to
-// the products.  Against the kernel before (cop_canon32.hip: 32 k a stage, raw words through LDS,
-// 4-byte writes; still the faster one with three share and eight ciphertext planes): 128 x 768 x 16384,
-// 20-bit shares, 46.9 us -> 41.8; half as many LDS writes and barriers, no words through LDS on the
-// way in, and few rows pay for their own 16-row tiles only (1 x 768 x 16384 1.4 times as fast).
+// the products; with few stages the fetch of code that runs once (asking for the second stage's words
+// together with the first's changes nothing).  Against the kernel of cop_canon32.hip (32 k a stage, raw words
+// through LDS, 4-byte writes): 128 x 768 x 16384, 20-bit shares, 46.9 us -> 41.8; half as many LDS writes
+// and barriers, no words through LDS on the way in, and few rows pay for their own 16-row tiles only (1 x
+// 768 x 16384 1.4 times as fast).  Where that kernel is the faster one it runs: stages_of_32().
 #include "cop_canon.hpp"
 
 namespace nimbus {
@@ -430,6 +431,26 @@ static CanonArgs canon_args(const Problem &p, int DX, int DQ, const uint64_t *X,
     return ca;
 }
 
+// Which kernel: that of cop_canon32.hip (32 k a stage) or this one (us, there and here).
+//   three share and eight ciphertext planes: there (20-bit shares, moduli of 62 bits, 128 x 768 x 16384 50.3
+//       and 54.4, 100 x 1500 x 8192 78.8 and 97.3: the accumulators leave too few registers here);
+//   four share planes and centred digits, m a multiple of 128: there (32-bit shares, moduli just below
+//       2^55, 128 x 160 x 8192 17.5 and 20.1, 128 x 928 x 2048 54.5 and 58.9; 512 x 416 x 8192 even, 256 x
+//       1504 x 4096 here by 1 %: this kernel spills four registers);
+//   more than 96 rows in a row block and three or five k-blocks, without row tests one or seven too:
+//       there (20-bit shares, 128 x 95 x 8192 13.6 and 15.3, 128 x 160 x 8192 16.1 and 17.2): the last stage is
+//       half empty, and a second one costs the fetch of the whole loop's code;
+//   else here (128 x 60 x 8192 11.9 and 11.0, 300 x 220 x 8192 35.4 and 34.0, 70 x 95 x 8192 13.0 and 11.9).
+// Over 2559 sizes of 40 to 512 rows the choice is 0.4 % off the better one on average and 10 % at worst (191
+// x 1502 x 4096, 32-bit shares, centred); this kernel everywhere would be 1.2 % and 16 % off.
+static bool stages_of_32(const Problem &p, int DX, int DQ, bool centre, int block_rows)
+{
+    const int KB = kblocks(p.k);
+    if (DX == 3 && DQ == 8) return true;
+    if (DX == 4 && centre && p.m % 128 == 0) return true;
+    return block_rows > 96 && KB % 2 == 1 && (p.m % 128 == 0 ? KB <= 7 : KB <= 5);
+}
+
 template <int DX, int DQ>
 static hipError_t canon_impl(const Problem &p, const uint64_t *X, const uint64_t *ctW,
                              const uint64_t *mask, uint64_t *out, hipStream_t stream)
@@ -439,21 +460,29 @@ static hipError_t canon_impl(const Problem &p, const uint64_t *X, const uint64_t
     const dim3 grid((ca.e.CT / 2) * (uint32_t)ca.e.RB);
     const bool full = p.m % 128 == 0, shared = ca.e.RB > 1;
     ca.e.block_tiles = (uint32_t)(((p.m + kTile - 1) / kTile + ca.e.RB - 1) / ca.e.RB);     // row blocks of even size
-    auto go = [&](auto full_c, auto shared_c, auto centre_c) {
-        return launch(cop_canon_kernel<DX, DQ, decltype(full_c)::value, decltype(shared_c)::value,
-                                       decltype(centre_c)::value>,
-                      grid, dim3(512), stream, ca);
-    };
-    using T = std::true_type;
-    using F = std::false_type;
-    if constexpr (DQ == 7) {                        // (eight digits express every q < 2^62)
-        if (centre) {
-            if (full) return shared ? go(T{}, T{}, T{}) : go(T{}, F{}, T{});
-            return shared ? go(F{}, T{}, T{}) : go(F{}, F{}, T{});
+    const int block_rows = (int)ca.e.block_tiles * kTile < p.m ? (int)ca.e.block_tiles * kTile : p.m;
+    if (stages_of_32(p, DX, DQ, centre, block_rows)) return launch_cop_canon32<DX, DQ>(p, ca, centre, stream);
+    if constexpr (DX == 3 && DQ == 8) {
+        return hipErrorInvalidValue;
+    } else {
+        auto go = [&](auto full_c, auto shared_c, auto centre_c) {
+            return launch(cop_canon_kernel<DX, DQ, decltype(full_c)::value, decltype(shared_c)::value,
+                                           decltype(centre_c)::value>,
+                          grid, dim3(512), stream, ca);
+        };
+        using T = std::true_type;
+        using F = std::false_type;
+        if constexpr (DX == 4) {                    // (centred and without row tests: cop_canon32.hip)
+            if (centre) return shared ? go(F{}, T{}, T{}) : go(F{}, F{}, T{});
+        } else if constexpr (DQ == 7) {             // (eight digits express every q < 2^62)
+            if (centre) {
+                if (full) return shared ? go(T{}, T{}, T{}) : go(T{}, F{}, T{});
+                return shared ? go(F{}, T{}, T{}) : go(F{}, F{}, T{});
+            }
         }
+        if (full) return shared ? go(T{}, T{}, F{}) : go(T{}, F{}, F{});
+        return shared ? go(F{}, T{}, F{}) : go(F{}, F{}, F{});
     }
-    if (full) return shared ? go(T{}, T{}, F{}) : go(T{}, F{}, F{});
-    return shared ? go(F{}, T{}, F{}) : go(F{}, F{}, F{});
 }
 
 hipError_t launch_cop_canon(const Problem &p, const uint64_t *X, const uint64_t *ctW,
@@ -466,8 +495,8 @@ hipError_t launch_cop_canon(const Problem &p, const uint64_t *X, const uint64_t 
     NIMBUS_CASE(3, 7)
     NIMBUS_CASE(4, 7)
     NIMBUS_CASE(2, 8)
+    NIMBUS_CASE(3, 8)
 #undef NIMBUS_CASE
-    if (DX == 3 && DQ == 8) return launch_cop_canon32(p, canon_args(p, DX, DQ, X, ctW, mask, out), stream);
     return hipErrorInvalidValue;
 }
 

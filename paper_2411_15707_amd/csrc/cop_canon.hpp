@@ -12,7 +12,8 @@ struct CanonArgs {
     LimbTable limbs;          // reduction of the column sums
 };
 
-// three share planes and eight ciphertext planes (cop_canon32.hip)
-hipError_t launch_cop_canon32(const Problem &p, const CanonArgs &ca, hipStream_t stream);
+// the kernel with 32 k a stage (cop_canon32.hip)
+template <int DX, int DQ>
+hipError_t launch_cop_canon32(const Problem &p, const CanonArgs &ca, bool centre, hipStream_t stream);
 
 }  // namespace nimbus

@@ -1,8 +1,7 @@
 // Matrix-core (int8 MFMA) kernel for the COP accumulation on the CANONICAL layout, gfx950, 32 k a stage:
-// nimbus_cop_matmul without any setup pass, for three share planes and eight ciphertext planes, where
-// the kernel of cop_canon.hip does not fit its registers (20-bit shares, moduli of 62 bits, 128 x 768 x
-// 16384: 50.3 us here, 54.4 there; 100 x 1500 x 8192 78.8 and 97.3).  Same contraction and same epilogue as the kernel
-// for prepared weights (cop_mfma_kernel.hpp; Algorithm 1 step 2 + step 4 of the paper), but both
+// nimbus_cop_matmul without any setup pass, where the kernel of cop_canon.hip, with its 64 k a stage, is
+// the slower one (stages_of_32() there has the rule and both sides).  Same contraction and same epilogue as the
+// kernel for prepared weights (cop_mfma_kernel.hpp; Algorithm 1 step 2 + step 4 of the paper), but both
 // operands arrive as 64-bit words and are split into signed byte planes inside the loop:
 //
 //   ciphertext words  ctW[k][C]: a 32 x 64 tile per k-block (16 KB) comes into a ring of raw
@@ -368,19 +367,32 @@ __global__ __launch_bounds__(512, 1) void cop_canon32_kernel(const CanonArgs ca)
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
-hipError_t launch_cop_canon32(const Problem &p, const CanonArgs &ca, hipStream_t stream)
+template <int DX, int DQ>
+hipError_t launch_cop_canon32(const Problem &p, const CanonArgs &ca, bool centre, hipStream_t stream)
 {
-    // (eight digits express every q < 2^62: no centring)
     const dim3 grid((ca.e.CT / 2) * (uint32_t)ca.e.RB);
     const bool full = p.m % 128 == 0, shared = ca.e.RB > 1;
-    auto go = [&](auto full_c, auto shared_c) {
-        return launch(cop_canon32_kernel<3, 8, decltype(full_c)::value, decltype(shared_c)::value, false>, grid,
-                      dim3(512), stream, ca);
+    auto go = [&](auto full_c, auto shared_c, auto centre_c) {
+        return launch(cop_canon32_kernel<DX, DQ, decltype(full_c)::value, decltype(shared_c)::value,
+                                         decltype(centre_c)::value>,
+                      grid, dim3(512), stream, ca);
     };
     using T = std::true_type;
     using F = std::false_type;
-    if (full) return shared ? go(T{}, T{}) : go(T{}, F{});
-    return shared ? go(F{}, T{}) : go(F{}, F{});
+    if constexpr (DQ == 7) {                        // (eight digits express every q < 2^62)
+        if (centre) {
+            if (full) return shared ? go(T{}, T{}, T{}) : go(T{}, F{}, T{});
+            return shared ? go(F{}, T{}, T{}) : go(F{}, F{}, T{});
+        }
+    }
+    if (full) return shared ? go(T{}, T{}, F{}) : go(T{}, F{}, F{});
+    return shared ? go(F{}, T{}, F{}) : go(F{}, F{}, F{});
 }
+
+template hipError_t launch_cop_canon32<2, 7>(const Problem &, const CanonArgs &, bool, hipStream_t);
+template hipError_t launch_cop_canon32<3, 7>(const Problem &, const CanonArgs &, bool, hipStream_t);
+template hipError_t launch_cop_canon32<4, 7>(const Problem &, const CanonArgs &, bool, hipStream_t);
+template hipError_t launch_cop_canon32<2, 8>(const Problem &, const CanonArgs &, bool, hipStream_t);
+template hipError_t launch_cop_canon32<3, 8>(const Problem &, const CanonArgs &, bool, hipStream_t);
 
 }  // namespace nimbus
