@@ -376,7 +376,7 @@ struct ThinPlan {
     uint64_t rounds;        // of workgroups on the compute units
     uint64_t stages;        // of a slice, and those rounded up to whole rounds of the stages in flight
     uint64_t padded;
-    uint64_t cost;          // tenths of a microsecond (up to 32 rows)
+    uint64_t depth;         // stages in flight of a wave
 };
 
 // (more than 32 rows: every 32-row tile by itself)
@@ -407,72 +407,74 @@ static ThinPlan thin_plan(const Problem &p, int count)
     plan.copied = p.m > 16 && p.m <= kThinRows && plan.log_ks == 0 && thin_planes_fit(p);
     // (whole rounds of the stages in flight: what is past the last one costs its products, but no loads)
     plan.stages = (S + (1u << plan.log_ks) - 1) >> plan.log_ks;
-    const uint64_t depth = (uint64_t)thin_depth(planes_x(p.x_bits), planes_q(p.q_bits_max), p.m <= 16 ? 1 : 2,
-                                                plan.copied ? kCopied : kDirect);
-    plan.padded = (plan.stages + depth - 1) / depth * depth;
-    plan.cost = plan.rounds * ((p.m <= 16 ? 63u : plan.copied ? 107u : 80u) + 9u * (plan.stages + plan.padded)) +
-                13u * plan.blocks * launches / cus;
+    plan.depth = (uint64_t)thin_depth(planes_x(p.x_bits), planes_q(p.q_bits_max), p.m <= 16 ? 1 : 2,
+                                      plan.copied ? kCopied : kDirect);
+    plan.padded = (plan.stages + plan.depth - 1) / plan.depth * plan.depth;
     return plan;
 }
 
-// From staged shares: where this kernel's rounds take less than those of the tile kernel, which starts
-// and ends a workgroup faster but shares the chip's tiles out by whole rounds and has no slices of k.
-// Both estimates in tenths of a microsecond, fitted to 5461 sizes on 256 compute units (1 to 32 rows,
-// k from 32 to 3072, 256 to 131072 columns, every plane count, one to sixteen problems): the
-// kernel that they choose is 0.2 % slower than the better of the two on average; this one
-// everywhere 9 %, the tile kernel everywhere 20 %.  (us, this kernel and the tiles, 20-bit
-// shares, 54-bit moduli: 16 x 32 x 4096 9.0 and 5.8, 32 x 32 x 131072 48.5 and 36.2, 32 x 128 x 49152
-// 28.9 and 22.1, 16 x 256 x 16384 11.7 and 10.9; 16 x 256 x 24576 13.5 and 18.5, 32 x 512 x 4096
-// 9.1 and 13.3, 32 x 1024 x 65536 84.8 and 94.3.)
-// The tiles' estimate of a short k is that of their kernel with 64-wide steps (3756 sizes of 8 to 32 rows;
-// there the choice is 0.02 % off the better kernel in three rounds and more, 6 % with the first estimate:
-// 8 x 64 x 131072, 32-bit shares, 40.5 us here and 25.4 there, 8 x 256 x 256 8.7 and 5.6).  Elsewhere the first
-// one is kept, which the sizes of the tests of this kernel's instances follow from (0.9 to 3 % off for
-// sixteen k-blocks and more, 7 % for fewer in two rounds of tiles).
 // A launch has fewer than 2^32 threads: 2^30 columns and more (240 GB of planes of one k-block) are
 // left to the tile kernel in any case; its workgroups walk the tiles.
 static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (1ull << 30); }
 
+// From staged shares: where this kernel's rounds take less than those of the tile kernel, which starts
+// and ends a workgroup faster but shares the chip's tiles out by whole rounds and has no slices of k.
+// Both estimates in hundredths of a microsecond, on 256 compute units: per round its start and end, per
+// k-block or stage the wait for its operands and its products, and the bytes of weights, mask and
+// results.  Fitted to both kernels' times at 3600 drawn sizes (1 to 32 rows, k from 20 to 3072, 64 to 131072
+// columns, every pair of plane counts, one to sixteen problems; profiles/choice_of_kernel.txt): the choice is 0.2 % slower
+// than the better kernel on average, and no more at 900 sizes that were left out; this kernel everywhere 39 %, the tile
+// kernel everywhere 8 %.  (us, this kernel and the tiles, 20-bit shares, 54-bit moduli where nothing else is
+// said: 12 x 28 x 24576, 32-bit shares, 11.1 and 7.3, 8 x 1006 x 16384 three times 63.8 and 57.3; 16 x 510 x
+// 8192 12.0 and 10.0; 32 x 2032 x 16384 twice, 32-bit shares, 62-bit moduli, 98.1 and 134.0.)
+static bool thin_few_apply(const Problem &p, int count)
+{
+    if (!thin_possible(p)) return false;
+    const ThinPlan plan = thin_plan(p, count);
+    const uint64_t cus = (uint64_t)compute_units();
+    const double KB = kblocks(p.k), n = (double)count, tile_rounds = (double)((p.C / 64u * (uint64_t)count + cus - 1) / cus);
+    const double products = planes_x(p.x_bits) * planes_q(p.q_bits_max);
+    const double weights = n * (double)p.C * KB * planes_q(p.q_bits_max), results = n * (double)p.m * (double)p.C;
+    const double start = p.m <= 16 ? 700 : plan.copied ? 822 : 733, padded = (double)plan.padded;
+    const double tiles = 317 + tile_rounds * (140 + KB * (9.5 + 0.98 * products)) + 2.3e-4 * weights + 2.2e-4 * results;
+    const double rows = (double)plan.rounds * (start + 33. * (double)plan.stages + 1.52 * products * (p.m <= 16 ? 1 : 2) * padded +
+                                               35. * padded / (double)plan.depth) +
+                        2.44e-4 * weights + 1e-4 * results;
+    return rows < tiles;
+}
+
 // More than 32 rows on few columns: where the tile kernel's workgroups leave compute units without a
 // tile, this kernel's row tiles and slices of k fill them (us, tiles and this kernel, 20-bit shares
-// and 54-bit moduli: 128 x 3072 x 1024 43.0 and 13.3, 128 x 1536 x 2048 24.8 and 13.1, 200 x 512 x 256
-// 11.9 and 6.9).  Every row tile reads the
-// weights again, from the L2, so the line is where the chip fills up (64 x 768 x 8192 16.3 and 18.5).
-// Both estimates in hundredths of a microsecond, fitted to 1360 sizes (33 to 512 rows, k from 512 to
-// 3072, 256 to 16384 columns, four pairs of plane counts) on 256 compute units: per round of workgroups
-// its start and end, per k-block or stage the wait for its operands and its products, and the bytes of
-// weights, mask and results.  With six per cent between them the choice is 0.2 % slower than the
-// better kernel on average and 7 % slower than the tiles at worst (96 x 3072 x 4096, 16-bit shares);
-// tiles everywhere would be 28 % slower.  Fewer k-blocks than sixteen, two for each of eight slices,
-// stay with the tiles.
+// and 54-bit moduli: 128 x 3072 x 1024 43.0 and 13.3, 128 x 1536 x 2048 24.8 and 13.1, 69 x 478 x 1024
+// 11.6 and 8.4).  Every row tile reads the weights again, from the L2, so the line is where the chip
+// fills up (64 x 768 x 8192 16.3 and 18.5); with fewer than eight workgroups to a problem and row tile the
+// row tiles are spread over the XCDs, and of a batch each fetches them (197 x 3330 x 256 eight times,
+// 16-bit shares, 40.2 and 57.3): a seventh more.
+// Estimates as above, fitted at 2000 sizes (33 to 512 rows, k from 300 to 4096, 64 to 16384 columns, one to
+// eight problems): the choice is 0.2 % slower than the better kernel on average and 27 % at worst (238 x 2547
+// x 256 eight times, 16-bit shares), no more than that on average at 500 sizes that were left out; tiles everywhere 34 %, this
+// kernel everywhere 23 %.  Fewer k-blocks than ten were not looked at and stay with the tiles.
 static bool thin_rows_apply(const Problem &p, int count)
 {
     const int KB = kblocks(p.k), DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);
     const TileBlocks tb = tile_blocks(p, count);
     const double cus = (double)compute_units(), n = (double)count;
-    if (KB < 16 || (double)(p.C / 64u) * tb.row_blocks * n > cus) return false;
+    if (KB < 10 || (double)(p.C / 64u) * tb.row_blocks * n > cus) return false;
     const ThinPlan plan = thin_plan(p, count);
     const int row_tiles = (p.m + kThinRows - 1) / kThinRows;
     if (plan.rounds > 2 || (uint64_t)plan.blocks * (uint64_t)row_tiles * 512u >= (1ull << 32)) return false;
     const int rows16 = ((tb.tiles * kTile < p.m ? tb.tiles * kTile : p.m) + 15) / 16;
     const double weights = n * (double)p.C * KB * DQ, results = n * (double)p.m * (double)p.C;
     const double products = DX * DQ, rounds = (double)plan.rounds;
-    const double tiles = 476 + KB * (10 + 0.66 * products * ((rows16 + 1) / 2)) + 1.5e-4 * weights + 2.8e-4 * results;
-    const double rows = rounds * (584 + 24. * (double)plan.stages + 3.5 * products * (double)plan.padded) +
-                        (3.7e-4 + 1.3e-5 * row_tiles) * weights + 1.5e-4 * results;
-    return 1.06 * rows < tiles;
+    const double tiles = 505 + KB * (8.8 + 0.716 * products * ((rows16 + 1) / 2)) + 1.72e-4 * weights + 2.68e-4 * results;
+    const double rows = rounds * (628 + 48. * (double)plan.stages + 2.74 * products * (double)plan.padded) +
+                        (3.44e-4 + 8e-6 * row_tiles) * weights + 2.55e-4 * results;
+    return (plan.blocks < 8 && count > 1 ? 1.15 : 1.) * rows < tiles;
 }
 
 bool thin_applies(const Problem &p, int count)
 {
-    if (p.m > kThinRows) return thin_rows_apply(p, count);
-    if (!thin_possible(p)) return false;
-    const uint64_t cus = (uint64_t)compute_units();
-    const uint64_t rounds = (p.C / (2u * kTile) * (uint64_t)count + cus - 1) / cus, KB = (uint64_t)kblocks(p.k);
-    const uint64_t products = (uint64_t)(planes_x(p.x_bits) * planes_q(p.q_bits_max));
-    const bool short_k = (rounds == 1 && KB <= 8) || (rounds >= 3 && KB < 16);
-    const uint64_t tiles = short_k ? 6u + rounds * (33u + KB * (400u + 23u * products) / 200u) : 20u + rounds * (47u + 6u * KB);
-    return thin_plan(p, count).cost < tiles;
+    return p.m > kThinRows ? thin_rows_apply(p, count) : thin_few_apply(p, count);
 }
 
 // With a second 16-row tile the splitting takes as long as the staging launch (m = 32 on 768 x 16384:

@@ -77,20 +77,19 @@ def test_few_rows(oracle, m, k, n, N, L, x_bits, q_bits):
 # column group alone in its workgroup; two, four and eight slices with and without a remainder;
 # every plane count; the last shape's planes do not fit the LDS
 ROUTED = [
-    (1, 1, 5120, 1024, 2, 20, 54, 1, (1, 0, 1)), (16, 31, 5120, 1024, 2, 16, 50, 1, (1, 0, 1)),
-    (15, 64, 10272, 32, 1, 32, 62, 1, (1, 0, 1)), (16, 65, 6144, 1024, 2, 24, 62, 1, (1, 0, 1)),
-    (9, 129, 5120, 1024, 2, 16, 62, 1, (1, 0, 1)), (7, 769, 3072, 1024, 2, 20, 54, 1, (1, 0, 2)),
-    (16, 257, 32, 32, 1, 32, 54, 1, (1, 0, 4)), (2, 321, 32, 32, 2, 20, 54, 1, (1, 0, 4)),
+    (1, 193, 5120, 1024, 2, 20, 54, 1, (1, 0, 1)), (16, 255, 5120, 1024, 2, 16, 50, 1, (1, 0, 1)),
+    (15, 128, 10272, 32, 1, 32, 62, 1, (1, 0, 1)), (16, 161, 6144, 1024, 2, 24, 62, 1, (1, 0, 1)),
+    (9, 225, 5120, 1024, 2, 16, 62, 1, (1, 0, 1)), (7, 865, 3072, 1024, 2, 20, 54, 1, (1, 0, 2)),
+    (16, 417, 32, 32, 1, 32, 54, 1, (1, 0, 4)), (2, 379, 32, 32, 1, 32, 62, 1, (1, 0, 4)),
     (16, 513, 64, 32, 1, 20, 55, 1, (1, 0, 8)), (16, 1025, 32, 32, 1, 32, 62, 1, (1, 0, 8)),
-    (17, 200, 5120, 1024, 2, 20, 54, 1, (2, 1, 1)), (32, 257, 6144, 1024, 2, 32, 62, 1, (2, 1, 1)),
-    (31, 225, 10272, 32, 1, 16, 62, 1, (2, 1, 1)), (32, 289, 5120, 1024, 2, 24, 62, 1, (2, 1, 1)),
-    (20, 1300, 5120, 1024, 2, 32, 54, 1, (2, 0, 1)), (18, 1400, 3072, 1024, 2, 20, 54, 1, (2, 0, 2)),
-    (17, 321, 32, 32, 1, 16, 50, 1, (2, 0, 4)), (32, 385, 64, 32, 1, 20, 54, 1, (2, 0, 4)),
+    (17, 1256, 5120, 1024, 2, 20, 54, 1, (2, 1, 1)), (32, 545, 6144, 1024, 2, 32, 62, 1, (2, 1, 1)),
+    (31, 1121, 5120, 1024, 2, 24, 62, 1, (2, 1, 1)), (20, 1364, 5120, 1024, 2, 32, 54, 1, (2, 0, 1)),
+    (17, 441, 32, 32, 1, 32, 62, 1, (2, 0, 4)), (32, 448, 32, 32, 2, 32, 62, 1, (2, 0, 4)),
     (25, 513, 32, 32, 2, 24, 62, 1, (2, 0, 8)), (32, 1025, 32, 32, 1, 32, 62, 1, (2, 0, 8)),
     # batches: problems with shares, weights and masks of their own
-    (16, 40, 2048, 1024, 2, 20, 54, 3, (1, 0, 1)), (5, 300, 64, 64, 1, 32, 62, 3, (1, 0, 4)),
-    (17, 460, 2048, 1024, 2, 20, 54, 3, (2, 1, 1)), (32, 300, 2048, 1024, 2, 32, 62, 3, (2, 1, 1)),
-    (32, 400, 64, 64, 1, 20, 54, 3, (2, 0, 4)), (24, 600, 64, 64, 2, 24, 62, 4, (2, 0, 8)),
+    (16, 168, 2048, 1024, 2, 20, 54, 3, (1, 0, 1)), (5, 364, 64, 64, 1, 32, 62, 3, (1, 0, 4)),
+    (17, 751, 2048, 1024, 2, 32, 54, 3, (2, 1, 1)), (32, 565, 2048, 1024, 2, 32, 62, 3, (2, 1, 1)),
+    (32, 441, 32, 32, 2, 32, 62, 3, (2, 0, 4)), (24, 600, 64, 64, 2, 24, 62, 4, (2, 0, 8)),
 ]
 
 

@@ -23,7 +23,7 @@ FORMS = {
     "two full blocks, long": (256, 4224, 2176, 448, True, (True, True, True), 128),
     "rows": (40, 256, 256, 100, True, (False, False, False), 128),
     "rows, two blocks": (130, 5504, 2816, 100, True, (False, False, True), 128),
-    "blocks of 64": (128, 1024, 1024, 450, True, (False, False, True), 64),
+    "blocks of 64": (128, 1024, 1024, 270, True, (False, False, True), 64),
 }
 CASES = [(form, planes, problems) for form in FORMS for planes in PLANES for problems in (1, 2)]
 
@@ -83,7 +83,7 @@ def test_every_instance_of_the_tile_kernel(oracle, form, planes, problems):
     (200, 100, 2048, 64, "cop_mfma_kernel<4, 8, false, false, true, 1>", "cop_mfma_kernel<4, 8, false, false, true, 1>"),
     (128, 64, 64, 64, "cop_mfma_kernel<4, 8, false, false, true, 1>", "cop_mfma_kernel<4, 8, false, false, true, 1>"),
     (40, 64, 64, 33, "cop_mfma_kernel<2, 8, false, false, false, 1>", "cop_mfma_kernel<4, 8, false, false, false, 1>"),
-    (20, 400, 64, 64, "cop_thin_kernel<4, 8, 2, (nimbus::ThinShares)0, 1>", "cop_thin_kernel<4, 8, 2, (nimbus::ThinShares)0, 1>"),
+    (20, 520, 64, 64, "cop_thin_kernel<4, 8, 2, (nimbus::ThinShares)0, 1>", "cop_thin_kernel<4, 8, 2, (nimbus::ThinShares)0, 1>"),
     (16, 64, 64, 48, "cop_thin_kernel<2, 8, 1, (nimbus::ThinShares)2, 1>", "cop_thin_kernel<4, 8, 1, (nimbus::ThinShares)2, 1>"),
 ])
 def test_both_passes_of_wide_shares(oracle, m, k, N, x_bits, upper, lower):

@@ -69,11 +69,11 @@ def test_every_launch_of_the_setup_has_fewer_than_2_to_32_threads():
 
 
 def test_slices_of_few_rows_follow_the_compute_units():
-    """a wave per 16 columns and slice, eight to a workgroup: 1024 column groups are two slices on 256
-    compute units, four where there are twice as many and none on half of them"""
+    """a wave per 16 columns and slice, eight to a workgroup: 512 column groups are four slices on 256
+    compute units, eight where there are twice as many, two on half of them and none on a quarter"""
     mods = moduli_of(54, 2)
-    for units, blocks in ((64, 128), (128, 128), (256, 256), (512, 512)):
-        line = nc.nimbus_route_matmul(1, 768, 20, 4096, 4096, 2, mods, staged=True, units=units)[0]
+    for units, blocks in ((64, 64), (128, 128), (256, 256), (512, 512)):
+        line = nc.nimbus_route_matmul(1, 3072, 20, 2048, 2048, 2, mods, staged=True, units=units)[0]
         assert line.startswith("cop_thin_kernel") and f"grid={blocks},1 " in line, (units, line)
 
 
@@ -92,18 +92,20 @@ def kernels(lines):
 
 
 # m, k, C, x_bits, problems, and the kernel from staged shares (measured on 256 compute units, us, the
-# kernel for few rows / the tiles: 9.0 / 5.8, 11.4 / 6.3, 8.3 / 7.2, 12.9 / 7.3, 35.5 / 32.8, 48.5 / 36.2,
-# 28.9 / 22.1, 11.7 / 10.9, 12.5 / 6.8, 377 / 304; 10.2 / 11.8, 13.5 / 18.5, 9.1 / 13.3, 17.4 / 19.2,
-# 84.8 / 94.3, 10.1 / 12.5)
+# kernel for few rows / the tiles: 9.3 / 4.3, 12.1 / 4.9, 8.7 / 5.0, 13.0 / 5.6, 36.1 / 19.5, 48.8 / 25.8,
+# 28.9 / 17.5, 12.2 / 8.7, 12.9 / 5.7, 370 / 199, 10.7 / 8.3, 17.5 / 15.5, 19.7 / 16.9, 20.2 / 17.2;
+# 30.8 / 38.5, 9.8 / 10.0, 98.1 / 134.0, 33.6 / 44.5)
 @pytest.mark.parametrize("m,k,C,x_bits,count,kernel", [
     (16, 32, 4096, 20, 1, "cop_mfma_kernel"), (32, 32, 4096, 20, 1, "cop_mfma_kernel"),
     (1, 128, 256, 20, 1, "cop_mfma_kernel"), (32, 64, 8192, 20, 1, "cop_mfma_kernel"),
     (16, 32, 131072, 20, 1, "cop_mfma_kernel"), (32, 32, 131072, 20, 1, "cop_mfma_kernel"),
     (32, 128, 49152, 20, 1, "cop_mfma_kernel"), (16, 256, 16384, 20, 1, "cop_mfma_kernel"),
     (24, 32, 4096, 20, 4, "cop_mfma_kernel"), (24, 64, 262144, 20, 4, "cop_mfma_kernel"),
-    (16, 64, 20480, 20, 1, "cop_thin_kernel"), (16, 256, 24576, 20, 1, "cop_thin_kernel"),
-    (32, 512, 4096, 20, 1, "cop_thin_kernel"), (32, 256, 24576, 20, 1, "cop_thin_kernel"),
-    (32, 1024, 65536, 20, 1, "cop_thin_kernel"), (32, 384, 512, 20, 16, "cop_thin_kernel"),
+    (16, 64, 20480, 20, 1, "cop_mfma_kernel"), (32, 256, 24576, 20, 1, "cop_mfma_kernel"),
+    (1, 768, 16384, 20, 1, "cop_mfma_kernel"), (16, 768, 16384, 20, 1, "cop_mfma_kernel"),
+    (1, 3072, 8192, 20, 1, "cop_thin_kernel"),
+    (32, 512, 4096, 20, 1, "cop_thin_kernel"), (32, 2032, 16384, 32, 2, "cop_thin_kernel"),
+    (4, 2097, 2944, 32, 3, "cop_thin_kernel"),
 ])
 def test_few_rows_take_the_faster_kernel(m, k, C, x_bits, count, kernel):
     n = C // 4                                      # (two limbs)
