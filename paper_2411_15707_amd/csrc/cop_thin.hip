@@ -427,20 +427,29 @@ static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (
 // kernel everywhere 8 %.  (us, this kernel and the tiles, 20-bit shares, 54-bit moduli where nothing else is
 // said: 12 x 28 x 24576, 32-bit shares, 11.1 and 7.3, 8 x 1006 x 16384 three times 63.8 and 57.3; 16 x 510 x
 // 8192 12.0 and 10.0; 32 x 2032 x 16384 twice, 32-bit shares, 62-bit moduli, 98.1 and 134.0.)
-static bool thin_few_apply(const Problem &p, int count)
+struct ThinEstimates {
+    double rows, tiles;
+    uint64_t tile_rounds;
+};
+static ThinEstimates thin_few_estimates(const Problem &p, int count)
 {
-    if (!thin_possible(p)) return false;
     const ThinPlan plan = thin_plan(p, count);
-    const uint64_t cus = (uint64_t)compute_units();
-    const double KB = kblocks(p.k), n = (double)count, tile_rounds = (double)((p.C / 64u * (uint64_t)count + cus - 1) / cus);
+    const uint64_t cus = (uint64_t)compute_units(), tile_rounds = (p.C / 64u * (uint64_t)count + cus - 1) / cus;
+    const double KB = kblocks(p.k), n = (double)count;
     const double products = planes_x(p.x_bits) * planes_q(p.q_bits_max);
     const double weights = n * (double)p.C * KB * planes_q(p.q_bits_max), results = n * (double)p.m * (double)p.C;
     const double start = p.m <= 16 ? 700 : plan.copied ? 822 : 733, padded = (double)plan.padded;
-    const double tiles = 317 + tile_rounds * (140 + KB * (9.5 + 0.98 * products)) + 2.3e-4 * weights + 2.2e-4 * results;
+    const double tiles = 317 + (double)tile_rounds * (140 + KB * (9.5 + 0.98 * products)) + 2.3e-4 * weights + 2.2e-4 * results;
     const double rows = (double)plan.rounds * (start + 33. * (double)plan.stages + 1.52 * products * (p.m <= 16 ? 1 : 2) * padded +
                                                35. * padded / (double)plan.depth) +
                         2.44e-4 * weights + 1e-4 * results;
-    return rows < tiles;
+    return {rows, tiles, tile_rounds};
+}
+static bool thin_few_apply(const Problem &p, int count)
+{
+    if (!thin_possible(p)) return false;
+    const ThinEstimates e = thin_few_estimates(p, count);
+    return e.rows < e.tiles;
 }
 
 // More than 32 rows on few columns: where the tile kernel's workgroups leave compute units without a
@@ -477,11 +486,20 @@ bool thin_applies(const Problem &p, int count)
     return p.m > kThinRows ? thin_rows_apply(p, count) : thin_few_apply(p, count);
 }
 
-// With a second 16-row tile the splitting takes as long as the staging launch (m = 32 on 768 x 16384:
-// 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).  Up to 16 rows without the staging launch
-// are ahead of staging and tiles at every k (8 x 32 x 4096 7.5 us a call and 8.4; even where a
-// k-block of 32-bit shares is all there is: 8.4 and 8.5, replayed from a graph 9.0 and 8.6).
-bool thin_raw_applies(const Problem &p) { return thin_possible(p) && p.m <= 16 && thin_planes_fit(p); }
+// From the shares themselves, without a staging launch.  With a second 16-row tile the splitting takes as long
+// as that launch (m = 32 on 768 x 16384: 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).
+// Up to 16 rows: always up to two rounds of tiles, where a call takes little more than its launches cost the
+// host, and one is cheaper than two (8 x 32 x 4096 7.4 us a call and 9.9; in a graph, where the host does
+// not count, 9 % slower over 1353 sizes of up to eight k-blocks, 45 % at worst, 15 % faster over 668 of up
+// to 31).  From three rounds on only where it is ahead of the tiles and a staging launch, two
+// microseconds: 444 sizes 0.3 % off the better one, 22 % from the shares everywhere (6 x 16 x 107520, 16-bit
+// shares, 62-bit moduli, 31.7 and 18.1; 14 x 748 x 39552 52.6 and 44.3).
+bool thin_raw_applies(const Problem &p)
+{
+    if (!thin_possible(p) || p.m > 16 || !thin_planes_fit(p)) return false;
+    const ThinEstimates e = thin_few_estimates(p, 1);
+    return e.tile_rounds <= 2 || e.rows < e.tiles + 200;
+}
 
 template <int DX, int DQ>
 static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int half_shift,

@@ -23,6 +23,7 @@ SHAPES = [
     (20, 70, 4096, 4096, 2, 16, [50, 50]), (5, 449, 8192, 8192, 2, 24, [55, 55]), (9, 321, 8192, 8192, 2, 20, [54, 54]),
     (17, 64, 8192, 8192, 2, 20, [54, 54]), (32, 90, 8192, 8192, 2, 32, [62, 62]), (32, 2000, 32, 32, 1, 32, [54]),
     (33, 64, 32, 32, 1, 20, [54]),
+    (6, 20, 24576, 8192, 2, 16, [62, 62]),              # three rounds of tiles: staged, then the tiles
     (16, 300, 64, 64, 2, 64, [59, 55]), (27, 130, 64, 64, 1, 40, [59]), (1, 70, 32, 32, 1, 48, [50]),
 ]
 

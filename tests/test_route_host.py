@@ -112,3 +112,17 @@ def test_few_rows_take_the_faster_kernel(m, k, C, x_bits, count, kernel):
     N = min(4096, n & -n)                           # the power of two in it
     lines = nc.nimbus_route_matmul(m, k, x_bits, n, N, 2, moduli_of(54, 2), staged=True, count=count, units=256)
     assert kernels(lines) == [kernel]
+
+
+# m, k, C, and the kernels from the shares themselves (us, split in the kernel / staged and tiles, replayed from
+# a graph: 31.7 / 18.1, 52.6 / 44.3; one launch where a call takes little more than that)
+@pytest.mark.parametrize("m,k,C,x_bits,q_bits,expected", [
+    (6, 16, 107520, 16, 62, ["x_planes_kernel", "cop_mfma_kernel"]),
+    (14, 748, 39552, 20, 54, ["x_planes_kernel", "cop_mfma_kernel"]),
+    (1, 768, 16384, 20, 54, ["cop_thin_kernel"]), (8, 32, 4096, 20, 54, ["cop_thin_kernel"]),
+    (4, 2097, 49152, 32, 62, ["cop_thin_kernel"]),
+])
+def test_few_rows_from_the_shares_themselves(m, k, C, x_bits, q_bits, expected):
+    n = C // 4
+    N = min(4096, n & -n)
+    assert kernels(nc.nimbus_route_matmul(m, k, x_bits, n, N, 2, moduli_of(q_bits, 2), units=256)) == expected
