@@ -2,9 +2,9 @@
 // COP kernel leans on, measured the same way the kernel uses them.  Not part of the COP
 // path; declared in include/nimbus_calib.h.
 //
-//  * int8 matrix-core rate: a register-only loop of v_mfma_i32_32x32x32_i8 with three A
-//    operands, seven B operands and nine accumulators per wave (the COP kernel's 3 x 7
-//    digit products), with zero or with random operand bytes.  The sustained rate depends
+//  * int8 matrix-core rate: a register-only loop of v_mfma_i32_16x16x64_i8 with three share
+//    operands of each of two 16-row tiles, seven ciphertext operands and nine accumulators per tile
+//    (the 3 x 7 digit products of the COP kernel), with zero or with random operand bytes.  The sustained rate depends
 //    on the operand values (the chip lowers its clock under load), so both are measured.
 //  * HBM read rate: a grid-stride read of a buffer with 16-byte loads.
 //  * butterfly rate: a register-only loop of the number-theoretic transform's butterfly as
@@ -19,7 +19,6 @@
 namespace {
 
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 __device__ inline uint32_t mix32(uint32_t x)
 {
@@ -29,25 +28,28 @@ __device__ inline uint32_t mix32(uint32_t x)
 
 __global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, int random_operands, int *sink)
 {
-    v4i a[3], b[7];
+    v4i a[6], b[7];
     const uint32_t seed = blockIdx.x * 256u + threadIdx.x;
-    for (int i = 0; i < 3; ++i)
+    for (int i = 0; i < 6; ++i)
         for (int r = 0; r < 4; ++r)
             a[i][r] = random_operands ? (int)mix32(seed * 31u + (uint32_t)(i * 4 + r) + 1u) : 0;
     for (int i = 0; i < 7; ++i)
         for (int r = 0; r < 4; ++r)
             b[i][r] = random_operands ? (int)mix32(seed * 77u + (uint32_t)(i * 4 + r) + 1000u) : 0;
-    v16i c[9];
-    for (int i = 0; i < 9; ++i)
-        for (int r = 0; r < 16; ++r) c[i][r] = 0;
+    v4i c[2][9];
+    for (int t = 0; t < 2; ++t)
+        for (int i = 0; i < 9; ++i) c[t][i] = v4i{0, 0, 0, 0};
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
-        for (int i = 0; i < 21; ++i)
-            c[i / 7 + i % 7] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i / 7], b[i % 7],
-                                                                    c[i / 7 + i % 7], 0, 0, 0);
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+            for (int i = 0; i < 21; ++i)
+                c[t][i / 7 + i % 7] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[3 * t + i / 7], b[i % 7],
+                                                                           c[t][i / 7 + i % 7], 0, 0, 0);
     }
     int s = 0;
-    for (int i = 0; i < 9; ++i) s += c[i][0];
+    for (int t = 0; t < 2; ++t)
+        for (int i = 0; i < 9; ++i) s += c[t][i][0];
     sink[blockIdx.x * 256 + threadIdx.x] = s;
 }
 
@@ -136,8 +138,8 @@ long long nimbus_calib_mfma_i8(int workgroups, int iters, int random_operands, v
     if (nimbus::launch(calib_mfma_kernel, dim3((uint32_t)workgroups), dim3(256), (hipStream_t)stream,
                        iters, random_operands, (int *)sink) != hipSuccess)
         return -1;
-    // int8 operations issued: 4 waves x iters x 21 instructions x 2 * 32*32*32 each
-    return (long long)workgroups * 4ll * iters * 21ll * 65536ll;
+    // int8 operations issued: 4 waves x iters x 42 instructions x 2 * 16*16*64 each
+    return (long long)workgroups * 4ll * iters * 42ll * 32768ll;
 }
 
 long long nimbus_calib_stream_read(const void *src, size_t bytes, void *sink, void *stream)

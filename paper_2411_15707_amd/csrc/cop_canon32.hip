@@ -28,6 +28,7 @@
 
 namespace nimbus {
 
+typedef int v16i __attribute__((ext_vector_type(16)));
 
 template <int OFF>
 __device__ __forceinline__ uint64_t lds_read_b64(uint32_t addr)
@@ -41,6 +42,7 @@ __device__ __forceinline__ void lds_write_b32(uint32_t addr, uint32_t v)
 {
     asm volatile("ds_write_b32 %0, %1 offset:%2" ::"v"(addr), "v"(v), "n"(OFF) : "memory");
 }
+__device__ __forceinline__ void tie_acc(v16i &x) { asm volatile("" : "+v"(x)); }
 __device__ __forceinline__ void tie64(uint64_t &x) { asm volatile("" : "+v"(x)); }
 
 // FULL: m is a multiple of 128.  SHARED: several row blocks per column tile (m > 128); they
@@ -360,8 +362,22 @@ __global__ __launch_bounds__(512, 1) void cop_canon32_kernel(const CanonArgs ca)
         add128(hi, lo, highs >> 32, highs << 32);
         colsum_S = barrett128(hi, lo, ca.limbs.limb[limb]);      // k * q < 2^(b+63)
     }
-    cop_epilogue<ND, FULL>(acc, a, a.mask, nullptr, a.out, limb, colsum_S, rt * kTile + 4 * (lane >> 5),
-                                  (ct2 * 2u + (uint32_t)wc) * kTile + (uint32_t)(lane & 31));
+    // element r of the lane is row 8 (r / 4) + r % 4 behind row0
+    const int row0 = rt * kTile + 4 * (lane >> 5);
+    const uint32_t col = (ct2 * 2u + (uint32_t)wc) * kTile + (uint32_t)(lane & 31);
+    auto roff = [](int r) -> int { return 8 * (r >> 2) + (r & 3); };
+    cop_finish<ND, 16, FULL>(
+        [&](int d, int r) -> int32_t { return acc[d][r]; }, roff,
+        [&](uint64_t (&mk)[16]) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) mk[r] = 0;
+            if (!a.mask) return;
+            const uint64_t *const mask0 = a.mask + ((size_t)row0 * C + col);
+#pragma unroll
+            for (int r = 0; r < 16; ++r)
+                if (FULL || row0 + roff(r) < a.m) mk[r] = __builtin_nontemporal_load(&mask0[(size_t)roff(r) * C]);
+        },
+        a, nullptr, a.out, limb, colsum_S, row0, col, a.m);
 }
 
 // ---------------------------------------------------------------------------

@@ -7,9 +7,7 @@
 
 namespace nimbus {
 
-
 typedef int v4i __attribute__((ext_vector_type(4)));
-typedef int v16i __attribute__((ext_vector_type(16)));
 
 __device__ __forceinline__ void add128(uint64_t &hi, uint64_t &lo, uint64_t ahi, uint64_t alo)
 {
@@ -19,23 +17,20 @@ __device__ __forceinline__ void add128(uint64_t &hi, uint64_t &lo, uint64_t ahi,
 }
 
 // ---------------------------------------------------------------------------
-// main kernel: arguments (the pipeline is described further down)
+// arguments that all kernels have (operands, mask and output of the kernels on prepared weights: BatchPtrs)
 // ---------------------------------------------------------------------------
 struct MfmaArgs {
-    const uint4 *xd;          // [RT][KB][DX][64] uint4
-    const uint4 *planes;      // [CT][KB][DQ][64] uint4
-    const uint64_t *colsum;   // [C]
     const uint64_t *mask;     // [m][C] or null
     const uint64_t *prev;     // [m][C] or null: result of the pass over the upper share halves
     uint64_t *out;            // [m][C]
     int m, KB, RB, N, L;
     uint32_t C, CT;
-    uint32_t tiles;           // 128 x 64 output tiles: (CT / 2) * RB
+    uint32_t tiles;           // output tiles of 64 columns and a row block: (CT / 2) * RB, of all problems
     uint32_t kb_magic;        // floor(2^32 / KB): x / KB = umulhi(x, kb_magic) or one more
     uint32_t log_n;           // N = 2^log_n
     uint32_t l_magic;         // ceil(2^32 / L) for L >= 2: x / L = umulhi(x, l_magic) for x < 2^31
     uint32_t offx;            // OFFX
-    uint32_t block_tiles;     // 32-row tiles of a row block, four at most (see mfma_impl())
+    uint32_t block_tiles;     // 32-row tiles of a row block, four at most (see tile_blocks())
     uint64_t q[kMaxLimbs];
     double qinv[kMaxLimbs];   // 1 / q_l, rounded
     // q_l << sh
@@ -172,8 +167,6 @@ __device__ __forceinline__ void wait_lds(v4i &x)
 // keeps the users of x behind the preceding volatile asm statements (and the producer of
 // x before the following ones)
 __device__ __forceinline__ void tie(v4i &x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void tie_acc(v16i &x) { asm volatile("" : "+v"(x)); }
-__device__ __forceinline__ void tie(int &x) { asm volatile("" : "+v"(x)); }
 
 // wait until at most PENDING of this wave's global loads (here: direct-to-LDS loads) are
 // outstanding
@@ -427,34 +420,6 @@ __device__ __forceinline__ void cop_finish(Digit D, RowOf roff, Masks masks, con
         // not sit dirty in L2 need no write-back when the kernel ends)
         if (FULL || row0 + roff(r) < row_end) __builtin_nontemporal_store(res, &out0[(size_t)roff(r) * a.C]);
     }
-}
-
-// the same for a wave's 32 x 32 tile (the kernel on the canonical layout):
-//   acc        ND accumulator tiles (element r of the lane is row row0 + 8 (r / 4) + r % 4)
-//   mask       the problem's mask (or null)
-template <int ND, bool FULL>
-__device__ __forceinline__ void cop_epilogue(v16i (&acc)[ND], const MfmaArgs &a,
-                                             const uint64_t *mask, const uint64_t *prev,
-                                             uint64_t *out, uint32_t limb, uint64_t colsum_S,
-                                             int row0, uint32_t col)
-{
-    auto roff = [](int r) -> int { return 8 * (r >> 2) + (r & 3); };
-    const uint64_t *const mask0 = mask ? mask + ((size_t)row0 * a.C + col) : nullptr;
-    cop_finish<ND, 16, FULL>(
-        [&](int d, int r) -> int32_t { return acc[d][r]; }, roff,
-        [&](uint64_t (&mk)[16]) {
-            if (mask) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r)
-                    mk[r] = (FULL || row0 + roff(r) < a.m)
-                                ? __builtin_nontemporal_load(&mask0[(size_t)roff(r) * a.C])
-                                : 0;
-            } else {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) mk[r] = 0;
-            }
-        },
-        a, prev, out, limb, colsum_S, row0, col, a.m);
 }
 
 }  // namespace nimbus

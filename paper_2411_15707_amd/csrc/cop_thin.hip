@@ -429,21 +429,24 @@ static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (
 // 8192 12.0 and 10.0; 32 x 2032 x 16384 twice, 32-bit shares, 62-bit moduli, 98.1 and 134.0.)
 struct ThinEstimates {
     double rows, tiles;
-    uint64_t tile_rounds;
 };
+static uint64_t tile_rounds_of(const Problem &p, int count)
+{
+    const uint64_t cus = (uint64_t)compute_units();
+    return (p.C / 64u * (uint64_t)count + cus - 1) / cus;
+}
 static ThinEstimates thin_few_estimates(const Problem &p, int count)
 {
     const ThinPlan plan = thin_plan(p, count);
-    const uint64_t cus = (uint64_t)compute_units(), tile_rounds = (p.C / 64u * (uint64_t)count + cus - 1) / cus;
     const double KB = kblocks(p.k), n = (double)count;
     const double products = planes_x(p.x_bits) * planes_q(p.q_bits_max);
     const double weights = n * (double)p.C * KB * planes_q(p.q_bits_max), results = n * (double)p.m * (double)p.C;
     const double start = p.m <= 16 ? 700 : plan.copied ? 822 : 733, padded = (double)plan.padded;
-    const double tiles = 317 + (double)tile_rounds * (140 + KB * (9.5 + 0.98 * products)) + 2.3e-4 * weights + 2.2e-4 * results;
+    const double tiles = 317 + (double)tile_rounds_of(p, count) * (140 + KB * (9.5 + 0.98 * products)) + 2.3e-4 * weights + 2.2e-4 * results;
     const double rows = (double)plan.rounds * (start + 33. * (double)plan.stages + 1.52 * products * (p.m <= 16 ? 1 : 2) * padded +
                                                35. * padded / (double)plan.depth) +
                         2.44e-4 * weights + 1e-4 * results;
-    return {rows, tiles, tile_rounds};
+    return {rows, tiles};
 }
 static bool thin_few_apply(const Problem &p, int count)
 {
@@ -497,8 +500,9 @@ bool thin_applies(const Problem &p, int count)
 bool thin_raw_applies(const Problem &p)
 {
     if (!thin_possible(p) || p.m > 16 || !thin_planes_fit(p)) return false;
+    if (tile_rounds_of(p, 1) <= 2) return true;
     const ThinEstimates e = thin_few_estimates(p, 1);
-    return e.tile_rounds <= 2 || e.rows < e.tiles + 200;
+    return e.rows < e.tiles + 200;
 }
 
 template <int DX, int DQ>

@@ -82,10 +82,10 @@ SMALL = [
     (200, 500, 256, 256, 1, 16, 50),    # ragged m, the last row block of 64 with 8 rows, 16 k-blocks
     # more output tiles than compute units: a workgroup walks several tiles, the first stages of
     # the next one in flight under the epilogue of the one before
-    (128, 512, 8192, 8192, 3, 20, 54),  # 768 tiles, mask tile through LDS
+    (128, 512, 8192, 8192, 3, 20, 54),  # 768 tiles, mask words ahead
     (70, 100, 8192, 8192, 3, 20, 54),   # 768 tiles, a wave without rows in every tile
     (200, 70, 4096, 4096, 2, 20, 54),   # 512 tiles in two row blocks, the second ragged
-    (128, 96, 16384, 16384, 1, 32, 62), # 512 tiles, 4 x 8 planes (one operand set)
+    (128, 96, 16384, 16384, 1, 32, 62), # 512 tiles, 4 x 8 planes (eleven accumulators)
     # the ends of the accepted ranges
     (6, 50, 64, 64, 4, 20, 54),         # four limbs
     (3, 33, 32768, 32768, 2, 20, 54),   # the paper's largest ring degree
@@ -124,8 +124,8 @@ def test_one_to_three_k_blocks_per_plane_count(oracle, t_bits, q_bits, k, m):
     _check_both(oracle, X, ctW, moduli, n, N, t_bits, mask, f"k={k} t={t_bits} q={q_bits}")
 
 
-# the kernel for few rows; the tile kernel with row tests, in blocks of 64 rows, and (8448 columns) in full
-# blocks of 128, the mask tile in LDS where there is one
+# the kernel for few rows, for more rows on few columns too (256 of them; with row tests, the tile kernel has
+# them in test_gpu_tile_rows.py), and (8448 columns) the tile kernel in full blocks of 128, mask words ahead
 @pytest.mark.parametrize("m,n", [(32, 64), (40, 64), (128, 64), (128, 2112)])
 def test_all_maximal_operands(oracle, m, n):
     """every share t-1 and every residue q-1: the largest sums the accumulators can see"""
@@ -500,7 +500,7 @@ BATCHES = [
     (33, 100, 40, 64, 2, 20, 54, 3, True),        # ragged rows and k
     (256, 100, 256, 256, 1, 20, 54, 3, True),     # four blocks of 64 rows per column tile
     (128, 96, 8192, 8192, 3, 20, 54, 2, False),   # 768 tiles each: more tiles than compute units
-    (64, 70, 64, 64, 1, 32, 62, 4, True),         # 4 x 8 planes (one operand set)
+    (64, 70, 64, 64, 1, 32, 62, 4, True),         # 4 x 8 planes (eleven accumulators)
     (8, 64, 64, 1024, 1, 16, 50, 16, True),       # the largest batch, config 1's shape
     (40, 96, 128, 128, 3, 24, 55, 1, True),       # a batch of one
 ]
@@ -556,7 +556,7 @@ def test_calibration_launches_run():
         nc.nimbus_calib_butterflies(8, 5, 1 << 54, bsink)  # even modulus: refused on the host
 
 
-# few rows; the tile kernel with row tests, and in blocks of 64 rows
+# the kernel for few rows, up to 32 and more of them on few columns (the tile kernel: test_gpu_tile_rows.py)
 @pytest.mark.parametrize("m", [3, 33, 128])
 @pytest.mark.parametrize("t_bits,q_bits", [(32, 62), (20, 54), (16, 50)])
 def test_longest_inner_dimension_with_extreme_digits(oracle, t_bits, q_bits, m):

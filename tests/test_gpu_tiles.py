@@ -1,5 +1,5 @@
-"""The tile kernel of more than 32 rows against the oracle: where its loop has a single operand set, at
-every length of the loop's ends; row blocks of 64 rows (few columns) and where they end."""
+"""More than 32 rows against the oracle: with ten and eleven accumulators at every length of the tile kernel's
+loop's ends; row blocks of 64 rows (few columns) and where they end."""
 import numpy as np
 import pytest
 
