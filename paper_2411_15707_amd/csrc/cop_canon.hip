@@ -437,7 +437,7 @@ static CanonArgs canon_args(const Problem &p, int DX, int DQ, const uint64_t *X,
 //   four share planes and centred digits, m a multiple of 128: there (32-bit shares, moduli just below
 //       2^55, 128 x 160 x 8192 17.5 and 20.1, 128 x 928 x 2048 54.5 and 58.9; 512 x 416 x 8192 even, 256 x
 //       1504 x 4096 here by 1 %: this kernel spills four registers);
-//   more than 96 rows in a row block and three or five k-blocks, without row tests one or seven too:
+//   more than 96 rows in a row block and one, three or five k-blocks, without row tests seven too:
 //       there (20-bit shares, 128 x 95 x 8192 13.6 and 15.3, 128 x 160 x 8192 16.1 and 17.2): the last stage is
 //       half empty, and a second one costs the fetch of the whole loop's code;
 //   else here (128 x 60 x 8192 11.9 and 11.0, 300 x 220 x 8192 35.4 and 34.0, 70 x 95 x 8192 13.0 and 11.9).
