@@ -26,7 +26,9 @@ __device__ inline uint32_t mix32(uint32_t x)
     return x;
 }
 
-__global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, int random_operands, int *sink)
+// (two workgroups per compute unit at least, and the sums tied: left alone the compiler puts the 18
+// accumulators into a second register file and copies about one operand per product to and fro)
+__global__ __launch_bounds__(256, 2) void calib_mfma_kernel(int iters, int random_operands, int *sink)
 {
     v4i a[6], b[7];
     const uint32_t seed = blockIdx.x * 256u + threadIdx.x;
@@ -43,9 +45,11 @@ __global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, int random_o
 #pragma unroll
         for (int t = 0; t < 2; ++t)
 #pragma unroll
-            for (int i = 0; i < 21; ++i)
-                c[t][i / 7 + i % 7] = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[3 * t + i / 7], b[i % 7],
-                                                                           c[t][i / 7 + i % 7], 0, 0, 0);
+            for (int i = 0; i < 21; ++i) {
+                v4i &sum = c[t][i / 7 + i % 7];
+                sum = __builtin_amdgcn_mfma_i32_16x16x64_i8(a[3 * t + i / 7], b[i % 7], sum, 0, 0, 0);
+                asm volatile("" : "+v"(sum));       // stays in its registers
+            }
     }
     int s = 0;
     for (int t = 0; t < 2; ++t)
