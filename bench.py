@@ -509,11 +509,13 @@ def main():
         # butterflies and N pointwise products, counted as the butterfly the kernels run for
         # these moduli: 16 and 13 where every modulus lies in [2^34, 2^58) (no conditional
         # subtractions, quotient estimate from three partial products), else 24 and 16
+        # (rings of 1024 to 8192: two stages fewer, and 39 for a coefficient's four products modulo X^4 - zeta)
         loose = all((1 << 34) <= q < (1 << 58) for q in moduli)
-        ops_bf, ops_pw = (16, 13) if loose else (24, 16)
-        int_ops = (N * logN * ops_bf + N * ops_pw) * Tb * L
+        blocks = loose and 10 <= logN <= 13
+        ops_bf, ops_pw = (16, 39 if blocks else 13) if loose else (24, 16)
+        int_ops = (N * (logN - 2 * blocks) * ops_bf + N * ops_pw) * Tb * L
         server = {
-            "kernel": f"rlwe_poly_kernel<{logN}>",
+            "kernel": f"rlwe_{'product' if blocks else 'poly'}_kernel<{logN}>",
             "encrypt_weight_rows_ms": round(enc_ms, 4),
             "encrypt_polynomials": k * cfg.Ch * L,
             "decrypt_output_rows_ms": round(dec_ms, 4),

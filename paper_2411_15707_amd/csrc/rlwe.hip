@@ -33,10 +33,13 @@
 // the benchmark configurations): no conditional subtractions, bounds tracked at compile time
 // instead, and a cheaper quotient estimate; see group_butterflies.
 //
+// Rings of 2^10 to 2^13 coefficients with moduli from 2^34 to 2^59 take another kernel, whose transform
+// stops two stages early: rlwe_product.hpp.
+//
 // Tables: the constants of a transform are read once per polynomial from the second-level
-// cache; they are stored a second and third time in the order in which the threads of the
+// cache; they are stored again, for each kind of batch, in the order in which the threads of the
 // product kernels read them (neighbouring lanes, neighbouring entries; see power_slot()).
-#include "rlwe_kernels.hpp"
+#include "rlwe_product.hpp"
 
 namespace nimbus {
 
@@ -88,7 +91,8 @@ __global__ __launch_bounds__(256) void rlwe_powers_kernel(RlweArgs a, int logN, 
 // setup: transform of the secret, times 1/N, with companions
 // one workgroup per limb
 // ---------------------------------------------------------------------------
-template <int LOGN, int PRE>
+// (SKIP: the last stages that are left out, with the factor 2^SKIP / N; see rlwe_product.hpp)
+template <int LOGN, int PRE, int SKIP>
 __global__ __launch_bounds__(threads_for(LOGN - PRE, 4)) void rlwe_secret_kernel(
     RlweArgs a, const int8_t *__restrict__ s, Twiddle *__restrict__ tables)
 {
@@ -111,13 +115,14 @@ __global__ __launch_bounds__(threads_for(LOGN - PRE, 4)) void rlwe_secret_kernel
             lds[pad(c)] = enter_part<PRE>(lifted(c), lifted(c + NP), w0, md, h);
     }
     __syncthreads();
-    forward_only<LOGN, PRE, 4, PRE, NT>(lds, t, md, tid, h);
+    forward_only<LOGN, PRE, 4, PRE, NT, LOGN - SKIP>(lds, t, md, tid, h);
     for (int c = tid; c < NP; c += NT) {
         uint64_t v = lds[pad(c)];               // [0, 4q)
         v = v >= 2 * q ? v - 2 * q : v;
         v = v >= q ? v - q : v;
         v = mulmod(v, P.n_inv, P.red);
-        t[2 * N + h * NP + c] = Twiddle{v, companion(v, q)};
+        if constexpr (SKIP > 0) v = mulmod(v, 1u << SKIP, P.red);
+        t[(SKIP > 0 ? product_secret_at(N) : 2 * N) + h * NP + c] = Twiddle{v, companion(v, q)};
     }
 }
 
@@ -136,6 +141,45 @@ __global__ __launch_bounds__(256) void rlwe_table_set_kernel(Twiddle *__restrict
     to[p] = from[e];
     to[N + p] = from[N + e];
     to[2 * N + secret_slot(logN, pre, maxs, (int)e)] = from[2 * N + e];
+}
+
+// setup: the set of rlwe_product_kernel for one kind of batch (see rlwe_product.hpp); one thread per
+// coefficient of the secret's transform, the first N/4 for a power each way too
+__global__ __launch_bounds__(256) void rlwe_product_set_kernel(RlweArgs a, Twiddle *__restrict__ tables, int logN,
+                                                               int L, int kind)
+{
+    const int N = 1 << logN, maxs = product_stages(logN, kind);
+    const uint32_t gid = blockIdx.x * 256u + threadIdx.x;
+    if (gid >= (uint32_t)N * (uint32_t)L) return;
+    const uint32_t l = gid >> logN;
+    const int c = (int)(gid & (uint32_t)(N - 1));
+    const Twiddle *const from = tables + (size_t)l * limb_table_entries(N);
+    Twiddle *const to = tables + (size_t)l * limb_table_entries(N) + product_set_at(N, kind);
+    int round = 0;                                      // the round whose stages hold the power's
+    if (c < N / 4) {
+        int slot = c;
+        if (c > 0) {
+            int s = 0;
+            while ((2 << s) <= c) ++s;                  // stage of entry c: 2^s <= c < 2^(s+1)
+            while (product_round_start(logN, maxs, round + 1) <= s) ++round;
+            const int p0 = product_round_start(logN, maxs, round), st = s - p0, b = c - (1 << s);
+            slot = (1 << s) + ((b & ((1 << st) - 1)) << p0) + (b >> st);
+        }
+        to[slot] = from[c];
+        to[product_inverse_at(N) + slot] = from[N + c];
+    }
+    while (product_round_start(logN, maxs, round + 1) < logN) ++round;
+    const int S = logN - product_round_start(logN, maxs, round);
+    const int block = c >> 2, i = c & 3, k = block & ((1 << (S - 2)) - 1), group = c >> S, groups = N >> S;
+    Twiddle *const at = to + product_blocks_at(N) + (size_t)k * 7 * groups + group;
+    const Twiddle b = from[product_secret_at(N) + c];
+    at[i * groups] = b;
+    if (i == 0) return;
+    // zeta: the parent block's power (stage log N - 3: N/8 blocks), for an odd block its negative
+    const Limb &P = a.limb[l].red;
+    const uint64_t root = from[N / 8 + (block >> 1)].w;
+    const uint64_t w = mulmod(b.w, block & 1 ? P.q - root : root, P);
+    at[(3 + i) * groups] = Twiddle{w, companion(w, P.q)};
 }
 
 // ---------------------------------------------------------------------------
@@ -431,15 +475,16 @@ static int scaling(int L, const uint64_t *moduli, int t_bits, Scaling *out)
     return NIMBUS_COP_OK;
 }
 
+template <int SKIP>
 static hipError_t launch_secret(const RlweArgs &a, int logN, int L, const int8_t *s,
                                 Twiddle *tables, hipStream_t stream)
 {
     if (logN == 15) {
-        return launch(rlwe_secret_kernel<15, 1>, dim3(2u * (unsigned)L), dim3(threads_for(14, 4)),
+        return launch(rlwe_secret_kernel<15, 1, 0>, dim3(2u * (unsigned)L), dim3(threads_for(14, 4)),
                       stream, a, s, tables);
     }
-    NIMBUS_RLWE_DISPATCH(logN, launch(rlwe_secret_kernel<LOGN, 0>, dim3((unsigned)L),
-                                      dim3(threads_for(LOGN, 4)), stream, a, s, tables));
+    NIMBUS_RLWE_DISPATCH(logN, (launch(rlwe_secret_kernel<LOGN, 0, LOGN >= kProductMinLogN && LOGN <= kProductMaxLogN ? SKIP : 0>,
+                                       dim3((unsigned)L), dim3(threads_for(LOGN, 4)), stream, a, s, tables)));
 }
 
 }  // namespace nimbus
@@ -477,15 +522,25 @@ int nimbus_rlwe_setup(int N, int L, const uint64_t *moduli, const int8_t *s,
     if (launch(rlwe_powers_kernel, dim3((total + 255u) / 256u), dim3(256), (hipStream_t)stream,
                a, logN, L, (Twiddle *)tables) != hipSuccess)
         return NIMBUS_COP_ERR_LAUNCH;
-    if (launch_secret(a, logN, L, s, (Twiddle *)tables, (hipStream_t)stream) != hipSuccess)
+    const dim3 grid((total + 255u) / 256u), block(256);
+    if (product_kernel_applies(a, L, logN)) {
+        if (launch_secret<2>(a, logN, L, s, (Twiddle *)tables, (hipStream_t)stream) != hipSuccess)
+            return NIMBUS_COP_ERR_LAUNCH;
+        for (int kind = 0; kind < product_kinds(logN); ++kind)
+            if (launch(rlwe_product_set_kernel, grid, block, (hipStream_t)stream, a, (Twiddle *)tables, logN, L,
+                       kind) != hipSuccess)
+                return NIMBUS_COP_ERR_LAUNCH;
+        return NIMBUS_COP_OK;
+    }
+    if (launch_secret<0>(a, logN, L, s, (Twiddle *)tables, (hipStream_t)stream) != hipSuccess)
         return NIMBUS_COP_ERR_LAUNCH;
-    // the same entries in the order of the product kernels: large batches, small batches
+    // the same entries in the order of the product kernel: large batches, small batches
     const int pre = logN == 15 ? 1 : 0;
     const int maxs_of[kTableSets] = {0, logN == 15 ? 4 : stages_large_batch(logN),
                                      logN == 15 ? 4 : stages_small_batch(logN)};
     for (int set = 1; set < kTableSets; ++set) {
-        if (launch(rlwe_table_set_kernel, dim3((total + 255u) / 256u), dim3(256), (hipStream_t)stream,
-                   (Twiddle *)tables, logN, L, pre, maxs_of[set], set) != hipSuccess)
+        if (launch(rlwe_table_set_kernel, grid, block, (hipStream_t)stream, (Twiddle *)tables, logN, L, pre,
+                   maxs_of[set], set) != hipSuccess)
             return NIMBUS_COP_ERR_LAUNCH;
     }
     return NIMBUS_COP_OK;
@@ -509,7 +564,7 @@ int nimbus_rlwe_phase(const uint64_t *ct, int T, int N, int L, const uint64_t *m
     a.L = L;
     a.src = ct;
     a.dst = phi;
-    const hipError_t e = launch_poly<false>(a, log2_exact(N), (size_t)T * L, (hipStream_t)stream);
+    const hipError_t e = launch_product<false>(a, log2_exact(N), (size_t)T * L, (hipStream_t)stream);
     return e == hipSuccess ? NIMBUS_COP_OK : NIMBUS_COP_ERR_LAUNCH;
 }
 

@@ -21,10 +21,11 @@ struct Twiddle {
     uint64_t ws;    // floor(w * 2^64 / q)
 };
 
-// Per limb three sets of  forward powers | inverse powers | transformed secret (times 1/N),
+// 9 N entries per limb.  Where rlwe_product_kernel applies, see rlwe_product.hpp; else three sets of
+//   forward powers | inverse powers | transformed secret (times 1/N),
 // N entries each: set 0 in the natural order (bit-reversed powers, secret by coefficient), sets
-// 1 and 2 the same entries in the order in which the product kernels for large and for small
-// batches read them (see table_slot()).
+// 1 and 2 the same entries in the order in which rlwe_poly_kernel reads them for large and for small
+// batches (see power_slot()).
 constexpr int kTableSets = 3;
 __host__ __device__ inline size_t set_entries(int N) { return (size_t)3 * (size_t)N; }
 __host__ __device__ inline size_t limb_table_entries(int N) { return kTableSets * set_entries(N); }
@@ -602,16 +603,16 @@ __device__ __forceinline__ void multiply_by_secret(uint64_t *lds, const Twiddle 
     }
 }
 
-// forward stages P0 .. LOGN-1 of the part in the LDS; ends with a barrier
-template <int LOGN, int PRE, int MAXS, int P0, int NT>
+// forward stages P0 .. END-1 of the part in the LDS; ends with a barrier
+template <int LOGN, int PRE, int MAXS, int P0, int NT, int END>
 __device__ __forceinline__ void forward_only(uint64_t *lds, const Twiddle *fwd, const Mod &md, int tid,
                                              int h)
 {
-    if constexpr (P0 < LOGN) {
-        constexpr int S = round_stages(LOGN - P0, MAXS);
+    if constexpr (P0 < END) {
+        constexpr int S = round_stages(END - P0, MAXS);
         ntt_round<LOGN, PRE, P0, S, kForward, NT>(lds, fwd, nullptr, nullptr, md, tid, h);
         __syncthreads();
-        forward_only<LOGN, PRE, MAXS, P0 + S, NT>(lds, fwd, md, tid, h);
+        forward_only<LOGN, PRE, MAXS, P0 + S, NT, END>(lds, fwd, md, tid, h);
     }
 }
 
@@ -631,7 +632,7 @@ __device__ __forceinline__ uint64_t enter_part(uint64_t u, uint64_t v, const Twi
 // ---------------------------------------------------------------------------
 struct PolyArgs {
     const Twiddle *tables;
-    int set;        // table set of the product kernel that is launched (1 or 2)
+    int set;        // table set: of rlwe_poly_kernel (1 or 2), or the kind of rlwe_product_kernel
     int L;
     // phase: src = ct [T][2][L][N], dst = phi [T][L][N]
     // encrypt: src = a [rows][L][N], dst = ctW [rows][2][L][N]
@@ -822,27 +823,35 @@ constexpr int kSetLargeBatch = 1, kSetSmallBatch = 2;
 
 // which of the kernels applies: without conditional subtractions where every modulus leaves
 // the room (see group_butterflies)
-static int lazy_kind(const PolyArgs &a)
+static int lazy_kind(const RlweArgs &a, int L)
 {
     int kind = kLoose;
-    for (int l = 0; l < a.L; ++l) {
-        const uint64_t q = a.limbs.limb[l].red.q;
+    for (int l = 0; l < L; ++l) {
+        const uint64_t q = a.limb[l].red.q;
         if (q < (1ull << 34) || q >= (1ull << 59)) return kNever;
         if (q >= (1ull << 58)) kind = kTight;
     }
     return kind;
 }
 
+// (rings that rlwe_product_kernel takes come here with moduli it does not take alone)
+constexpr int kProductMinLogN = 10, kProductMaxLogN = 13;      // rings of rlwe_product_kernel
+template <bool ENCRYPT, int MAXS, int LAZY, int LOGN>
+static hipError_t launch_poly_ring(const PolyArgs &a, size_t polys, hipStream_t stream)
+{
+    if constexpr (LOGN >= kProductMinLogN && LOGN <= kProductMaxLogN && LAZY != kNever) return hipErrorInvalidValue;
+    else return launch(rlwe_poly_kernel<LOGN, 0, MAXS, ENCRYPT, LAZY>, dim3((unsigned)polys),
+                       dim3(threads_for(LOGN, MAXS)), stream, a);
+}
 template <bool ENCRYPT, int MAXS, int LAZY>
 static hipError_t launch_poly_with(const PolyArgs &a, int logN, size_t polys, hipStream_t stream)
 {
-    NIMBUS_RLWE_DISPATCH(logN, launch(rlwe_poly_kernel<LOGN, 0, MAXS, ENCRYPT, LAZY>, dim3((unsigned)polys),
-                                      dim3(threads_for(LOGN, MAXS)), stream, a));
+    NIMBUS_RLWE_DISPATCH(logN, (launch_poly_ring<ENCRYPT, MAXS, LAZY, LOGN>(a, polys, stream)));
 }
 template <bool ENCRYPT, int MAXS>
 static hipError_t launch_poly_stages(const PolyArgs &a, int logN, size_t polys, hipStream_t stream)
 {
-    switch (lazy_kind(a)) {
+    switch (lazy_kind(a.limbs, a.L)) {
     case kLoose: return launch_poly_with<ENCRYPT, MAXS, kLoose>(a, logN, polys, stream);
     case kTight: return launch_poly_with<ENCRYPT, MAXS, kTight>(a, logN, polys, stream);
     default: return launch_poly_with<ENCRYPT, MAXS, kNever>(a, logN, polys, stream);
@@ -856,7 +865,7 @@ static hipError_t launch_poly_in_parts(PolyArgs a, size_t polys, hipStream_t str
     a.set = kSetLargeBatch;
     const dim3 grid(2u * (unsigned)polys), block(threads_for(14, 4));
     hipError_t e;
-    switch (lazy_kind(a)) {
+    switch (lazy_kind(a.limbs, a.L)) {
     case kLoose: e = launch(rlwe_poly_kernel<15, 1, 4, ENCRYPT, kLoose>, grid, block, stream, a); break;
     case kTight: e = launch(rlwe_poly_kernel<15, 1, 4, ENCRYPT, kTight>, grid, block, stream, a); break;
     default: e = launch(rlwe_poly_kernel<15, 1, 4, ENCRYPT, kNever>, grid, block, stream, a); break;

@@ -137,3 +137,51 @@ def test_no_word_overflows_without_conditional_subtractions():
                     assert most <= units, (log_n, maxs, i)
                     bin_ = max(after)
                 assert bin_ <= 2                          # what the last round leaves: below 2q
+
+
+# ---- the product kernel: a transform without its last two stages, products modulo X^4 - zeta ----
+def _product_rounds(log_n, maxs):
+    f = -(-log_n // maxs)
+    return [log_n - (f - 1) * maxs] + [maxs] * (f - 1)
+
+
+def test_no_word_overflows_in_the_product_kernel():
+    """forward: all stages but two; middle: four products summed; inverse: as many stages back"""
+    for units, prod, q_bits in ((64, 4, 58), (32, 2, 59)):
+        for log_n, kinds in ((10, (2,)), (11, (2, 3)), (12, (2, 3, 4)), (13, (3,))):
+            for maxs in kinds:
+                stages = _product_rounds(log_n, maxs)
+                assert sum(stages) == log_n and 1 <= stages[0] <= maxs and stages[-1] >= 2
+                stages[-1] -= 2
+                assert 1 + prod * (log_n - 2) <= units
+                bin_, order = 4 * prod, stages[::-1]
+                for i, S in enumerate(order):
+                    tout = units >> order[i + 1] if i + 1 < len(order) else 2
+                    most, after = _inverse_round(S, bin_, tout, prod)
+                    assert max(most, bin_) <= units, (log_n, maxs, i)
+                    bin_ = max(after)
+                assert bin_ <= 2
+
+
+def test_block_product_with_shared_quotients():
+    """c_k = sum a_i b_(k-i) + sum a_i zb_(k+4-i) modulo X^4 - zeta; the quotients' sum, wrapped, times 2^64 - q
+    leaves a value below 16q (three partial products) or 8q (exact quotients)"""
+    rng = random.Random(5)
+    for bits, exact in ((58, False), (55, False), (59, True)):
+        for q in _moduli(rng, 35, bits, 10):
+            zeta = rng.randrange(q)
+            b = [rng.randrange(q) for _ in range(4)]
+            const = b + [zeta * v % q for v in b[1:]]
+            comp = [(w << 64) // q for w in const]
+            for _ in range(20):
+                a = [rng.choice([0, M64, rng.getrandbits(64)]) for _ in range(4)]
+                for k in range(4):
+                    h = p = 0
+                    for i in range(4):
+                        e = k - i if i <= k else 7 + k - i
+                        x0, x1, w0, w1 = a[i] & 0xFFFFFFFF, a[i] >> 32, comp[e] & 0xFFFFFFFF, comp[e] >> 32
+                        h += (a[i] * comp[e]) >> 64 if exact else x1 * w1 + ((x0 * w1) >> 32) + ((x1 * w0) >> 32)
+                        p += a[i] * const[e]
+                    got = ((p & M64) + (h & M64) * ((1 << 64) - q)) & M64
+                    want = sum(a[i] * (b[k - i] if i <= k else zeta * b[k + 4 - i]) for i in range(4)) % q
+                    assert got < (8 if exact else 16) * q and got % q == want
