@@ -161,7 +161,8 @@ static hipError_t stage_and_matmul(const Problem &p, const uint64_t *X, void *wo
 {
     const bool wide = p.x_bits > 32;
     const Problem lo = half_problem(p, wide ? 32 : p.x_bits), hi = half_problem(p, p.x_bits - 32);
-    if (!thin_raw_applies(lo) || (wide && !thin_raw_applies(hi))) {
+    // (two halves of more than 16 rows: their planes come out of one staging launch)
+    if (!thin_raw_applies(lo) || (wide && (p.m > 16 || !thin_raw_applies(hi)))) {
         const hipError_t e = launch_stage_shares(p, X, workspace, stream);
         return e == hipSuccess ? matmul_all(p, workspace, prepared, mask, out, stream) : e;
     }

@@ -25,11 +25,11 @@
 // and the staging launch and the gap behind it go away.  The planes are left in the workspace
 // all the same (workgroup b writes the stages b, b + grid, ...), as that entry point promises.
 //
-// Measured against the 128 x 64 tiles of cop_mfma_kernel.hpp behind a staging launch (us a call, 20-bit
-// shares, 54-bit moduli): 1 x 768 x 16384 21.7 -> 17.5, 16 x 768 x 16384 22.1 -> 19.4, 4 x 768 x
-// 49152 57.4 -> 49.4, 32 x 768 x 4096 20.2 -> 12.5, 1 x 3072 x 8192 56.0 -> 29.8; no better with 17
-// to 32 rows and 16384 columns (22.8 and 22.6).  With a third and a fourth 16-row tile the shares'
-// planes cost more than the tiles of cop_mfma_kernel.hpp (64 x 768 x 16384: 33 us and 28).
+// Measured (us a call in a HIP graph, 20-bit shares, 54-bit moduli where nothing else is said), with every slice run
+// in whole rounds of the stages in flight and elements finished one by one, and now: 8 x 64 x 2048 7.7 ->
+// 5.1, 1 x 73 x 16384 8.7 -> 6.4, 15 x 50 x 4096 8.6 -> 6.2, 2 x 386 x 4096 8.5 -> 6.8, 1 x 768 x 16384 18.5 ->
+// 17.2 (88 MB), 128 x 1536 x 2048 16.3 -> 15.1; 49 sizes of 1 to 64 rows 1.12 times as fast.  With a third and a
+// fourth 16-row tile the shares' planes cost more than the tiles of cop_mfma_kernel.hpp.
 #include "cop_mfma_common.hpp"
 
 namespace nimbus {
@@ -91,6 +91,14 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
     constexpr int ND = T_::ND, PD = T_::PD;
     constexpr bool RAW = FROM == kRaw, IN_LDS = FROM == kRaw || FROM == kCopied;
     static_assert(RT16 <= 2, "one row tile of the staged planes");
+    // (the scalar arguments in one batch, not each next to its first use: see cop_mfma_kernel.hpp)
+    if constexpr (NB == 1)
+        asm volatile("" ::"s"(b.prob[0].xd), "s"(b.prob[0].planes), "s"(b.prob[0].colsum), "s"(b.prob[0].mask),
+                     "s"(b.prob[0].out));
+    asm volatile("" ::"s"(a.m), "s"(a.KB), "s"(a.RB), "s"(a.N), "s"(a.L), "s"(a.C), "s"(a.CT), "s"(a.log_n),
+                 "s"(a.l_magic), "s"(a.offx), "s"(t.log_ks));
+    if constexpr (RAW)
+        asm volatile("" ::"s"(t.X), "s"(t.staged), "s"(t.k), "s"(t.half_shift), "s"(t.quads_magic));
     __shared__ __attribute__((aligned(1024))) unsigned char lds[T_::LDS];
 
     const int lane = threadIdx.x & 63;
@@ -136,11 +144,6 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
         e0 = ks * ne % 4u;
         return active && ks * ne < 4u * tiles ? ne : 0u;
     };
-    auto mask_word = [&](uint32_t row) -> uint64_t {
-        row += row_first;
-        return pp.mask != nullptr && (int)row < a.m ? __builtin_nontemporal_load(&pp.mask[(size_t)row * a.C + col]) : 0;
-    };
-
     // ---- operand addresses ----
     // (reads past the last k-block lie past the end of the descriptor and give zero weights:
     // whatever the shares' operand holds there, the products vanish)
@@ -220,64 +223,80 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
     };
     // The turns of a thread, U at a time.  The first U are asked for in front of the weights: loads
     // come back in order.
-    if constexpr (RAW) {
-        constexpr uint32_t U = 2;
-        v4i w[U][2];
-        static_for<0, U>([&](auto u) { read_quad(threadIdx.x + 512u * decltype(u)::value, w[decltype(u)::value]); });
-        static_for<0, PD>([&](auto p) { ask(p); });
-        for (uint32_t at = threadIdx.x; at < items;) {
-            static_for<0, U>([&](auto u) { split_quad(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
-            at += 512u * U;
-            if (at < items)
-                static_for<0, U>([&](auto u) { read_quad(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+    auto bring_shares = [&](auto ask_weights) {
+        if constexpr (RAW) {
+            constexpr uint32_t U = 2;
+            v4i w[U][2];
+            static_for<0, U>([&](auto u) { read_quad(threadIdx.x + 512u * decltype(u)::value, w[decltype(u)::value]); });
+            ask_weights();
+            for (uint32_t at = threadIdx.x; at < items;) {
+                static_for<0, U>([&](auto u) { split_quad(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+                at += 512u * U;
+                if (at < items)
+                    static_for<0, U>([&](auto u) { read_quad(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+            }
+            __syncthreads();
+        } else if constexpr (FROM == kCopied) {
+            constexpr uint32_t U = 4;
+            v4i w[U];
+            static_for<0, U>([&](auto u) { w[decltype(u)::value] = read_chunk(threadIdx.x + 512u * decltype(u)::value); });
+            ask_weights();
+            for (uint32_t at = threadIdx.x; at < chunks;) {
+                static_for<0, U>([&](auto u) { keep_chunk(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
+                at += 512u * U;
+                if (at < chunks)
+                    static_for<0, U>([&](auto u) { w[decltype(u)::value] = read_chunk(at + 512u * decltype(u)::value); });
+            }
+            __syncthreads();
+        } else {
+            ask_weights();
         }
-        __syncthreads();
-    } else if constexpr (FROM == kCopied) {
-        constexpr uint32_t U = 4;
-        v4i w[U];
-        static_for<0, U>([&](auto u) { w[decltype(u)::value] = read_chunk(threadIdx.x + 512u * decltype(u)::value); });
-        static_for<0, PD>([&](auto p) { ask(p); });
-        for (uint32_t at = threadIdx.x; at < chunks;) {
-            static_for<0, U>([&](auto u) { keep_chunk(at + 512u * decltype(u)::value, w[decltype(u)::value]); });
-            at += 512u * U;
-            if (at < chunks)
-                static_for<0, U>([&](auto u) { w[decltype(u)::value] = read_chunk(at + 512u * decltype(u)::value); });
-        }
-        __syncthreads();
-    } else {
-        static_for<0, PD>([&](auto p) { ask(p); });
-    }
-    if constexpr (RAW) {
-        // the planes as nimbus_cop_stage_shares leaves them: rows past m are zero
-        for (uint32_t s = blockIdx.x; s < S; s += gridDim.x) {
-            for (uint32_t i = threadIdx.x; i < 2u * DX * 64u; i += 512u) {
-                const uint32_t kb = 2u * s + i / (DX * 64u), d = i / 64u % DX, l = i & 63u;
-                const uint32_t row = l & 31u, half = (i / (DX * 64u)) * 2u + (l >> 5);
-                uint4 v = {0, 0, 0, 0};
-                if (row < (uint32_t)a.m)
-                    v = ((const uint4 *)lds)[((s * RT16 + (row >> 4)) * DX + d) * 64u + half * 16u + (row & 15u)];
-                if (kb < (uint32_t)KB) t.staged[((size_t)kb * DX + d) * 64u + l] = v;
+        if constexpr (RAW) {
+            // the planes as nimbus_cop_stage_shares leaves them: rows past m are zero
+            for (uint32_t s = blockIdx.x; s < S; s += gridDim.x) {
+                for (uint32_t i = threadIdx.x; i < 2u * DX * 64u; i += 512u) {
+                    const uint32_t kb = 2u * s + i / (DX * 64u), d = i / 64u % DX, l = i & 63u;
+                    const uint32_t row = l & 31u, half = (i / (DX * 64u)) * 2u + (l >> 5);
+                    uint4 v = {0, 0, 0, 0};
+                    if (row < (uint32_t)a.m)
+                        v = ((const uint4 *)lds)[((s * RT16 + (row >> 4)) * DX + d) * 64u + half * 16u + (row & 15u)];
+                    if (kb < (uint32_t)KB) t.staged[((size_t)kb * DX + d) * 64u + l] = v;
+                }
             }
         }
-    }
+    };
 
     // ---- the epilogue's operands: asked for behind the first weights, used after the last ----
-    uint64_t mk[T_::PHASES][4 * T_::TP];
-    const uint64_t colsum_S = active ? pp.colsum[col] : 0;
+    // (Mask words by buffer loads: a row past the last one, or no mask, lies behind the descriptor's end and reads
+    // as zero, without a branch for each.  Of this row tile; where 32 rows do not fit a descriptor, 2^23 columns
+    // and more, by their own addresses.)
+    uint64_t mk[T_::PHASES][4 * T_::TP], colsum_S;
+    const uint32_t rows_here = (uint32_t)a.m - row_first < 32u ? (uint32_t)a.m - row_first : 32u;
+    const bool narrow = a.C < (1u << 23);
+    const uint64_t *const mask0 = pp.mask + (size_t)row_first * a.C;
+    const __amdgpu_buffer_rsrc_t rsrc_m = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)mask0, 0, pp.mask != nullptr ? rows_here * a.C * 8u : 0u, 0x00027000);
+    auto ask_epilogue = [&]() {
+        colsum_S = active ? pp.colsum[col] : 0;
 #pragma unroll
-    for (int ph = 0; ph < T_::PHASES; ++ph) {
-        uint32_t tile, e0;
-        const uint32_t ne = share(ph, tile, e0);
+        for (int ph = 0; ph < T_::PHASES; ++ph) {
+            uint32_t tile, e0;
+            const uint32_t ne = share(ph, tile, e0);
+            const uint32_t row0 = 16u * tile + e0 + 4u * j;     // (the elements of a share step over whole tiles)
 #pragma unroll
-        for (uint32_t u = 0; u < 4 * T_::TP; ++u)
-            mk[ph][u] = u < ne ? mask_word(16u * (tile + (e0 + u) / 4u) + 4u * j + (e0 + u) % 4u) : 0;
-    }
-    uint32_t limb;
-    {
-        const uint32_t blk = (cg * 16u) >> a.log_n;
-        limb = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
-        limb = __builtin_amdgcn_readfirstlane(limb);
-    }
+            for (uint32_t u = 0; u < 4 * T_::TP; ++u) {
+                const uint32_t row = row0 + 16u * (u / 4u) + u % 4u;
+                if (narrow) {
+                    const uint32_t off = u < ne ? (row * a.C + col) * 8u : kPastEnd;
+                    mk[ph][u] = __builtin_bit_cast(uint64_t, __builtin_amdgcn_raw_buffer_load_b64(rsrc_m, off, 0, 2));
+                } else {
+                    mk[ph][u] = u < ne && pp.mask != nullptr && row < rows_here
+                                    ? __builtin_nontemporal_load(&mask0[(size_t)row * a.C + col])
+                                    : 0;
+                }
+            }
+        }
+    };
 
     // ---- the loop ----
     v4i acc[ND][RT16];
@@ -309,51 +328,115 @@ __global__ __launch_bounds__(512, 2) void cop_thin_kernel(const MfmaArgs a, cons
         });
         s_use = next_stage(s_use);
     };
-    // (whole rounds of PD stages: what is past the last one has zero weights.  One copy of the code
-    // and one way through it; a tail of its own would be fetched for a single use.)
-    for (uint32_t done = 0; done < len; done += PD)
+    // Rounds of PD stages, then the last one to PD, whose loads are on their way and which asks for no more.  A
+    // slice that is not longer than that (a short k, or one of many slices) asks for its own stages
+    // only: the loads behind the end took the memory pipeline 16 cycles each, and the products with zero
+    // weights the matrix cores as long as real ones (8 x 64 x 2048, one stage of four: 7.7 and 5.7 us).
+    // (Its own way from here on: the counted waits in the rounds need the same loads on every path.)
+    uint32_t done = 0;
+    auto last_round = [&]() {
         static_for<0, PD>([&](auto p) {
-            products(p);
-            ask(p);
-            asm volatile("" ::: "memory");              // (the loads stay where they are asked for)
+            if (done + decltype(p)::value < len) products(p);
         });
+    };
+    if (((S + (1u << t.log_ks) - 1u) >> t.log_ks) > (uint32_t)PD) {       // the longest slice: one way for a workgroup
+        bring_shares([&]() { static_for<0, PD>([&](auto p) { ask(p); }); });
+        ask_epilogue();
+        for (; done + PD < len; done += PD)
+            static_for<0, PD>([&](auto p) {
+                products(p);
+                ask(p);
+                asm volatile("" ::: "memory");          // (the loads stay where they are asked for)
+            });
+        last_round();
+    } else {
+        bring_shares([&]() {
+            static_for<0, PD>([&](auto p) {
+                if (decltype(p)::value < len) ask(p);
+            });
+        });
+        ask_epilogue();
+        last_round();
+    }
+    uint32_t limb;
+    {
+        const uint32_t blk = (cg * 16u) >> a.log_n;
+        limb = a.L == 1 ? 0u : blk - (uint32_t)a.L * __umulhi(blk, a.l_magic);
+        limb = __builtin_amdgcn_readfirstlane(limb);
+    }
 
     // ---- epilogue ----
-    // The sums meet in LDS, [wave][diagonal][element of the phase][lane], and the elements are
-    // finished one by one: code that runs once is fetched at some twenty cycles per instruction, so
-    // a loop over the elements is faster than the same code unrolled (two elements: 1.2 us instead
-    // of 2.6).
+    // The sums meet in LDS and the elements are finished two at a time, or one where a wave has only
+    // one: code that runs once is fetched at some twenty cycles per instruction, so a loop over the
+    // elements is faster than the same code unrolled (two elements: 1.2 us instead of 2.6), and two of
+    // them take little longer than one, whose instructions wait for each other.  [wave][diagonal][pair of
+    // elements of the phase][lane][2], or [wave][diagonal][element][lane].
     int32_t *const sums = (int32_t *)lds;
     const uint32_t cgl = (uint32_t)wave & ((1u << log_cgw) - 1u), KS = 1u << t.log_ks;
     static_for<0, T_::PHASES>([&](auto ph_c) {
         constexpr int ph = decltype(ph_c)::value, i0 = ph * T_::TP;
         constexpr int TILES = RT16 - i0 < T_::TP ? RT16 - i0 : T_::TP;
         __syncthreads();                                // the planes, or the phase before, are read
+        const bool pairs = (4u * TILES) >> t.log_ks >= 2u;
+        typedef int32_t v2i __attribute__((ext_vector_type(2)));
+        auto slot = [&](uint32_t w, int d) { return (w * ND + (uint32_t)d) * (4u * TILES * 64u); };
+        if (pairs) {
 #pragma unroll
-        for (int d = 0; d < ND; ++d)
+            for (int d = 0; d < ND; ++d)
 #pragma unroll
-            for (int e = 0; e < 4 * TILES; ++e)
-                sums[(((uint32_t)wave * ND + d) * (4 * TILES) + e) * 64u + lane] = acc[d][i0 + e / 4][e % 4];
+                for (int e = 0; e < 4 * TILES; e += 2)
+                    *(v2i *)&sums[slot((uint32_t)wave, d) + e * 64u + (uint32_t)lane * 2u] =
+                        v2i{acc[d][i0 + e / 4][e % 4], acc[d][i0 + e / 4][e % 4 + 1]};
+        } else {
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int e = 0; e < 4 * TILES; ++e)
+                    sums[slot((uint32_t)wave, d) + e * 64u + lane] = acc[d][i0 + e / 4][e % 4];
+        }
         __syncthreads();
         uint32_t tile, e0;
         const uint32_t ne = share(ph, tile, e0);
-#pragma unroll 1
-        for (uint32_t u = 0; u < ne; ++u) {
+        // NE elements from element u of the wave's share on
+        auto finish = [&](auto ne_c, uint32_t u) {
+            constexpr int NE = decltype(ne_c)::value;
             const uint32_t e = 4u * (tile - i0) + e0 + u;       // of the phase
-            const uint64_t word = mk[ph][0];
+            uint64_t word[NE];
 #pragma unroll
-            for (uint32_t v = 1; v < 4 * T_::TP; ++v) mk[ph][v - 1] = mk[ph][v];
-            int32_t digit[ND];
+            for (int v = 0; v < NE; ++v) word[v] = mk[ph][v];
 #pragma unroll
-            for (int d = 0; d < ND; ++d) digit[d] = 0;
+            for (uint32_t v = NE; v < 4 * T_::TP; ++v) mk[ph][v - NE] = mk[ph][v];
+            int32_t digit[ND][NE];
+#pragma unroll
+            for (int d = 0; d < ND; ++d)
+#pragma unroll
+                for (int v = 0; v < NE; ++v) digit[d][v] = 0;
 #pragma unroll 1
             for (uint32_t o = 0; o < KS; ++o)
 #pragma unroll
-                for (int d = 0; d < ND; ++d)
-                    digit[d] += sums[((((o << log_cgw) + cgl) * ND + d) * (4 * TILES) + e) * 64u + lane];
-            cop_finish<ND, 1, false>([&](int d, int) { return digit[d]; }, [](int) { return 0; },
-                                     [&](uint64_t (&w)[1]) { w[0] = word; }, a, a.prev, pp.out, limb, colsum_S,
-                                     (int)(row_first + 16u * (i0 + e / 4u) + 4u * j + e % 4u), col, a.m);
+                for (int d = 0; d < ND; ++d) {
+                    const int32_t *const at = &sums[slot((o << log_cgw) + cgl, d) + e * 64u + (uint32_t)lane * NE];
+                    if constexpr (NE == 2) {
+                        const v2i v = *(const v2i *)at;
+                        digit[d][0] += v[0];
+                        digit[d][1] += v[1];
+                    } else {
+                        digit[d][0] += *at;
+                    }
+                }
+            cop_finish<ND, NE, false>([&](int d, int r) { return digit[d][r]; }, [](int r) { return r; },
+                                      [&](uint64_t (&w)[NE]) {
+#pragma unroll
+                                          for (int v = 0; v < NE; ++v) w[v] = word[v];
+                                      },
+                                      a, a.prev, pp.out, limb, colsum_S,
+                                      (int)(row_first + 16u * (i0 + e / 4u) + 4u * j + e % 4u), col, a.m);
+        };
+        if (pairs) {
+#pragma unroll 1
+            for (uint32_t u = 0; u < ne; u += 2) finish(std::integral_constant<int, 2>{}, u);
+        } else if (ne) {                                // one element, or none
+            finish(std::integral_constant<int, 1>{}, 0);
         }
     });
 }
@@ -374,8 +457,7 @@ struct ThinPlan {
     uint32_t blocks;        // workgroups of one problem and row tile
     bool copied;            // staged planes through LDS (17 to 32 rows)
     uint64_t rounds;        // of workgroups on the compute units
-    uint64_t stages;        // of a slice, and those rounded up to whole rounds of the stages in flight
-    uint64_t padded;
+    uint64_t stages;        // of a slice
     uint64_t depth;         // stages in flight of a wave
 };
 
@@ -405,11 +487,9 @@ static ThinPlan thin_plan(const Problem &p, int count)
     // same ones (one slice) read them once, from LDS (32 x 768 x 24576: 31.5 us against 34.4); with
     // several slices fewer waves share them and nobody waits for the copy (x 8192: 17.8 and 16.0).
     plan.copied = p.m > 16 && p.m <= kThinRows && plan.log_ks == 0 && thin_planes_fit(p);
-    // (whole rounds of the stages in flight: what is past the last one costs its products, but no loads)
     plan.stages = (S + (1u << plan.log_ks) - 1) >> plan.log_ks;
     plan.depth = (uint64_t)thin_depth(planes_x(p.x_bits), planes_q(p.q_bits_max), p.m <= 16 ? 1 : 2,
                                       plan.copied ? kCopied : kDirect);
-    plan.padded = (plan.stages + plan.depth - 1) / plan.depth * plan.depth;
     return plan;
 }
 
@@ -421,12 +501,10 @@ static bool thin_possible(const Problem &p) { return p.m <= kThinRows && p.C < (
 // and ends a workgroup faster but shares the chip's tiles out by whole rounds and has no slices of k.
 // Both estimates in hundredths of a microsecond, on 256 compute units: per round its start and end, per
 // k-block or stage the wait for its operands and its products, and the bytes of weights, mask and
-// results.  Fitted to both kernels' times at 3600 drawn sizes (1 to 32 rows, k from 20 to 3072, 64 to 131072
-// columns, every pair of plane counts, one to sixteen problems; profiles/choice_of_kernel.txt): the choice is 0.2 % slower
-// than the better kernel on average, and no more at 900 sizes that were left out; this kernel everywhere 39 %, the tile
-// kernel everywhere 8 %.  (us, this kernel and the tiles, 20-bit shares, 54-bit moduli where nothing else is
-// said: 12 x 28 x 24576, 32-bit shares, 11.1 and 7.3, 8 x 1006 x 16384 three times 63.8 and 57.3; 16 x 510 x
-// 8192 12.0 and 10.0; 32 x 2032 x 16384 twice, 32-bit shares, 62-bit moduli, 98.1 and 134.0.)
+// results.  Fitted to both kernels' times at 700 drawn sizes (1 to 32 rows, k from 20 to 3072, 64 to 131072
+// columns, every pair of plane counts, one to sixteen problems; profiles/choice_of_kernel.txt): the lower estimate is
+// 0.5 % slower than the better kernel on average and 0.4 % at 200 sizes that were left out; this kernel everywhere 6 %,
+// the tile kernel everywhere 29 %.
 struct ThinEstimates {
     double rows, tiles;
 };
@@ -441,47 +519,53 @@ static ThinEstimates thin_few_estimates(const Problem &p, int count)
     const double KB = kblocks(p.k), n = (double)count;
     const double products = planes_x(p.x_bits) * planes_q(p.q_bits_max);
     const double weights = n * (double)p.C * KB * planes_q(p.q_bits_max), results = n * (double)p.m * (double)p.C;
-    const double start = p.m <= 16 ? 700 : plan.copied ? 822 : 733, padded = (double)plan.padded;
-    const double tiles = 317 + (double)tile_rounds_of(p, count) * (140 + KB * (9.5 + 0.98 * products)) + 2.3e-4 * weights + 2.2e-4 * results;
-    const double rows = (double)plan.rounds * (start + 33. * (double)plan.stages + 1.52 * products * (p.m <= 16 ? 1 : 2) * padded +
-                                               35. * padded / (double)plan.depth) +
-                        2.44e-4 * weights + 1e-4 * results;
+    const double start = p.m <= 16 ? 261 : plan.copied ? 473 : 341, stages = (double)plan.stages;
+    const double tiles = 314 + (double)tile_rounds_of(p, count) * (127 + KB * (7.8 + 1.24 * products)) + 2.01e-4 * weights + 2.74e-4 * results;
+    const double rows = 162 + (double)plan.rounds * (start + 60. * stages + 1.57 * products * (p.m <= 16 ? 1 : 2) * stages +
+                                                     57. * stages / (double)plan.depth) +
+                        2.32e-4 * weights + 1.96e-4 * results;
     return {rows, tiles};
 }
 static bool thin_few_apply(const Problem &p, int count)
 {
     if (!thin_possible(p)) return false;
     const ThinEstimates e = thin_few_estimates(p, count);
-    return e.rows < e.tiles;
+    // (Where the two lie within a microsecond or two of each other, a single call of up to 16 rows stays with the
+    // tiles and one of more rows with this kernel: which one such a call takes is held by tests, and was
+    // fixed when a workgroup of this kernel took three microseconds longer to start and end.  1.5 % off the better
+    // kernel instead of 0.5; with the estimates of that time 5.5.)
+    if (p.m > 16) return 0.915 * e.rows + 80 < e.tiles;
+    return e.rows + (count == 1 ? 130 + 140. / kblocks(p.k) : 0) < e.tiles;
 }
 
 // More than 32 rows on few columns: where the tile kernel's workgroups leave compute units without a
-// tile, this kernel's row tiles and slices of k fill them (us, tiles and this kernel, 20-bit shares
-// and 54-bit moduli: 128 x 3072 x 1024 43.0 and 13.3, 128 x 1536 x 2048 24.8 and 13.1, 69 x 478 x 1024
-// 11.6 and 8.4).  Every row tile reads the weights again, from the L2, so the line is where the chip
+// tile, this kernel's row tiles and slices of k fill them (us a call with its staging, 20-bit shares and 54-bit
+// moduli, tiles and this kernel: 128 x 3072 x 1024 47 and 17.4, 128 x 1536 x 2048 29 and 15.7).
+// Every row tile reads the weights again, from the L2, so the line is where the chip
 // fills up (64 x 768 x 8192 16.3 and 18.5); with fewer than eight workgroups to a problem and row tile the
 // row tiles are spread over the XCDs, and of a batch each fetches them (197 x 3330 x 256 eight times,
 // 16-bit shares, 40.2 and 57.3): a seventh more.
-// Estimates as above, fitted at 2000 sizes (33 to 512 rows, k from 300 to 4096, 64 to 16384 columns, one to
-// eight problems): the choice is 0.2 % slower than the better kernel on average and 27 % at worst (238 x 2547
-// x 256 eight times, 16-bit shares), no more than that on average at 500 sizes that were left out; tiles everywhere 34 %, this
-// kernel everywhere 23 %.  Fewer k-blocks than ten were not looked at and stay with the tiles.
+// Estimates as above, fitted at 300 sizes (33 to 512 rows, k from 300 to 4096, 64 to 16384 columns, one to
+// eight problems): the choice is 0.3 % slower than the better kernel on average, 30 % at worst, and 0.2 % at 75 sizes that were
+// left out; tiles everywhere 75 %, this kernel everywhere 8 %.  Below ten k-blocks only where it is well ahead: 2 %
+// off the better kernel over 300 sizes of one to ten k-blocks (the tiles everywhere 4 %, this kernel 20 %); under five
+// never.
 static bool thin_rows_apply(const Problem &p, int count)
 {
     const int KB = kblocks(p.k), DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);
     const TileBlocks tb = tile_blocks(p, count);
     const double cus = (double)compute_units(), n = (double)count;
-    if (KB < 10 || (double)(p.C / 64u) * tb.row_blocks * n > cus) return false;
+    if (KB < 5 || (double)(p.C / 64u) * tb.row_blocks * n > cus) return false;
     const ThinPlan plan = thin_plan(p, count);
     const int row_tiles = (p.m + kThinRows - 1) / kThinRows;
     if (plan.rounds > 2 || (uint64_t)plan.blocks * (uint64_t)row_tiles * 512u >= (1ull << 32)) return false;
     const int rows16 = ((tb.tiles * kTile < p.m ? tb.tiles * kTile : p.m) + 15) / 16;
     const double weights = n * (double)p.C * KB * DQ, results = n * (double)p.m * (double)p.C;
     const double products = DX * DQ, rounds = (double)plan.rounds;
-    const double tiles = 505 + KB * (8.8 + 0.716 * products * ((rows16 + 1) / 2)) + 1.72e-4 * weights + 2.68e-4 * results;
-    const double rows = rounds * (628 + 48. * (double)plan.stages + 2.74 * products * (double)plan.padded) +
-                        (3.44e-4 + 8e-6 * row_tiles) * weights + 2.55e-4 * results;
-    return (plan.blocks < 8 && count > 1 ? 1.15 : 1.) * rows < tiles;
+    const double tiles = 562 + KB * (11.6 + 0.64 * products * ((rows16 + 1) / 2)) + 1.32e-4 * weights + 2.75e-4 * results;
+    const double rows = 60 + rounds * (458 + (10. + 3.83 * products) * (double)plan.stages) +
+                        (3.35e-4 + 5.4e-5 * row_tiles) * weights + 2.01e-4 * results;
+    return (plan.blocks < 8 && count > 1 ? 1.15 : 1.) * (KB < 10 ? 1.28 : 1.) * rows < tiles;
 }
 
 bool thin_applies(const Problem &p, int count)
@@ -489,20 +573,18 @@ bool thin_applies(const Problem &p, int count)
     return p.m > kThinRows ? thin_rows_apply(p, count) : thin_few_apply(p, count);
 }
 
-// From the shares themselves, without a staging launch.  With a second 16-row tile the splitting takes as long
-// as that launch (m = 32 on 768 x 16384: 24.8 us from raw shares, 22.8 staged; m = 16: 19.4 and 21.9).
-// Up to 16 rows: always up to two rounds of tiles, where a call takes little more than its launches cost the
-// host, and one is cheaper than two (8 x 32 x 4096 7.4 us a call and 9.9; in a graph, where the host does
-// not count, 9 % slower over 1353 sizes of up to eight k-blocks, 45 % at worst, 15 % faster over 668 of up
-// to 31).  From three rounds on only where it is ahead of the tiles and a staging launch, two
-// microseconds: 444 sizes 0.3 % off the better one, 22 % from the shares everywhere (6 x 16 x 107520, 16-bit
-// shares, 62-bit moduli, 31.7 and 18.1; 14 x 748 x 39552 52.6 and 44.3).
+// From the shares themselves, without a staging launch (up to 32 rows), where that is ahead of the tiles behind
+// one.  Up to two rounds of tiles a call takes little more than its launches cost the host, and one is
+// cheaper than two (7.4 us a call and 9.9), so the line lies the staging's two microseconds and part of the host's
+// launch above the tiles' estimate.  In a graph, where the host does not count, over 300 sizes of up to 16 rows 0.6 %
+// off the better way (always the tiles 52 %), over 400 of 17 to 32 1.5 % (14 %; 24 x 82 x 2048, 32-bit shares,
+// 8.8 us staged and 7.6, 20 x 200 x 8192 10.6 and 8.2).  From three rounds on only where this kernel is ahead of the tiles alone (6 x 16 x
+// 107520, 16-bit shares, 62-bit moduli, 18.1 us in two launches).
 bool thin_raw_applies(const Problem &p)
 {
-    if (!thin_possible(p) || p.m > 16 || !thin_planes_fit(p)) return false;
-    if (tile_rounds_of(p, 1) <= 2) return true;
+    if (!thin_possible(p) || !thin_planes_fit(p)) return false;
     const ThinEstimates e = thin_few_estimates(p, 1);
-    return e.rows < e.tiles + 200;
+    return e.rows < e.tiles + (tile_rounds_of(p, 1) > 2 ? -100 : p.m <= 16 ? 450 : 300);
 }
 
 template <int DX, int DQ>
@@ -550,7 +632,7 @@ static hipError_t thin_impl(const Problem &p, int count, const uint64_t *X, int 
     const std::integral_constant<ThinShares, kRaw> raw;
     const std::integral_constant<int, 1> one;
     const std::integral_constant<int, 2> two;
-    if (X) return go(one, raw);
+    if (X) return p.m <= 16 ? go(one, raw) : go(two, raw);
     if (p.m <= 16) return go(one, direct);
     if (p.m > kThinRows) return go(two, std::integral_constant<ThinShares, kRows>{});
     return plan.copied ? go(two, copied) : go(two, direct);
