@@ -12,6 +12,7 @@ import os
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libnimbus_cop.so"
 _lib = None
+_calls = None         # the entry points that run per layer, without ctypes (csrc/calls.cpp)
 NIMBUS_INVALID = -1
 
 EXPORTED_SYMBOLS = (
@@ -69,7 +70,7 @@ def lib_path() -> str:
 
 def load_library():
     """dlopen the HIP library; raises if it has not been built"""
-    global _lib
+    global _lib, _calls
     if _lib is not None:
         return _lib
     path = lib_path()
@@ -80,7 +81,7 @@ def load_library():
     # The library launches on PyTorch's streams and pointers, so both must use one and the
     # same HIP runtime: PyTorch ships its own copy and loads it by path, and whichever copy
     # is mapped first serves every later request for that soname.  Import torch first.
-    import torch  # noqa: F401
+    import torch
     lib = ctypes.CDLL(path)
     vp, ci, sz = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t
     lib.nimbus_cop_matmul.restype = ci
@@ -147,7 +148,16 @@ def load_library():
     lib.nimbus_cop_strerror.argtypes = [ci]
     lib.nimbus_cop_version.restype = ci
     lib.nimbus_cop_version.argtypes = []
-    _lib = lib
+    # (the order of Entries in csrc/calls.cpp)
+    entries = (lib.nimbus_cop_matmul, lib.nimbus_cop_prepare, lib.nimbus_cop_workspace_bytes, lib.nimbus_cop_matmul_prepared,
+               lib.nimbus_cop_stage_shares_batch, lib.nimbus_cop_matmul_staged_batch, lib.nimbus_cop_packed_count,
+               lib.nimbus_cop_pack, lib.nimbus_rlwe_decrypt, lib.nimbus_rlwe_encrypt)
+    from . import _calls as calls       # raises if it has not been built
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    calls.bind(tuple(ctypes.cast(f, vp).value for f in entries),
+               getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device),
+               raw or (lambda device: torch.cuda.current_stream(device).cuda_stream))
+    _calls, _lib = calls, lib
     return lib
 
 
@@ -200,6 +210,14 @@ def _stream(stream):
     return stream.cuda_stream
 
 
+# The calls below that go to _calls first come back from it with their status, or with None where the
+# arguments are not the ordinary ones (nothing has been launched then): the rest of the function checks
+# them one by one and raises, or calls through ctypes.
+def _done(rc, where):
+    if rc != 0:
+        raise NimbusCopError(rc, where)
+
+
 def _columns(n, N, L):
     return (-(-n // N)) * 2 * L * N
 
@@ -228,6 +246,11 @@ def _canonical(entry, X, m, k, x_bits, ctW, n, N, L, moduli, mask, out, stream):
 
 
 def nimbus_cop_matmul(X, m, k, x_bits, ctW, n, N, L, moduli, mask, out, stream=None):
+    if _calls is None:
+        load_library()
+    rc = _calls.matmul(X, m, k, x_bits, ctW, n, N, L, moduli, mask, out, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_cop_matmul")
     _canonical("nimbus_cop_matmul", X, m, k, x_bits, ctW, n, N, L, moduli, mask, out, stream)
 
 
@@ -240,6 +263,11 @@ def nimbus_cop_prepared_bytes(k, n, N, L, moduli) -> int:
 
 
 def nimbus_cop_prepare(ctW, k, n, N, L, moduli, prepared, stream=None):
+    if _calls is None:
+        load_library()
+    rc = _calls.prepare(ctW, k, n, N, L, moduli, prepared, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_cop_prepare")
     lib = load_library()
     _words(ctW, "ctW", k * _columns(n, N, L))
     nbytes = prepared.numel() * prepared.element_size()
@@ -281,6 +309,11 @@ def nimbus_cop_matmul_staged(staged, m, k, x_bits, prepared, n, N, L, moduli, ma
 
 def nimbus_cop_stage_shares_batch(Xs, m, k, x_bits, workspaces, stream=None):
     """nimbus_cop_stage_shares for several share matrices of one shape in one launch"""
+    if _calls is None:
+        load_library()
+    rc = _calls.stage_shares_batch(Xs, m, k, x_bits, workspaces, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_cop_stage_shares_batch")
     lib = load_library()
     count = len(Xs)
     if len(workspaces) != count:
@@ -300,6 +333,11 @@ def nimbus_cop_matmul_staged_batch(staged, m, k, x_bits, prepared, n, N, L, modu
                                    stream=None):
     """`len(outs)` calls of nimbus_cop_matmul_staged in one launch; staged, prepared, masks (or
     None) and outs are sequences of tensors, one per problem"""
+    if _calls is None:
+        load_library()
+    rc = _calls.matmul_staged_batch(staged, m, k, x_bits, prepared, n, N, L, moduli, masks, outs, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_cop_matmul_staged_batch")
     lib = load_library()
     count = len(outs)
     if len(staged) != count or len(prepared) != count or (masks is not None and len(masks) != count):
@@ -325,6 +363,11 @@ def nimbus_cop_matmul_staged_batch(staged, m, k, x_bits, prepared, n, N, L, modu
 
 def nimbus_cop_matmul_prepared(X, m, k, x_bits, prepared, n, N, L, moduli, mask, out,
                                workspace, stream=None):
+    if _calls is None:
+        load_library()
+    rc = _calls.matmul_prepared(X, m, k, x_bits, prepared, n, N, L, moduli, mask, out, workspace, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_cop_matmul_prepared")
     lib = load_library()
     C = _columns(n, N, L)
     _words(X, "X", m * k)
@@ -361,6 +404,11 @@ def nimbus_cop_packed_count(m, n, N) -> int:
 
 
 def nimbus_cop_pack(rows, m, n, N, L, moduli, mask, packed, stream=None):
+    if _calls is None:
+        load_library()
+    rc = _calls.pack(rows, m, n, N, L, moduli, mask, packed, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_cop_pack")
     lib = load_library()
     T = nimbus_cop_packed_count(m, n, N)
     _words(rows, "rows", m * 2 * L * N)
@@ -486,6 +534,11 @@ def nimbus_rlwe_decode(phi, T, N, L, moduli, t_bits, m_hat, stream=None):
 
 
 def nimbus_rlwe_decrypt(ct, T, N, L, moduli, t_bits, tables, phi, m_hat, stream=None):
+    if _calls is None:
+        load_library()
+    rc = _calls.decrypt(ct, T, N, L, moduli, t_bits, tables, phi, m_hat, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_rlwe_decrypt")
     lib = load_library()
     _words(ct, "ct", T * 2 * L * N)
     _words(phi, "phi", T * L * N)
@@ -498,6 +551,11 @@ def nimbus_rlwe_decrypt(ct, T, N, L, moduli, t_bits, tables, phi, m_hat, stream=
 
 
 def nimbus_rlwe_encrypt(W, k, n, t_bits, N, L, moduli, tables, a, e, ctW, stream=None):
+    if _calls is None:
+        load_library()
+    rc = _calls.encrypt(W, k, n, t_bits, N, L, moduli, tables, a, e, ctW, stream)
+    if rc is not None:
+        return _done(rc, "nimbus_rlwe_encrypt")
     lib = load_library()
     Ch = -(-n // N)
     _words(W, "W", k * n)

@@ -1,4 +1,5 @@
-"""Compile the HIP sources under csrc/ into paper_2411_15707_amd/libnimbus_cop.so (gfx950)."""
+"""Compile the HIP sources under csrc/ into paper_2411_15707_amd/libnimbus_cop.so (gfx950), and the module that
+calls it from Python without ctypes (csrc/calls.cpp) into paper_2411_15707_amd/_calls.so."""
 import concurrent.futures
 import glob
 import os
@@ -9,6 +10,7 @@ import tempfile
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnimbus_cop.so")
+CALLS = os.path.join(HERE, "_calls.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -21,6 +23,19 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def build_calls() -> str:
+    import sysconfig
+    from torch.utils import cpp_extension
+    flags = ["-std=c++17", "-O2", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden"]
+    for path in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
+        flags += ["-isystem", path]
+    # (torch's own libraries are in the process already when the module is imported)
+    links = ["-L" + path for path in cpp_extension.library_paths()] + ["-ltorch_python", "-ltorch_cpu", "-lc10"]
+    cxx = os.environ.get("CXX", "g++")
+    subprocess.run([cxx] + flags + ["-o", CALLS, os.path.join(CSRC, "calls.cpp")] + links, check=True)
+    return CALLS
+
+
 def build(extra_flags=()) -> str:
     """one object per source, compiled side by side, then one link"""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -30,8 +45,10 @@ def build(extra_flags=()) -> str:
             obj = os.path.join(tmp, os.path.basename(src) + ".o")
             subprocess.run([hipcc] + HIPCC_FLAGS + list(extra_flags) + ["-c", "-o", obj, src], check=True)
             return obj
-        with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs))) as pool:
+        with concurrent.futures.ThreadPoolExecutor(max_workers=min(8, len(srcs) + 1)) as pool:
+            calls = pool.submit(build_calls)
             objs = list(pool.map(compile_one, srcs))
+            calls.result()
         subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB] + objs, check=True)
     return LIB
 
