@@ -51,3 +51,14 @@ def test_prepared_weights_have_the_documented_layout(k, n, N, L, q_bits):
     assert got.size == tiles.size + 8 * sums.size
     assert np.array_equal(got[tiles.size:].view(np.uint64), sums)
     assert np.array_equal(got[:tiles.size], tiles)
+
+
+# where the waves per tile and the columns per workgroup change: 4 / 5, 8 / 9, 16 / 17 k-blocks and an
+# odd number of them (a workgroup of half a tile takes pairs); 128 column tiles, 132, 256, 264 and 1024
+@pytest.mark.parametrize("k,n,N,L,q_bits", [
+    (128, 32, 32, 1, 54), (129, 32, 32, 1, 62), (250, 64, 64, 2, 59), (257, 2048, 1024, 1, 54),
+    (530, 33, 32, 1, 54), (1100, 64, 32, 2, 62), (160, 2048, 2048, 1, 54), (161, 2080, 32, 1, 54),
+    (192, 4096, 4096, 1, 62), (200, 4200, 64, 1, 54), (300, 4096, 4096, 1, 59), (257, 16384, 8192, 1, 54),
+])
+def test_prepared_weights_where_the_split_changes(k, n, N, L, q_bits):
+    test_prepared_weights_have_the_documented_layout(k, n, N, L, q_bits)
