@@ -101,13 +101,18 @@ struct Args {
     void *stream(Py_ssize_t i)
     {
         if (!ok) return nullptr;
-        if (PyLong_CheckExact(arg[i])) return PyLong_AsVoidPtr(arg[i]);
-        if (arg[i] != Py_None) return fail();
-        PyObject *const device = PyObject_CallNoArgs(current_device);
-        PyObject *const handle = device ? PyObject_CallOneArg(raw_stream, device) : nullptr;
-        void *const s = handle ? PyLong_AsVoidPtr(handle) : nullptr;
-        Py_XDECREF(device);
-        Py_XDECREF(handle);
+        void *s = nullptr;
+        if (PyLong_CheckExact(arg[i])) {
+            s = PyLong_AsVoidPtr(arg[i]);
+        } else if (arg[i] == Py_None) {
+            PyObject *const device = PyObject_CallNoArgs(current_device);
+            PyObject *const handle = device ? PyObject_CallOneArg(raw_stream, device) : nullptr;
+            if (handle) s = PyLong_AsVoidPtr(handle);
+            Py_XDECREF(device);
+            Py_XDECREF(handle);
+        } else {
+            return fail();
+        }
         if (PyErr_Occurred()) {
             PyErr_Clear();
             return fail();
