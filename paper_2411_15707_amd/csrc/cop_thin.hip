@@ -533,9 +533,9 @@ static bool thin_few_apply(const Problem &p, int count)
     // (Where the two lie within a microsecond or two of each other, a single call of up to 16 rows stays with the
     // tiles and one of more rows with this kernel: which one such a call takes is held by tests, and was
     // fixed when a workgroup of this kernel took three microseconds longer to start and end.
-    // 17 to 32 rows, one problem: where tiles about fill their last round (more so if the planes are not copied) this kernel has to
-    // be ahead by the second line too (31 x 1329 x 32768 55.7 us with the tiles and 61.8; 24 x 987 x 24576, whose last
-    // round of tiles is half empty, 43.8 and 39.1).  0.5 % off the better kernel at 650 sizes; 1.1 % without that line.)
+    // 17 to 32 rows, one problem: where tiles about fill their last round, this kernel has to be ahead by the last
+    // condition too (31 x 1329 x 32768 55.7 us with the tiles and 61.8; 24 x 987 x 24576, whose last
+    // round of tiles is half empty, 43.8 and 39.1).  0.5 % off the better kernel at 650 sizes; 1.1 % without it.)
     if (p.m > 16) {
         const ThinPlan plan = thin_plan(p, count);
         const double idle = 1. - (double)(p.C / 64u) * count / ((double)tile_rounds_of(p, count) * compute_units());
@@ -586,10 +586,10 @@ bool thin_applies(const Problem &p, int count)
 // launch above the tiles' estimate.  In a graph, where the host does not count, over 300 sizes of up to 16 rows 0.6 %
 // off the better way (always the tiles 52 %).  From three rounds on only where this kernel is ahead of the tiles alone
 // (6 x 16 x 107520, 16-bit shares, 62-bit moduli, 18.1 us in two launches).
-// 17 to 32 rows: every workgroup splits all shares, which takes as long as the launch that it saves at some
-// 180 k of 32-bit shares (31 x 610 x 16384, 24-bit shares, 23.8 us and staged 19.1; 24 x 82 x 2048, 32-bit, 7.6 and
+// 17 to 32 rows: every workgroup splits all shares, which takes as long as the launch that it saves at a k of
+// some 600 with 32-bit shares (31 x 610 x 16384, 24-bit shares, 23.8 us and staged 19.1; 24 x 82 x 2048, 32-bit, 7.6 and
 // 8.8; 20 x 200 x 8192 8.2 and 10.6).  In a graph over 330 sizes 0.5 % off the better way, 10 % at worst (2 % and 26 %
-// without that term, staged everywhere 5 %, from the shares everywhere 9 %).
+// without that term, staged everywhere 7 %, from the shares everywhere 4 %).
 bool thin_raw_applies(const Problem &p)
 {
     if (!thin_possible(p) || !thin_planes_fit(p)) return false;
