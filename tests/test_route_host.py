@@ -114,6 +114,21 @@ def test_few_rows_take_the_faster_kernel(m, k, C, x_bits, count, kernel):
     assert kernels(lines) == [kernel]
 
 
+# 17 to 32 rows from the shares themselves: split in the kernel, or staged and one kernel or the other (us, split
+# in the kernel / staged: 7.6 / 8.8, 8.2 / 10.6, 23.8 / 19.1; the kernel for few rows / the tiles: 61.8 / 55.7,
+# 39.1 / 43.8)
+@pytest.mark.parametrize("m,k,C,x_bits,launched", [
+    (24, 82, 2048, 32, ["cop_thin_kernel"]), (20, 200, 8192, 20, ["cop_thin_kernel"]),
+    (31, 610, 16384, 24, ["x_planes_kernel", "cop_mfma_kernel"]),
+    (31, 1329, 32768, 24, ["x_planes_kernel", "cop_mfma_kernel"]),
+    (24, 987, 24576, 32, ["x_planes_kernel", "cop_thin_kernel"]),
+])
+def test_17_to_32_rows_take_the_faster_way(m, k, C, x_bits, launched):
+    n = C // 4                                      # (two limbs)
+    lines = nc.nimbus_route_matmul(m, k, x_bits, n, n & -n, 2, moduli_of(54, 2), units=256)
+    assert kernels(lines) == launched
+
+
 # m, k, C, and the kernels from the shares themselves (us, split in the kernel / staged and tiles, replayed from
 # a graph: 31.7 / 18.1, 52.6 / 44.3; one launch where a call takes little more than that)
 @pytest.mark.parametrize("m,k,C,x_bits,q_bits,expected", [
