@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_NAME = "libnimbus_cop.so"
@@ -66,6 +67,26 @@ class NimbusCopError(RuntimeError):
 
 def lib_path() -> str:
     return os.path.join(_HERE, _LIB_NAME)
+
+
+class _NoCalls:
+    """in the place of _calls: takes no call, so that every one of them goes through ctypes"""
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _native_calls(torch):
+    """The module of csrc/calls.cpp.  It is built for one interpreter and one torch, whose tensors it looks
+    into; without it, or with another one's, the calls lose 2 us of the host's time and nothing else."""
+    try:
+        from . import _calls as calls
+        if calls.torch_version == torch.__version__:
+            return calls
+        why = f"built for torch {calls.torch_version}, this is {torch.__version__}"
+    except (ImportError, AttributeError) as e:
+        why = str(e)
+    warnings.warn(f"the per-layer entry points go through ctypes: {why}", RuntimeWarning, stacklevel=3)
+    return _NoCalls()
 
 
 def load_library():
@@ -152,7 +173,7 @@ def load_library():
     entries = (lib.nimbus_cop_matmul, lib.nimbus_cop_prepare, lib.nimbus_cop_workspace_bytes, lib.nimbus_cop_matmul_prepared,
                lib.nimbus_cop_stage_shares_batch, lib.nimbus_cop_matmul_staged_batch, lib.nimbus_cop_packed_count,
                lib.nimbus_cop_pack, lib.nimbus_rlwe_decrypt, lib.nimbus_rlwe_encrypt)
-    from . import _calls as calls       # raises if it has not been built
+    calls = _native_calls(torch)
     raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
     calls.bind(tuple(ctypes.cast(f, vp).value for f in entries),
                getattr(torch._C, "_cuda_getDevice", torch.cuda.current_device),

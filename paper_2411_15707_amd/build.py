@@ -1,16 +1,17 @@
 """Compile the HIP sources under csrc/ into paper_2411_15707_amd/libnimbus_cop.so (gfx950), and the module that
-calls it from Python without ctypes (csrc/calls.cpp) into paper_2411_15707_amd/_calls.so."""
+calls it from Python without ctypes (csrc/calls.cpp) into paper_2411_15707_amd/_calls<suffix of the interpreter>."""
 import concurrent.futures
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libnimbus_cop.so")
-CALLS = os.path.join(HERE, "_calls.so")
+CALLS = os.path.join(HERE, "_calls" + sysconfig.get_config_var("EXT_SUFFIX"))     # (of one interpreter)
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -24,9 +25,10 @@ def sources():
 
 
 def build_calls() -> str:
-    import sysconfig
+    import torch
     from torch.utils import cpp_extension
-    flags = ["-std=c++17", "-O2", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden"]
+    flags = ["-std=c++17", "-O2", "-Wall", "-fPIC", "-shared", "-fvisibility=hidden",
+             f'-DNIMBUS_TORCH_VERSION="{torch.__version__}"']
     for path in cpp_extension.include_paths() + [sysconfig.get_paths()["include"]]:
         flags += ["-isystem", path]
     # (torch's own libraries are in the process already when the module is imported)

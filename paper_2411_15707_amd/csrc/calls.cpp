@@ -303,4 +303,13 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_calls", nullptr, -1, methods, nul
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__calls(void) { return PyModule_Create(&module); }
+// torch_version: the torch whose tensors this file was compiled to look into (binding.py compares it)
+PyMODINIT_FUNC PyInit__calls(void)
+{
+    PyObject *const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", NIMBUS_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -1,10 +1,16 @@
 """The entry points called without ctypes (csrc/calls.cpp): they answer None for every call that is not the
 ordinary one, before anything is launched, and the binding then refuses or accepts it as ever."""
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
 import paper_2411_15707_amd as nc
 from paper_2411_15707_amd import binding
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 def _arguments():
@@ -67,3 +73,41 @@ def test_the_binding_refuses_what_it_refused():
     nc.nimbus_cop_matmul_prepared(**good, stream=side)
     nc.nimbus_cop_matmul_prepared(**good, stream=side.cuda_stream)
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("missing", ["sys.modules['paper_2411_15707_amd._calls'] = None",
+                                     "import types; sys.modules['paper_2411_15707_amd._calls'] = types.ModuleType('_calls')",
+                                     "import torch; torch.__version__ = '1.0'"])
+def test_without_the_native_module_calls_go_through_ctypes(missing):
+    """not built, another file of that name, built for another torch: the library loads all the same, with a warning"""
+    code = f"""
+import sys, warnings
+sys.path.insert(0, {ROOT!r})
+import paper_2411_15707_amd as nc
+from paper_2411_15707_amd import binding
+{missing}
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    nc.load_library()
+assert any("ctypes" in str(w.message) for w in seen), seen
+assert nc.nimbus_cop_packed_count(8, 64, 1024) == 1
+for name in {sorted(_arguments())!r}:
+    assert getattr(binding._calls, name)() is None
+import torch
+try:
+    nc.nimbus_cop_prepare(torch.zeros(4096, dtype=torch.int64), 64, 32, 32, 1, ({ci_prime()},), torch.zeros(1 << 20, dtype=torch.uint8))
+except ValueError as e:
+    assert "on the GPU" in str(e)
+else:
+    raise AssertionError("host memory accepted")
+"""
+    done = subprocess.run([sys.executable, "-c", code], capture_output=True, text=True, timeout=300)
+    assert done.returncode == 0, done.stderr
+
+
+def test_the_native_module_is_there():
+    """built with the library, for this interpreter and this torch"""
+    import torch
+    nc.load_library()
+    assert not isinstance(binding._calls, binding._NoCalls)
+    assert binding._calls.torch_version == torch.__version__
