@@ -17,6 +17,12 @@ SHAPES = [
     (97, 700, 96, 32, 1, 24, 62, 1, 8), (128, 1000, 320, 64, 1, 20, 54, 1, 8), (200, 600, 160, 32, 1, 32, 62, 1, 8),
     (40, 520, 2048, 1024, 1, 16, 62, 1, 4), (70, 1600, 1536, 128, 1, 20, 54, 1, 2), (513, 512, 32, 32, 1, 9, 40, 1, 8),
     (50, 640, 64, 64, 1, 20, 54, 3, 8),
+    # seven to nine k-blocks: slices of one stage and of two, the last k-block alone in its stage or short of
+    # rows, a last row tile of one row to 32, columns that are not whole groups of a workgroup, batches
+    (33, 221, 127, 128, 2, 20, 54, 3, 4), (34, 215, 300, 512, 2, 20, 54, 1, 4), (63, 193, 707, 512, 1, 32, 54, 1, 4),
+    (64, 224, 64, 32, 1, 16, 50, 1, 4), (65, 225, 128, 512, 2, 24, 40, 1, 4), (97, 248, 131, 512, 1, 20, 62, 1, 4),
+    (128, 256, 29, 256, 1, 32, 54, 1, 4), (130, 257, 160, 32, 1, 32, 62, 1, 4), (161, 275, 23, 128, 1, 24, 40, 1, 4),
+    (193, 255, 121, 128, 1, 9, 54, 2, 4), (255, 288, 30, 128, 1, 32, 54, 2, 4), (48, 283, 35, 64, 2, 20, 62, 2, 4),
 ]
 
 
