@@ -63,18 +63,20 @@ PHASE_SHAPES = [
     (128, 3, 55, 2),         # three limbs
     (256, 1, 30, 3),         # small modulus
     (512, 4, 40, 2),         # four limbs, 2 + 2 + 2 + 2 + 1
-    (1024, 1, 50, 8),        # config 1 ring
+    (1024, 1, 50, 8),        # config 1 ring; rings of 1024 to 8192 with moduli from 2^34 to 2^59 take the kernel
+                             # whose transform stops two stages early (test_gpu_product.py has its ends)
     (2048, 2, 62, 3),        # widest moduli
-    (4096, 2, 54, 7),        # BERT-base ring: six rounds of 2 stages, 1024 threads
-    (8192, 3, 55, 3),        # config 5 ring: 3 + 3 + 3 + 2 + 2
+    (4096, 2, 54, 7),        # BERT-base ring: 2 stages a round, 1024 threads
+    (8192, 3, 55, 3),        # config 5 ring: 1 + 3 + 3 + 3 + 3, the last two stages left out
     (16384, 1, 61, 2),       # largest ring: 136 KiB of LDS, 4 + 4 + 3 + 3
-    # the stages per round follow the ring degree and the batch size: batches of 1024
+    # the stages per round follow the ring degree and the batch size: of the full transform batches of 1024
     # polynomials and more take min(4, log N - 8) stages per round (256 threads each), smaller
-    # ones (all shapes above) min(4, log N - 10) but at least 2 (up to 1024 threads each)
+    # ones (all shapes above) min(4, log N - 10) but at least 2 (up to 1024 threads each); of the
+    # other one up to 256 polynomials, fewer than 1024 and more are apart
     (256, 2, 54, 600),       # 1200 polynomials, 2 stages per round
-    (2048, 1, 50, 1100),     # 3 stages per round: 3 + 3 + 3 + 2
+    (2048, 1, 50, 1100),     # 3 stages per round: 2 + 3 + 3 + 3
     (4096, 2, 54, 512),      # BERT-base ring, 1024 polynomials: 4 + 4 + 4
-    (8192, 3, 55, 350),      # config 5 ring, 1050 polynomials: 4 + 3 + 3 + 3
+    (8192, 3, 55, 350),      # config 5 ring, 1050 polynomials: the rounds of the small batch
     (16384, 2, 61, 520),     # largest ring, 4 + 4 + 3 + 3, two groups per thread and round
     (1024, 1, 50, 1100),     # config 1 ring in a large batch: 2 stages per round
     (32768, 2, 54, 2),       # ring that does not fit the LDS: two halves and a joining pass
@@ -88,7 +90,7 @@ PHASE_SHAPES = [
     (32768, 1, 59, 2),       # ... a stage on the way in and 14 in the LDS: 31 q in a word
     (2048, 1, 60, 3),        # just above: conditional subtractions
     (4096, 2, 58, 512),      # largest moduli of the range: least room, 4 + 4 + 4
-    (8192, 2, 58, 3),        # 3 + 3 + 3 + 2 + 2
+    (8192, 2, 58, 3),        # 1 + 3 + 3 + 3 + 3
     (16384, 1, 58, 2),       # 14 stages
     (16384, 2, 58, 520),     # two groups per thread and round
     (32768, 1, 58, 2),       # a stage on the way in, 14 in the LDS
@@ -153,7 +155,7 @@ def test_phase_with_extreme_residues(oracle, N, q_bits):
 
 def test_phase_with_the_moduli_of_the_64_bit_setting(oracle):
     """N = 8192 with one 59-bit and one 55-bit limb (Section 5, experimental setup): the limbs of
-    one call take the same kernel, the one the wider modulus allows; small and large batch"""
+    one call take the same kernel, the one the wider modulus allows; few and many polynomials"""
     N = 8192
     moduli = (ci.limb_primes(59, 14, 1)[0], ci.limb_primes(55, 14, 1)[0])
     assert [q.bit_length() for q in moduli] == [59, 55]
