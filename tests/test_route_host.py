@@ -91,10 +91,12 @@ def kernels(lines):
     return [LINE.match(x).group(1) for x in lines]
 
 
-# m, k, C, x_bits, problems, and the kernel from staged shares (measured on 256 compute units, us, the
-# kernel for few rows / the tiles: 9.3 / 4.3, 12.1 / 4.9, 8.7 / 5.0, 13.0 / 5.6, 36.1 / 19.5, 48.8 / 25.8,
-# 28.9 / 17.5, 12.2 / 8.7, 12.9 / 5.7, 370 / 199, 10.7 / 8.3, 17.5 / 15.5, 19.7 / 16.9, 20.2 / 17.2;
-# 30.8 / 38.5, 9.8 / 10.0, 98.1 / 134.0, 33.6 / 44.5)
+# m, k, C, x_bits, problems, and the kernel from staged shares (us on 256 compute units, the kernel for few rows /
+# the tiles, 54-bit moduli: 5.1 / 4.4, 7.8 / 4.8, 4.7 / 5.0, 9.1 / 5.9, 20.2 / 19.7, 32.4 / 26.3, 23.2 / 17.7, 9.2 / 9.1,
+# 8.9 / 5.8, 253 / 197, 6.9 / 8.5, 16.7 / 15.5, 18.7 / 17.7, 19.0 / 18.0; 30.3 / 38.5, 7.9 / 10.3, 89.7 / 75.8,
+# 31.6 / 42.5).  Held is what the rule chooses: the faster one but for 1 x 128 x 256 and 16 x 64 x 20480, which its
+# margin for a single call of up to 16 rows leaves with the tiles, and 32 x 2032 x 16384 twice, where both
+# estimates are off (62-bit moduli, an older tile kernel: 98.1 / 134.0).
 @pytest.mark.parametrize("m,k,C,x_bits,count,kernel", [
     (16, 32, 4096, 20, 1, "cop_mfma_kernel"), (32, 32, 4096, 20, 1, "cop_mfma_kernel"),
     (1, 128, 256, 20, 1, "cop_mfma_kernel"), (32, 64, 8192, 20, 1, "cop_mfma_kernel"),
@@ -107,11 +109,27 @@ def kernels(lines):
     (32, 512, 4096, 20, 1, "cop_thin_kernel"), (32, 2032, 16384, 32, 2, "cop_thin_kernel"),
     (4, 2097, 2944, 32, 3, "cop_thin_kernel"),
 ])
-def test_few_rows_take_the_faster_kernel(m, k, C, x_bits, count, kernel):
+def test_which_kernel_few_rows_take(m, k, C, x_bits, count, kernel):
     n = C // 4                                      # (two limbs)
     N = min(4096, n & -n)                           # the power of two in it
     lines = nc.nimbus_route_matmul(m, k, x_bits, n, N, 2, moduli_of(54, 2), staged=True, count=count, units=256)
     assert kernels(lines) == [kernel]
+
+
+# 33 rows and more on few columns, k-blocks and the kernel (us, the kernel for few rows / the tiles, 54-bit moduli, 64 x
+# 1024 columns and 20-bit shares by k-blocks: 6.3 / 7.0, 6.9 / 7.5, 6.9 / 7.7, 6.4 / 8.8, 6.3 / 9.1, 6.9 / 9.6, 6.5 / 9.8;
+# 256 x 2048 and 32-bit shares: 10.0 / 11.0, 10.7 / 11.7).  Under five k-blocks always the tiles, from five to nine only
+# where this kernel is well ahead by the estimates
+@pytest.mark.parametrize("m,C,x_bits,kernels_at", [
+    (64, 1024, 20, {1: "mfma", 4: "mfma", 5: "mfma", 6: "mfma", 7: "thin", 8: "thin", 9: "mfma", 10: "thin", 11: "thin"}),
+    (256, 2048, 32, {8: "mfma", 9: "mfma", 10: "thin"}),
+    (128, 256, 32, {4: "mfma", 7: "thin", 9: "thin", 10: "thin"}),
+])
+def test_which_kernel_more_rows_take_by_k_blocks(m, C, x_bits, kernels_at):
+    for k_blocks, kernel in kernels_at.items():
+        for k in (32 * k_blocks - 31, 32 * k_blocks):
+            lines = nc.nimbus_route_matmul(m, k, x_bits, C // 2, C // 2, 1, moduli_of(54, 1), staged=True, units=256)
+            assert kernels(lines) == [f"cop_{kernel}_kernel"], (k_blocks, k)
 
 
 # 17 to 32 rows from the shares themselves: split in the kernel, or staged and one kernel or the other (us, split
