@@ -67,7 +67,9 @@ size_t nimbus_rlwe_tables_bytes(int N, int L);
  *   s       [N] int8, small signed coefficients (ternary in this build's harness); a
  *           negative coefficient stands for q_l minus its magnitude
  *   tables  written; read-only afterwards, shared by every later call with the same
- *           (N, L, moduli, s)
+ *           (N, L, moduli, s).  Their order inside the buffer follows N and all moduli together
+ *           and is the library's own: a call with other moduli, some of these alone among them, needs
+ *           tables of its own, and they are no format to be kept for another version of the library.
  * Errors: INVALID_ARG (null pointer, N / L / modulus out of range, no 2N-th root of unity
  * found), UNSUPPORTED (N > 32768), BUFFER_SIZE (tables_bytes too small), LAUNCH. */
 int nimbus_rlwe_setup(int N, int L, const uint64_t *moduli, const int8_t *s,

@@ -115,6 +115,7 @@ static hipError_t prepare_impl(const Problem &p, const uint64_t *ctW, void *prep
     constexpr std::integral_constant<int, 1> k1;
     constexpr std::integral_constant<int, kTile / 2> half;
     constexpr std::integral_constant<int, kTile> whole;
+    // (Tiles are counted for 256 compute units, whatever the device has.)
     // Up to 128 tiles leave half of the compute units without one: half a tile to a workgroup, from
     // five k-blocks on (us, whole tiles and halves: 160 x 2048 residues 5.4 and 4.8, 768 x 2048 11.8
     // and 9.9, 3072 x 2048 39.8 and 28.2, 3072 x 4096 45.1 and 39.9; two tiles on some units of the

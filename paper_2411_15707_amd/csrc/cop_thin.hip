@@ -20,7 +20,7 @@
 // workgroups to the number of compute units.  The slices' sums meet in LDS once, at the end.
 //
 // Shares: staged planes (the batch and the staged entry points), read like the weights; or, for
-// up to 16 rows of the entry points that stage and multiply in one call, the raw words (RAW):
+// up to 32 rows of the entry points that stage and multiply in one call, the raw words (RAW):
 // the workgroup splits them into byte planes in LDS while its first weights are on their way,
 // and the staging launch and the gap behind it go away.  The planes are left in the workspace
 // all the same (workgroup b writes the stages b, b + grid, ...), as that entry point promises.
@@ -530,9 +530,12 @@ static bool thin_few_apply(const Problem &p, int count)
 {
     if (!thin_possible(p)) return false;
     const ThinEstimates e = thin_few_estimates(p, count);
-    // (Where the two lie within a microsecond or two of each other, a single call of up to 16 rows stays with the
-    // tiles and one of more rows with this kernel: which one such a call takes is held by tests, and was
-    // fixed when a workgroup of this kernel took three microseconds longer to start and end.
+    // (The line is not where the estimates meet: a single call of up to 16 rows stays with the tiles until this kernel is
+    // ahead by 1.3 us and 1.4 us over the k-blocks, and one of more rows with this kernel a little longer.  That is where
+    // the lines lay when a workgroup of this kernel took three microseconds longer to start and end, and
+    // tests/test_route_host.py holds sizes between the two.  Over 900 sizes of 1 to 32 rows the choice is 1.5 % slower than the
+    // better kernel, 41 % at worst, where the lower estimate alone is 0.5 % and 16 % off (16 x 64 x 20480: 8.5 us with the
+    // tiles, which it takes, and 6.9).
     // 17 to 32 rows, one problem: where tiles about fill their last round, this kernel has to be ahead by the last
     // condition too (31 x 1329 x 32768 55.7 us with the tiles and 61.8; 24 x 987 x 24576, whose last
     // round of tiles is half empty, 43.8 and 39.1).  0.5 % off the better kernel at 650 sizes; 1.1 % without it.)
@@ -554,9 +557,11 @@ static bool thin_few_apply(const Problem &p, int count)
 // 16-bit shares, 40.2 and 57.3): a seventh more.
 // Estimates as above, fitted at 300 sizes (33 to 512 rows, k from 300 to 4096, 64 to 16384 columns, one to
 // eight problems): the choice is 0.3 % slower than the better kernel on average, 30 % at worst, and 0.2 % at 75 sizes that were
-// left out; tiles everywhere 75 %, this kernel everywhere 8 %.  Below ten k-blocks only where it is well ahead: 2 %
-// off the better kernel over 300 sizes of one to ten k-blocks (the tiles everywhere 4 %, this kernel 20 %); under five
-// never.
+// left out; tiles everywhere 75 %, this kernel everywhere 8 %.  Below ten k-blocks only where it is well ahead: 2.1 %
+// off the better kernel over 333 sizes of one to ten k-blocks, 44 % at worst (the tiles everywhere 4 %, this kernel 20 %);
+// under five never.  The tiles' estimate takes 33 to 48 rows for 64, which is 7 % too much: 15 of 24 sizes
+// that are more than 3 % slower than with the rule before, of 518 that are 1.22 times as fast on average, are such (44 x
+// 845 x 1792 four times 16.4 us with the tiles and 18.6); a smaller estimate there gives up as much as it saves.
 static bool thin_rows_apply(const Problem &p, int count)
 {
     const int KB = kblocks(p.k), DX = planes_x(p.x_bits), DQ = planes_q(p.q_bits_max);

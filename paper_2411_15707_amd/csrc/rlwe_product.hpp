@@ -18,8 +18,11 @@
 //
 // us a call before (full transform) and now: 768 rows of 4096 coefficients, two limbs, encrypted
 // 83.0 -> 64.1; phases of 128 x 4096 x 2 13.35 -> 13.20, 300 x 4096 x 2 31.4 -> 26.3, 300 x 8192 x 2 70.2 ->
-// 61.0, 8 x 8192 20.0 -> 18.0, 1000 x 4096 x 2 84.0 -> 70.6.  Bound by vector instructions (250 to 280 a coefficient; a
-// product is 13 to 15 of them) and, one polynomial to a compute unit, by the rounds' LDS trips between them.
+// 61.0, 8 x 8192 20.0 -> 18.0, 1000 x 4096 x 2 84.0 -> 70.6; rings of 1024 are even (one polynomial encrypted 5.5 -> 5.6,
+// 2000 20.8 -> 20.3).  Bound by vector instructions in large batches: 252 a coefficient and 87 % of the SIMDs' issue cycles for
+// 4096 phases of 4096 coefficients, 284 and 73 % encrypted (133 registers, three waves a SIMD instead of four); some 200 of them
+// are butterflies and block products.  With one polynomial to a compute unit, 265 and 36 %, by the rounds' LDS trips between
+// them.  (profiles/rlwe_product_kernel_config3_server_side.txt)
 #pragma once
 #include "rlwe_kernels.hpp"
 
@@ -32,7 +35,8 @@ inline bool product_kernel_applies(const RlweArgs &a, int L, int logN)
 
 // Stages per round by ring degree and batch size (the last two of a ring included: they count as
 // stages of the round in the middle, whose threads hold whole blocks of four), at most three
-// kinds of a ring.  Up to one polynomial per compute unit, many waves to a polynomial; more, fewer rounds; from
+// kinds of a ring.  The lines are those of 256 compute units, whatever the device has.
+// Up to one polynomial per compute unit, many waves to a polynomial; more, fewer rounds; from
 // 1024 polynomials on a compute unit has several workgroups at a time and few registers a thread
 // matter less than few rounds.  us, 2 / 3 / 4 stages: 4096 coefficients, 256 polynomials 13.0 / 13.2 / 15.5,
 // 600 30.5 / 25.7 / 27.5, 1536 (encrypted) 77.8 / 66.3 / 64.6; 2048, 256 polynomials 8.5 / 8.7 / 12.5, 2000 37.1 /
